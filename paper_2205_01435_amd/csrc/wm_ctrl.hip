@@ -1,0 +1,853 @@
+// The controller of the per-step path and the standalone controller step.
+#include <hip/hip_runtime.h>
+#include <math.h>
+#include <stdint.h>
+
+#include <algorithm>
+#include <type_traits>
+
+#include "wm_device.h"
+#include "wm_gemm.h"
+#include "wm_kernels.h"
+#include "wm_profile.h"
+#include "wm_steps.h"
+
+namespace wm {
+
+// ===========================================================================
+// k_ctrl: controller logits for BM = 16*MBW rows (all Nc outputs in one
+// block; four waves take interleaved 16-output slices), weights read
+// straight from global memory, activations staged through LDS in K chunks.
+//   mode 0: controller step (probs + action)
+//   mode 1: rollout step t: resolve transition t-1, choose a_t
+//   mode 2: rollout tail: resolve transition T-1 only
+// ===========================================================================
+// Rollout bookkeeping of row m at step t (modes 1 and 2 of the controller
+// kernels).  First the previous transition t-1 is resolved if the row was
+// live then: its reward is the reward head on h_t and it is done when
+// sigmoid(done head) exceeds the stream-3 uniform of step t-1.  Then (mode 1)
+// the row takes action `a` (the masked Gumbel-max, -1 if no action is valid)
+// or, if done, the frozen outputs; a row without a valid action ends here.
+// A step past the row's horizon is padding: no action, reward 0, done 0 (its
+// state is kept like a frozen row's; the latent is zeroed afterwards).
+__device__ __forceinline__ void ctrl_row_commit(const CtrlArgs& p, const Rng& rng, int m, int a,
+                                                float rr, float rd) {
+  int ds = p.done_state[m];
+  if (p.act_prev && p.act_prev[m] >= 0) {
+    p.rew_prev[m] = rr;
+    int d = 0;
+    if (p.use_done) {
+      const uint4 w = rng.block(0, p.step - 1u, p.traj0 + (uint32_t)m, STREAM_DONE);
+      d = sigmoidf(rd) > word_to_uniform(w.x);
+    }
+    p.done_prev[m] = (uint8_t)d;
+    if (d) ds = 1;
+  }
+  if (p.mode == 1) {
+    const bool pad = p.lengths && p.t >= p.lengths[m];
+    if (ds || pad) a = -1;
+    else if (a < 0) ds = 1;
+    p.act_t[m] = a;
+    if (a < 0) {
+      p.rew_t[m] = 0.f;
+      p.done_t[m] = pad ? 0 : 1;
+    }
+  }
+  p.done_state[m] = ds;
+}
+
+// Two-level pick of row m (section 3.1.3) by its TPR threads (thread q of
+// the row), from its logits lg (bias not yet added): an xfer among the valid
+// ones (stream 0, index x; x = N is the NO-OP), then a location valid for
+// that xfer (stream 4, index l).  two_level_xfer returns x (-1 when none is
+// valid), two_level_loc the location of xfer x < N (-1 when none is valid),
+// two_level_pick the flat action x Lc + l, -2 for the NO-OP, -1 when nothing
+// is valid; the same value in every thread of the row.  Ties go to the
+// lowest index.  LMAX bounds Lc.
+template <int TPR>
+__device__ __forceinline__ void row_argmax(float& best, int& bidx) {
+#pragma unroll
+  for (int off = 1; off < TPR; off <<= 1) {
+    const float ob = __shfl_xor(best, off);
+    const int oi = __shfl_xor(bidx, off);
+    if (oi >= 0 && (bidx < 0 || ob > best || (ob == best && oi < bidx))) { best = ob; bidx = oi; }
+  }
+}
+
+template <int TPR>
+__device__ __forceinline__ int two_level_xfer(const CtrlArgs& p, const Rng& rng, const float* lg, int m,
+                                              bool on, int q, uint32_t traj) {
+  const int NX = p.N + 1;
+  float best = -INFINITY;
+  int x = -1;
+  if (on) {
+    for (int i = q; i < NX; i += TPR) {
+      if (!p.mask[(long)m * NX + i]) continue;
+      const uint4 w = rng.block((uint32_t)i >> 2, p.step, traj, STREAM_CONTROLLER);
+      const float sc = lg[i] + p.bc[i] + gumbel(word_to_uniform(word_of(w, i & 3)));
+      if (sc > best) { best = sc; x = i; }
+    }
+  }
+  row_argmax<TPR>(best, x);
+  return x;
+}
+
+template <int TPR, int LMAX>
+__device__ __forceinline__ int two_level_loc(const CtrlArgs& p, const Rng& rng, const float* lg, int m,
+                                             bool on, int q, uint32_t traj, int x) {
+  const int N = p.N, NX = N + 1, Lc = p.Lc;
+  const uint8_t* lm = p.mask + (long)p.M * NX + ((long)m * N + x) * Lc;
+  // thread q takes the contiguous locations [l0, l1) (a multiple of four:
+  // one Philox block each); their mask bytes are all loaded before the
+  // first is used, instead of one dependent load per location
+  constexpr int MAXW = (((LMAX + TPR - 1) / TPR + 3) & ~3) / 4;
+  const int cpt = ((Lc + TPR - 1) / TPR + 3) & ~3;
+  const int l0 = q * cpt, l1 = min(l0 + cpt, Lc);
+  uint32_t mw[MAXW];
+#pragma unroll
+  for (int k = 0; k < MAXW; ++k) {
+    uint32_t wv = 0;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int i = l0 + 4 * k + v;
+      if (on && i < l1 && lm[i]) wv |= 1u << (8 * v);
+    }
+    mw[k] = wv;
+  }
+  float best = -INFINITY;
+  int l = -1;
+#pragma unroll
+  for (int k = 0; k < MAXW; ++k) {
+    if (mw[k] == 0) continue;
+    const int b = l0 + 4 * k;
+    const uint4 w = rng.block((uint32_t)b >> 2, p.step, traj, STREAM_LOCATION);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      if ((mw[k] >> (8 * v)) & 1u) {
+        const float sc = lg[NX + b + v] + p.bc[NX + b + v] + gumbel(word_to_uniform(word_of(w, v)));
+        if (sc > best) { best = sc; l = b + v; }
+      }
+    }
+  }
+  row_argmax<TPR>(best, l);
+  return l;
+}
+
+template <int TPR, int LMAX = 316>
+__device__ __forceinline__ int two_level_pick(const CtrlArgs& p, const Rng& rng, const float* lg,
+                                              int m, bool on, int q, uint32_t traj) {
+  const int x = two_level_xfer<TPR>(p, rng, lg, m, on, q, traj);
+  if (x < 0) return -1;
+  if (x == p.N) return -2;
+  const int l = two_level_loc<TPR, LMAX>(p, rng, lg, m, on, q, traj, x);
+  return l < 0 ? -1 : x * p.Lc + l;
+}
+
+// The two-level controller from stored logits (k_ctrl_wide with logits_out),
+// one wave per row, for controllers too wide for the staged tiles and for
+// the controller step.  Rollout modes: the pick and the row's commit (the
+// reward and done logits are columns Ac, Ac + 1).  Mode 0: the action and,
+// over the row's logits in place, the probabilities: the softmax of the
+// valid xfers' logits [N+1], then the softmax of the valid locations of the
+// picked xfer [Lc] (0 after a NO-OP or when nothing is valid).
+constexpr int kRowsMax = 1024;  // N + 1 and Lc at most this
+__global__ void __launch_bounds__(256) k_ctrl_rows(const CtrlArgs p) {
+  const int lane = threadIdx.x & 63;
+  const int m = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (m >= p.M) return;  // the whole wave
+  float* lg = p.logits_out + (long)m * p.ldl;
+  const Rng rng{p.k0, p.k1};
+  const uint32_t traj = p.traj0 + (uint32_t)m;
+  const int N = p.N, NX = N + 1, Lc = p.Lc;
+  if (p.mode != 0) {
+    int a = -1;
+    if (p.mode == 1) {
+      const int x = two_level_xfer<64>(p, rng, lg, m, true, lane, traj);
+      if (x == N) a = -2;
+      else if (x >= 0) {
+        const int l = two_level_loc<64, kRowsMax>(p, rng, lg, m, true, lane, traj, x);
+        a = l < 0 ? -1 : x * Lc + l;
+      }
+    }
+    const int Ar = NX + Lc;
+    if (lane == 0) ctrl_row_commit(p, rng, m, a, lg[Ar] + p.bc[Ar], lg[Ar + 1] + p.bc[Ar + 1]);
+    return;
+  }
+  const int x = two_level_xfer<64>(p, rng, lg, m, true, lane, traj);
+  const bool locs = x >= 0 && x < N;
+  const int l = locs ? two_level_loc<64, kRowsMax>(p, rng, lg, m, true, lane, traj, x) : -1;
+  const int a = x < 0 ? -1 : x == N ? -2 : l < 0 ? -1 : x * Lc + l;
+  // every logit this lane needs, read before any probability is written
+  constexpr int PER = kRowsMax / 64;
+  const uint8_t* lm = p.mask + (long)p.M * NX + ((long)m * N + (locs ? x : 0)) * Lc;
+  float vx[PER], vl[PER];
+  float mxx = -INFINITY, mxl = -INFINITY;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int i = lane + 64 * k;
+    const bool okx = i < NX && p.mask[(long)m * NX + i];
+    vx[k] = okx ? lg[i] + p.bc[i] : -INFINITY;
+    mxx = fmaxf(mxx, vx[k]);
+    const bool okl = locs && i < Lc && lm[i];
+    vl[k] = okl ? lg[NX + i] + p.bc[NX + i] : -INFINITY;
+    mxl = fmaxf(mxl, vl[k]);
+  }
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    mxx = fmaxf(mxx, __shfl_xor(mxx, off));
+    mxl = fmaxf(mxl, __shfl_xor(mxl, off));
+  }
+  float sx = 0.f, sl = 0.f;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    vx[k] = vx[k] == -INFINITY ? 0.f : expf(vx[k] - mxx);
+    vl[k] = vl[k] == -INFINITY ? 0.f : expf(vl[k] - mxl);
+    sx += vx[k];
+    sl += vl[k];
+  }
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    sx += __shfl_xor(sx, off);
+    sl += __shfl_xor(sl, off);
+  }
+  const float ix = sx > 0.f ? 1.0f / sx : 0.f, il = sl > 0.f ? 1.0f / sl : 0.f;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int i = lane + 64 * k;
+    if (i < NX) lg[i] = vx[k] * ix;
+    if (i < Lc) lg[NX + i] = vl[k] * il;
+  }
+  if (lane == 0) p.action[m] = a;
+}
+
+// Activation source of the controller kernels for rows m0 .. m0+rows-1.
+template <class S>
+__device__ __forceinline__ S ctrl_src(const CtrlArgs& p, int m0, int rows) {
+  using DT = typename S::DT;
+  if constexpr (S::kTwo) return S(p.z, p.h, p.Z, p.H, m0, rows, p.M);
+  else return S(reinterpret_cast<const DT*>(p.x), p.ldx, p.ldx, m0, rows, p.M);
+}
+
+template <class S, int NBW, int MBW, int BKC>
+__global__ void __launch_bounds__(256) k_ctrl_wide(const CtrlArgs p) {
+  using DT = typename S::DT;
+  constexpr int VEC = DType<DT>::VEC;
+  constexpr int BM = 16 * MBW;
+  constexpr int LDL = BKC + 2 * VEC;
+  __shared__ __attribute__((aligned(16))) DT xl[BM * LDL];
+  __shared__ float s_best[4][BM];
+  __shared__ int s_idx[4][BM];
+  __shared__ float s_max[4][BM];
+  __shared__ float s_rho[BM][2];
+  __shared__ float s_fin[BM][2];
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int g = lane >> 4, r16 = lane & 15;
+  const int m0 = blockIdx.x * BM;
+  const int nbtot = p.Nc / 16;
+  const DT* W = reinterpret_cast<const DT*>(p.Wc);
+  const S src = ctrl_src<S>(p, m0, BM);
+
+  f32x4 acc[NBW][MBW];
+#pragma unroll
+  for (int i = 0; i < NBW; ++i)
+#pragma unroll
+    for (int j = 0; j < MBW; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  for (int kc = 0; kc < (int)p.ldk; kc += BKC) {
+    __syncthreads();
+    for (int v = tid; v < BM * (BKC / VEC); v += 256) {
+      const int r = v / (BKC / VEC), kv = v % (BKC / VEC);
+      *reinterpret_cast<uint4*>(xl + r * LDL + kv * VEC) = src.load(src.row(r), kc + kv * VEC, (int)p.ldk);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int ks = 0; ks < BKC; ks += Mfma<DT>::KSLICE) {
+      if (kc + ks >= (int)p.ldk) break;  // last chunk may overhang the padded K
+      // the slice's weight fragments are loaded in groups of GW, one group
+      // ahead of its MFMAs, from rows clamped into the matrix (blocks past
+      // nbtot are loaded but not used). Unguarded loads let each MFMA wait
+      // for its own fragment only; under the guard it waited for all of them.
+      constexpr int GW = 8, NG = (NBW + GW - 1) / GW;
+      uint4 a[2][GW];
+      auto load_group = [&](int gi, uint4(&dst)[GW]) {
+#pragma unroll
+        for (int q = 0; q < GW; ++q) {
+          const int i = gi * GW + q;
+          if (i < NBW) {
+            const int nb = min(wave + 4 * i, nbtot - 1);
+            dst[q] = *reinterpret_cast<const uint4*>(W + (long)(nb * 16 + r16) * p.ldk + kc + ks + g * VEC);
+          }
+        }
+      };
+      load_group(0, a[0]);
+      uint4 b[MBW];
+#pragma unroll
+      for (int j = 0; j < MBW; ++j)
+        b[j] = *reinterpret_cast<const uint4*>(xl + (j * 16 + r16) * LDL + ks + g * VEC);
+#pragma unroll
+      for (int gi = 0; gi < NG; ++gi) {
+        if (gi + 1 < NG) load_group(gi + 1, a[(gi + 1) & 1]);
+#pragma unroll
+        for (int q = 0; q < GW; ++q) {
+          const int i = gi * GW + q;
+          if (i < NBW && wave + 4 * i < nbtot) {
+#pragma unroll
+            for (int j = 0; j < MBW; ++j) Mfma<DT>::step(acc[i][j], a[gi & 1][q], b[j]);
+          }
+        }
+      }
+    }
+  }
+
+  // ---- epilogue ----
+  if (p.logits_out) {  // logits only (bias not added); k_ctrl_rows picks
+#pragma unroll
+    for (int j = 0; j < MBW; ++j) {
+      const int m = m0 + j * 16 + r16;
+      if (m >= p.M) continue;
+#pragma unroll
+      for (int i = 0; i < NBW; ++i) {
+        const int nb = wave + 4 * i;
+        const int n = nb * 16 + 4 * g;
+        if (nb >= nbtot) continue;
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          if (n + v < p.ncol) p.logits_out[(long)m * p.ldl + n + v] = acc[i][j][v];
+      }
+    }
+    return;
+  }
+  const Rng rng{p.k0, p.k1};
+  const int A = p.A;
+  const bool want_action = p.mode != 2;
+  // the mask bytes of this lane's actions (n .. n+3 of each block, each
+  // row), all loaded before the first is used
+  uint32_t mk[NBW][MBW];
+#pragma unroll
+  for (int j = 0; j < MBW; ++j) {
+    const int m = m0 + j * 16 + r16;
+#pragma unroll
+    for (int i = 0; i < NBW; ++i) {
+      const int n = (wave + 4 * i) * 16 + 4 * g;
+      uint32_t wv = 0;
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        if (m < p.M && wave + 4 * i < nbtot && n + v < A && p.mask[(long)m * A + n + v]) wv |= 1u << (8 * v);
+      mk[i][j] = wv;
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < MBW; ++j) {
+    const int ml = j * 16 + r16;
+    const int m = m0 + ml;
+    float best = -INFINITY, mx = -INFINITY;
+    int bidx = -1;
+    if (m < p.M) {
+#pragma unroll
+      for (int i = 0; i < NBW; ++i) {
+        const int nb = wave + 4 * i;
+        if (nb >= nbtot) continue;
+        const int n = nb * 16 + 4 * g;
+        const float4 b4 = *reinterpret_cast<const float4*>(p.bc + n);
+        const float lg[4] = {acc[i][j][0] + b4.x, acc[i][j][1] + b4.y, acc[i][j][2] + b4.z,
+                             acc[i][j][3] + b4.w};
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          if (n + v == A) s_rho[ml][0] = lg[v];
+          if (n + v == A + 1) s_rho[ml][1] = lg[v];
+        }
+        if (want_action && n < A) {
+          const uint4 w = rng.block((uint32_t)(n >> 2), p.step, p.traj0 + (uint32_t)m, STREAM_CONTROLLER);
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            if ((mk[i][j] >> (8 * v)) & 1u) {
+              mx = fmaxf(mx, lg[v]);
+              const float s = lg[v] + gumbel(word_to_uniform(word_of(w, v)));
+              if (s > best) { best = s; bidx = n + v; }
+            }
+          }
+        }
+      }
+    }
+    // reduce over the four lane groups (same row), lowest index on ties
+#pragma unroll
+    for (int off = 16; off <= 32; off <<= 1) {
+      const float ob = __shfl_xor(best, off);
+      const int oi = __shfl_xor(bidx, off);
+      const float om = __shfl_xor(mx, off);
+      if (oi >= 0 && (bidx < 0 || ob > best || (ob == best && oi < bidx))) { best = ob; bidx = oi; }
+      mx = fmaxf(mx, om);
+    }
+    if (g == 0) {
+      s_best[wave][ml] = best;
+      s_idx[wave][ml] = bidx;
+      s_max[wave][ml] = mx;
+    }
+  }
+  __syncthreads();
+
+  if (p.mode == 0) {
+    // combine waves; then probabilities
+    if (tid < BM) {
+      float best = -INFINITY, mx = -INFINITY;
+      int bidx = -1;
+      for (int w = 0; w < 4; ++w) {
+        const float ob = s_best[w][tid];
+        const int oi = s_idx[w][tid];
+        if (oi >= 0 && (bidx < 0 || ob > best || (ob == best && oi < bidx))) { best = ob; bidx = oi; }
+        mx = fmaxf(mx, s_max[w][tid]);
+      }
+      s_fin[tid][0] = mx;
+      const int m = m0 + tid;
+      if (m < p.M) p.action[m] = bidx;
+    }
+    __syncthreads();
+    if (p.probs) {
+      // sum of exp(l - max) over valid actions
+#pragma unroll
+      for (int j = 0; j < MBW; ++j) {
+        const int ml = j * 16 + r16;
+        const int m = m0 + ml;
+        float se = 0.f;
+        if (m < p.M) {
+          const float mx = s_fin[ml][0];
+#pragma unroll
+          for (int i = 0; i < NBW; ++i) {
+            const int nb = wave + 4 * i;
+            if (nb >= nbtot) continue;
+            const int n = nb * 16 + 4 * g;
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+              if ((mk[i][j] >> (8 * v)) & 1u) se += expf(acc[i][j][v] + p.bc[n + v] - mx);
+          }
+        }
+        se += __shfl_xor(se, 16);
+        se += __shfl_xor(se, 32);
+        if (g == 0) s_best[wave][ml] = se;
+      }
+      __syncthreads();
+      if (tid < BM) s_fin[tid][1] = s_best[0][tid] + s_best[1][tid] + s_best[2][tid] + s_best[3][tid];
+      __syncthreads();
+#pragma unroll
+      for (int j = 0; j < MBW; ++j) {
+        const int ml = j * 16 + r16;
+        const int m = m0 + ml;
+        if (m >= p.M) continue;
+        const float mx = s_fin[ml][0], inv = s_fin[ml][1] > 0.f ? 1.0f / s_fin[ml][1] : 0.f;
+#pragma unroll
+        for (int i = 0; i < NBW; ++i) {
+          const int nb = wave + 4 * i;
+          if (nb >= nbtot) continue;
+          const int n = nb * 16 + 4 * g;
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            if (n + v < A) {
+              const bool ok = (mk[i][j] >> (8 * v)) & 1u;
+              p.probs[(long)m * A + n + v] = ok ? expf(acc[i][j][v] + p.bc[n + v] - mx) * inv : 0.f;
+            }
+          }
+        }
+      }
+    }
+    return;
+  }
+
+  // rollout modes: one thread per row
+  if (tid < BM) {
+    const int m = m0 + tid;
+    if (m < p.M) {
+      float best = -INFINITY;
+      int a = -1;
+      for (int w = 0; w < 4; ++w) {
+        const float ob = s_best[w][tid];
+        const int oi = s_idx[w][tid];
+        if (oi >= 0 && (a < 0 || ob > best || (ob == best && oi < a))) { best = ob; a = oi; }
+      }
+      ctrl_row_commit(p, rng, m, a, s_rho[tid][0], s_rho[tid][1]);
+    }
+  }
+}
+
+// k_ctrl: controller on the pipelined GEMM core for A + 2 <= 64 * NBW
+// outputs (all Nc weight rows of a row block in one tile).  The logit tile
+// is staged through LDS as E[row][output]; each row is then handled by TPR
+// adjacent threads, thread q taking the contiguous actions
+// [q * APT, (q + 1) * APT) (APT a multiple of 4: one Philox block per four
+// actions).  The mask bytes of those actions are fetched as 32-bit words
+// before the GEMM when A % 4 == 0 (byte loads otherwise).
+template <class C, class S>
+__global__ void __launch_bounds__(C::NT) k_ctrl(const CtrlArgs p) {
+  using DT = typename C::DT;
+  constexpr int NBW = C::NBW, MBW = C::MBW, BM = C::BM;
+  constexpr int TPR = C::NT / BM;               // threads per row
+  constexpr int MAXB = (C::BN / TPR + 3) / 4;  // Philox blocks per thread
+  constexpr int ELD = C::BN + 4;
+  constexpr int E_BYTES = BM * ELD * 4;
+  constexpr int LDS = C::LDS_BYTES > E_BYTES ? C::LDS_BYTES : E_BYTES;
+  static_assert(C::NT % BM == 0 && (TPR & (TPR - 1)) == 0 && TPR <= 16, "row groups inside a wave");
+  __shared__ __attribute__((aligned(16))) char lds_raw[LDS];
+
+  const int m0 = blockIdx.x * BM;
+  const int r = threadIdx.x / TPR, q = threadIdx.x % TPR;
+  const int m = m0 + r;
+  const bool row_ok = m < p.M;
+  const int A = p.A;
+  const int apt = (A + 4 * TPR - 1) / (4 * TPR) * 4;  // actions per thread
+  const int a0 = q * apt;
+  const bool want_action = p.mode != 2;
+
+  // mask words of this thread's actions, ahead of the GEMM
+  uint32_t mk[MAXB];
+  const rsrc_t rmask = make_rsrc(p.mask + (long)m0 * A, (uint32_t)(max(0, min(BM, p.M - m0)) * A));
+  const bool words = (A & 3) == 0 && (reinterpret_cast<uintptr_t>(p.mask) & 3) == 0;
+#pragma unroll
+  for (int b = 0; b < MAXB; ++b) {
+    const int a = a0 + 4 * b;
+    const bool ok = want_action && row_ok && p.N == 0 && 4 * b < apt && a < A;
+    const uint32_t off = (uint32_t)(r * A + a);
+    if (words) {
+      mk[b] = bload4(rmask, ok ? off : kOffNone);
+    } else {
+      mk[b] = 0;
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        mk[b] |= bload1(rmask, ok && a + v < A ? off + v : kOffNone) << (8 * v);
+    }
+  }
+
+  const Rng rng{p.k0, p.k1};
+  const uint32_t traj = p.traj0 + (uint32_t)m;
+  const bool flat_pick = want_action && row_ok && p.N == 0;
+  // On the sixteen-wave direct tile, the Gumbel noise of all of the thread's
+  // actions is drawn while the GEMM's first chunks load (it does not depend
+  // on the logits).  It is drawn whatever the mask: the mask words are still
+  // in flight there, and waiting for them would wait for the chunks too.
+  // (On the four-wave 32-row tiles of the large rollout the same draw made
+  // the controller slower, 12.0 -> 12.8 us per step.)
+  constexpr bool kPre = IsGemmD<C>::value && C::NT >= 1024 && MAXB <= 5;
+  float gq[kPre ? MAXB : 1][4];
+  auto draw = [&]() {
+    if constexpr (kPre) {
+#pragma unroll
+      for (int b = 0; b < MAXB; ++b) {
+        if (flat_pick && 4 * b < apt && a0 + 4 * b < A) {
+          const uint4 wd = rng.block((uint32_t)((a0 + 4 * b) >> 2), p.step, traj, STREAM_CONTROLLER);
+#pragma unroll
+          for (int v = 0; v < 4; ++v) gq[b][v] = gumbel(word_to_uniform(word_of(wd, v)));
+        }
+      }
+    }
+  };
+
+  f32x4 acc[NBW][MBW];
+  const SrcX<DT> w(reinterpret_cast<const DT*>(p.Wc), p.ldk, p.ldk, 0, p.Nc, p.Nc);
+  if constexpr (kPre)
+    C::run(acc, w, ctrl_src<S>(p, m0, BM), (int)p.ldk, reinterpret_cast<DT*>(lds_raw), draw);
+  else
+    C::run(acc, w, ctrl_src<S>(p, m0, BM), (int)p.ldk, reinterpret_cast<DT*>(lds_raw));
+  float* E = reinterpret_cast<float*>(lds_raw);
+  if (C::kw() == 0) {
+    const int lane = threadIdx.x & 63, r16 = lane & 15, g = lane >> 4;
+    const int wn = C::wn(), wmi = C::wm();
+#pragma unroll
+    for (int j = 0; j < MBW; ++j)
+#pragma unroll
+      for (int i = 0; i < NBW; ++i)
+        *reinterpret_cast<f32x4*>(E + ((wmi * MBW + j) * 16 + r16) * ELD + (wn * NBW + i) * 16 + 4 * g) =
+            acc[i][j];
+  }
+  __syncthreads();
+
+  const float* lg = E + r * ELD;
+  float best = -INFINITY, mx = -INFINITY;
+  int bidx = -1;
+  if (flat_pick) {
+#pragma unroll
+    for (int b = 0; b < MAXB; ++b) {
+      if (mk[b] == 0) continue;  // no valid action in the block (or outside the range)
+      const int a = a0 + 4 * b;
+      uint4 wd = make_uint4(0u, 0u, 0u, 0u);
+      if constexpr (!kPre) wd = rng.block((uint32_t)(a >> 2), p.step, traj, STREAM_CONTROLLER);
+      const float4 l4 = *reinterpret_cast<const float4*>(lg + a);
+      const float4 b4 = *reinterpret_cast<const float4*>(p.bc + a);
+      const float lv[4] = {l4.x + b4.x, l4.y + b4.y, l4.z + b4.z, l4.w + b4.w};
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        if ((mk[b] >> (8 * v)) & 0xffu) {
+          mx = fmaxf(mx, lv[v]);
+          float gv;
+          if constexpr (kPre) gv = gq[b][v];
+          else gv = gumbel(word_to_uniform(word_of(wd, v)));
+          const float sc = lv[v] + gv;
+          if (sc > best) { best = sc; bidx = a + v; }
+        }
+      }
+    }
+  }
+  // reduce over the TPR threads of the row, lowest index on ties
+#pragma unroll
+  for (int off = 1; off < TPR; off <<= 1) {
+    const float ob = __shfl_xor(best, off);
+    const int oi = __shfl_xor(bidx, off);
+    const float om = __shfl_xor(mx, off);
+    if (oi >= 0 && (bidx < 0 || ob > best || (ob == best && oi < bidx))) { best = ob; bidx = oi; }
+    mx = fmaxf(mx, om);
+  }
+  if (p.mode == 0) {
+    if (row_ok && q == 0) p.action[m] = bidx;
+    if (p.probs) {
+      float se = 0.f;
+#pragma unroll
+      for (int b = 0; b < MAXB; ++b)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          if ((mk[b] >> (8 * v)) & 0xffu) se += expf(lg[a0 + 4 * b + v] + p.bc[a0 + 4 * b + v] - mx);
+#pragma unroll
+      for (int off = 1; off < TPR; off <<= 1) se += __shfl_xor(se, off);
+      const float inv = se > 0.f ? 1.0f / se : 0.f;
+      if (row_ok) {
+#pragma unroll
+        for (int b = 0; b < MAXB; ++b)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const int a = a0 + 4 * b + v;
+            if (4 * b + v < apt && a < A)
+              p.probs[(long)m * A + a] = ((mk[b] >> (8 * v)) & 0xffu) ? expf(lg[a] + p.bc[a] - mx) * inv : 0.f;
+          }
+      }
+    }
+    return;
+  }
+  if (p.N > 0) bidx = two_level_pick<TPR>(p, rng, lg, m, want_action && row_ok, q, traj);
+  const int Ar = p.N > 0 ? p.N + 1 + p.Lc : A;  // the reward and done logit rows
+  if (row_ok && q == 0) ctrl_row_commit(p, rng, m, bidx, lg[Ar] + p.bc[Ar], lg[Ar + 1] + p.bc[Ar + 1]);
+}
+
+// Controller on the register-direct core: all Nc outputs x 16 rows.  Each row
+// is handled by 16 lanes of one wave (four waves, four rows per wave), each
+// lane taking the action blocks sub + 16 h, h < 4 (four actions and one
+// Philox block each); their Gumbel noise and mask bits are drawn before the
+// GEMM.  Requires A <= 256.
+template <class R, class S>
+__global__ void __launch_bounds__(R::MAXT) k_ctrl_rd(const CtrlArgs p) {
+  using DT = typename R::DT;
+  extern __shared__ __attribute__((aligned(16))) float lds_dyn[];
+  const int m0 = blockIdx.x * R::BM;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int ml = 4 * wave + (lane >> 4), sub = lane & 15;
+  const int m = m0 + ml;
+  const bool row_ok = wave < 4 && m < p.M;
+  const int A = p.A;
+  const Rng rng{p.k0, p.k1};
+  float gn[16];
+  unsigned valid = 0;
+  if (row_ok && p.mode != 2) {
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+      const int b = sub + 16 * h;
+      if (4 * b < A) {
+        const uint4 w = rng.block((uint32_t)b, p.step, p.traj0 + (uint32_t)m, STREAM_CONTROLLER);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int a = 4 * b + v;
+          gn[4 * h + v] = gumbel(word_to_uniform(word_of(w, v)));
+          if (a < A && p.mask[(long)m * A + a]) valid |= 1u << (4 * h + v);
+        }
+      }
+    }
+  }
+  const SrcX<DT> w(reinterpret_cast<const DT*>(p.Wc), p.ldk, p.ldk, 0, R::BN, p.Nc);
+  R::run(lds_dyn, w, ctrl_src<S>(p, m0, R::BM), (int)p.ldk);
+  if (wave >= 4) return;  // rows live in the first four waves; no barrier below
+  const float* lg = R::E(lds_dyn) + ml * R::ELD;
+  float best = -INFINITY, mx = -INFINITY;
+  int bidx = -1;
+#pragma unroll
+  for (int h = 0; h < 4; ++h)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      if (valid & (1u << (4 * h + v))) {
+        const int a = 4 * (sub + 16 * h) + v;
+        const float l = lg[a] + p.bc[a];
+        mx = fmaxf(mx, l);
+        const float sc = l + gn[4 * h + v];
+        if (sc > best) { best = sc; bidx = a; }
+      }
+    }
+  // reduce over the 16 lanes of the row, lowest index on ties
+#pragma unroll
+  for (int off = 8; off >= 1; off >>= 1) {
+    const float ob = __shfl_xor(best, off);
+    const int oi = __shfl_xor(bidx, off);
+    const float om = __shfl_xor(mx, off);
+    if (oi >= 0 && (bidx < 0 || ob > best || (ob == best && oi < bidx))) { best = ob; bidx = oi; }
+    mx = fmaxf(mx, om);
+  }
+  if (p.mode == 0) {
+    if (row_ok && sub == 0) p.action[m] = bidx;
+    if (p.probs) {
+      float se = 0.f;
+      if (row_ok)
+        for (int a = sub; a < A; a += 16)
+          if (p.mask[(long)m * A + a]) se += expf(lg[a] + p.bc[a] - mx);
+#pragma unroll
+      for (int off = 8; off >= 1; off >>= 1) se += __shfl_xor(se, off);
+      const float inv = se > 0.f ? 1.0f / se : 0.f;
+      if (row_ok)
+        for (int a = sub; a < A; a += 16)
+          p.probs[(long)m * A + a] = p.mask[(long)m * A + a] ? expf(lg[a] + p.bc[a] - mx) * inv : 0.f;
+    }
+    return;
+  }
+  if (row_ok && sub == 0) ctrl_row_commit(p, rng, m, bidx, lg[A] + p.bc[A], lg[A + 1] + p.bc[A + 1]);
+}
+
+namespace {
+
+// Controller tiles by dtype.
+template <typename DT> struct Cfgs;
+template <> struct Cfgs<float> {
+  static constexpr bool kXL = false;  // fp32 calls this large take the 32-row controller tiles
+  template <int NB> using CtrlLarge = Gemm<float, NB, 4, 4, 1, 1, 32, 3>;  // 64NB x 64
+  template <int NB> using CtrlLargeX = GemmD<float, NB, 2, 4, 1, 3>;      // 64NB x 32
+  template <int NB> using CtrlXL = CtrlLargeX<NB>;
+  static constexpr int WIDE_BKC = 64;
+};
+template <> struct Cfgs<bf16_t> {
+  static constexpr bool kXL = true;
+  template <int NB> using CtrlLarge = Gemm<bf16_t, NB, 4, 4, 1, 1, 64, 2>;
+  template <int NB> using CtrlLargeX = GemmD<bf16_t, NB, 2, 4, 1, 3>;
+  // 64-row controller tiles, three stages: half the weight re-reads of the
+  // 32-row tiles.  With five 64-output blocks (A up to 318) sixteen waves of
+  // one 16-row block each, which hide more of the chunk loads' latency than
+  // eight waves of two (xlarge controller 23.9 -> 22.6 us per step; four
+  // waves of four blocks: 32 us)
+  template <int NB> using CtrlXL = std::conditional_t<NB == 5, GemmD<bf16_t, NB, 1, 4, 4, 3>,
+                                                      GemmD<bf16_t, NB, 2, 4, 2, 3>>;
+  static constexpr int WIDE_BKC = 128;
+};
+
+// The 256-row tiles serve calls that still give every CU at least one tile.
+constexpr long kXLTiles = 256;
+
+// The register-direct controller serves calls with at most this many rows,
+// when the K slices fit SMAX per wave on the compiled block size.
+constexpr int kRdCtrlRows = 1024;
+template <class C, class S>
+hipError_t launch_ctrl_cfg(const CtrlArgs& a, hipStream_t s) {
+  return launch("ctrl", k_ctrl<C, S>, dim3((a.M + C::BM - 1) / C::BM), dim3(C::NT), 0, s, a);
+}
+
+template <class S, int NBW, int MBW>
+hipError_t launch_ctrl_wide(const CtrlArgs& a, hipStream_t s) {
+  constexpr int BM = 16 * MBW;
+  return launch("ctrl", k_ctrl_wide<S, NBW, MBW, Cfgs<typename S::DT>::WIDE_BKC>,
+                dim3((a.M + BM - 1) / BM), dim3(256), 0, s, a);
+}
+
+template <class R, class S>
+hipError_t launch_ctrl_rd(const CtrlArgs& a, int nw, hipStream_t s) {
+  const size_t lds = R::lds_bytes(nw);
+  hipError_t e = allow_lds(k_ctrl_rd<R, S>, lds);
+  if (e != hipSuccess) return e;
+  return launch("ctrl", k_ctrl_rd<R, S>, dim3((a.M + R::BM - 1) / R::BM), dim3(64 * nw), lds, s, a);
+}
+
+}  // namespace
+
+// S: activation source (SrcX for the rollout's X_t, SrcZH for the step).
+template <class S>
+hipError_t launch_ctrl(const CtrlArgs& a, hipStream_t s) {
+  using DT = typename S::DT;
+  using Cf = Cfgs<DT>;
+  const int nbtot = a.Nc / 16;
+  const int nbw = (nbtot + 3) / 4;  // output blocks per wave over four waves
+  // the two-level controller of the controller step, and in rollouts where
+  // its logit rows do not fit the staged tiles: the logits are stored (into
+  // probs for the step, the workspace in a rollout), then picked per row
+  if (a.N > 0 && (a.mode == 0 || nbw > 5)) {
+    CtrlArgs g = a;
+    g.logits_out = a.mode == 0 ? a.probs : a.lg_ws;
+    g.ldl = a.mode == 0 ? a.N + 1 + a.Lc : a.Nc;
+    g.ncol = a.mode == 0 ? a.N + 1 + a.Lc : a.Nc;
+    if (!g.logits_out) return hipErrorInvalidValue;
+    hipError_t e;
+    if (nbw <= 8) e = launch_ctrl_wide<S, 8, 2>(g, s);
+    else if (nbw <= 12) e = launch_ctrl_wide<S, 12, 2>(g, s);
+    else if (nbw <= 17) e = launch_ctrl_wide<S, 17, 1>(g, s);
+    else if (nbw <= 24) e = launch_ctrl_wide<S, 24, 1>(g, s);
+    else if (nbw <= 33) e = launch_ctrl_wide<S, 33, 1>(g, s);
+    else return hipErrorInvalidValue;
+    if (e != hipSuccess) return e;
+    return launch("ctrl", k_ctrl_rows, dim3((unsigned)((a.M + 3) / 4)), dim3(256), 0, s, g);
+  }
+  // (otherwise the two-level controller runs on the kernels that stage whole logit rows)
+  if (a.M <= kRdCtrlRows && nbtot <= 9 && a.N == 0) {
+    const int nb = nbtot <= 1 ? 1 : nbtot <= 2 ? 2 : nbtot <= 3 ? 3 : nbtot <= 5 ? 5 : 9;
+    const int smax = nb <= 5 ? 8 : 4;  // register budget
+    const int nw = rd_waves((int)a.ldk, Mfma<DT>::KSLICE, smax, 4);
+    if (nw <= 8 && GemmRD<DT, 9, 1, 4, 512>::lds_bytes(nw) <= kRdLdsMax) {
+      switch (nb) {
+        case 1: return launch_ctrl_rd<GemmRD<DT, 1, 1, 8, 512>, S>(a, nw, s);
+        case 2: return launch_ctrl_rd<GemmRD<DT, 2, 1, 8, 512>, S>(a, nw, s);
+        case 3: return launch_ctrl_rd<GemmRD<DT, 3, 1, 8, 512>, S>(a, nw, s);
+        case 5: return launch_ctrl_rd<GemmRD<DT, 5, 1, 8, 512>, S>(a, nw, s);
+        default: return launch_ctrl_rd<GemmRD<DT, 9, 1, 4, 512>, S>(a, nw, s);
+      }
+    }
+  }
+  const int nb = nbw;
+  if constexpr (S::kTwo) {
+    if (nb <= 1) return launch_ctrl_cfg<typename Cf::template CtrlLarge<1>, S>(a, s);
+    if (nb <= 2) return launch_ctrl_cfg<typename Cf::template CtrlLarge<2>, S>(a, s);
+    if (nb <= 3) return launch_ctrl_cfg<typename Cf::template CtrlLarge<3>, S>(a, s);
+    if (nb <= 5) return launch_ctrl_cfg<typename Cf::template CtrlLarge<5>, S>(a, s);
+  } else {
+    // 64-row tiles once they still give every CU one, 32-row tiles below
+    if (Cf::kXL && (long)(a.M + 63) / 64 >= kXLTiles) {
+      if (nb <= 1) return launch_ctrl_cfg<typename Cf::template CtrlXL<1>, S>(a, s);
+      if (nb <= 2) return launch_ctrl_cfg<typename Cf::template CtrlXL<2>, S>(a, s);
+      if (nb <= 3) return launch_ctrl_cfg<typename Cf::template CtrlXL<3>, S>(a, s);
+      if (nb <= 5) return launch_ctrl_cfg<typename Cf::template CtrlXL<5>, S>(a, s);
+    }
+    if (nb <= 1) return launch_ctrl_cfg<typename Cf::template CtrlLargeX<1>, S>(a, s);
+    if (nb <= 2) return launch_ctrl_cfg<typename Cf::template CtrlLargeX<2>, S>(a, s);
+    if (nb <= 3) return launch_ctrl_cfg<typename Cf::template CtrlLargeX<3>, S>(a, s);
+    if (nb <= 5) return launch_ctrl_cfg<typename Cf::template CtrlLargeX<5>, S>(a, s);
+  }
+  if (nb <= 8) return launch_ctrl_wide<S, 8, 2>(a, s);
+  if (nb <= 12) return launch_ctrl_wide<S, 12, 2>(a, s);
+  if (nb <= 17) return launch_ctrl_wide<S, 17, 1>(a, s);
+  if (nb <= 24) return launch_ctrl_wide<S, 24, 1>(a, s);
+  if (nb <= 33) return launch_ctrl_wide<S, 33, 1>(a, s);
+  return hipErrorInvalidValue;
+}
+
+template hipError_t launch_ctrl<SrcX<float>>(const CtrlArgs&, hipStream_t);
+template hipError_t launch_ctrl<SrcX<bf16_t>>(const CtrlArgs&, hipStream_t);
+
+hipError_t launch_controller_step(const Packed& P, int B, uint32_t traj0, const float* z,
+                                  const float* h, const uint8_t* mask, uint32_t k0, uint32_t k1,
+                                  uint32_t step, float* probs, int32_t* action, hipStream_t s) {
+  const Layout& L = P.L;
+  const char* base = reinterpret_cast<const char*>(P.base);
+  CtrlArgs ca{};
+  ca.Wc = base + L.off_Wc;
+  ca.bc = reinterpret_cast<const float*>(base + L.off_bc);
+  ca.ldk = L.ldk;
+  ca.Z = L.Z; ca.H = L.H; ca.A = L.A; ca.Nc = L.Nc; ca.M = B;
+  ca.z = z;
+  ca.h = h;
+  ca.mask = mask;
+  ca.k0 = k0; ca.k1 = k1; ca.step = step; ca.traj0 = traj0;
+  ca.mode = 0;
+  ca.probs = probs;
+  ca.action = action;
+  ca.N = L.N;
+  ca.Lc = L.Lc;
+  if (L.dt == 0) return launch_ctrl<SrcZH<float>>(ca, s);
+  return launch_ctrl<SrcZH<bf16_t>>(ca, s);
+}
+
+}  // namespace wm

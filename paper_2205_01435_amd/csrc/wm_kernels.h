@@ -1,5 +1,5 @@
-// Launch interface between the C ABI (wm_api.cpp) and the HIP kernels
-// (wm_kernels.hip).  Internal to libwm.
+// Launch interface between the C ABI (wm_api.cpp) and the HIP kernels.
+// Internal to libwm.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -97,6 +97,8 @@ hipError_t launch_check_nll(int T, int B, int A, const int32_t* actions, const u
                             const int32_t* lengths, unsigned* sync, hipStream_t s);
 
 hipError_t launch_nll(const Packed& P, const NllBufs& N, hipStream_t s);
+// The fp32 pass's recurrence only (X_1 .. X_T, and the traces asked for).
+hipError_t launch_nll_recurrence(const Packed& P, const NllBufs& N, hipStream_t s);
 
 // Persistent single-launch kernels (wm_persist.hip) for small fp32 batches.
 // The launchers return hipErrorNotSupported when the dims, the batch or the

@@ -36,15 +36,20 @@ import sys
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
-HEADERS = ["wm_device.h", "wm_kernels.h", "wm_layout.h"]
+HEADERS = ["wm_device.h", "wm_gemm.h", "wm_kernels.h", "wm_layout.h", "wm_steps.h"]
 CALIB_BYTES = 256 << 20
 XCDS, SIMDS = 8, 1024  # MI355X: 8 XCDs, 256 CUs x 4 SIMDs
 
 
 def kernel_sources(kernel: str) -> list[str]:
     """The sources a kernel is compiled from: the persistent kernels live in
-    wm_persist.hip, every other kernel in wm_kernels.hip."""
-    return ["wm_persist.hip" if "persist" in kernel else "wm_kernels.hip", *HEADERS]
+    wm_persist.hip, the mixture, controller and gradient kernels of the
+    per-step path in files of their own, the others in wm_kernels.hip."""
+    for part, name in (("persist", "wm_persist.hip"), ("k_mdn", "wm_mdn.hip"), ("k_ctrl", "wm_ctrl.hip"),
+                       ("k_grad", "wm_grad.hip"), ("k_gemm", "wm_grad.hip")):
+        if part in kernel:
+            return [name, *HEADERS]
+    return ["wm_kernels.hip", *HEADERS]
 
 
 def kernel_source_hash(sources: list[str]) -> str:
