@@ -22,6 +22,20 @@ namespace wm {
 //   mode 1: rollout step t: resolve transition t-1, choose a_t
 //   mode 2: rollout tail: resolve transition T-1 only
 // ===========================================================================
+// What the bookkeeping of row m reads: its done state, the action of the
+// previous transition (-1 at the first step) and whether step t is padding.
+// Kernels load it ahead of their product.
+struct RowState {
+  int ds, prev, pad;
+};
+__device__ __forceinline__ RowState row_state(const CtrlArgs& p, int m) {
+  RowState r;
+  r.ds = p.done_state[m];
+  r.prev = p.act_prev ? p.act_prev[m] : -1;
+  r.pad = p.lengths && p.t >= p.lengths[m];
+  return r;
+}
+
 // Rollout bookkeeping of row m at step t (modes 1 and 2 of the controller
 // kernels).  First the previous transition t-1 is resolved if the row was
 // live then: its reward is the reward head on h_t and it is done when
@@ -31,9 +45,9 @@ namespace wm {
 // A step past the row's horizon is padding: no action, reward 0, done 0 (its
 // state is kept like a frozen row's; the latent is zeroed afterwards).
 __device__ __forceinline__ void ctrl_row_commit(const CtrlArgs& p, const Rng& rng, int m, int a,
-                                                float rr, float rd) {
-  int ds = p.done_state[m];
-  if (p.act_prev && p.act_prev[m] >= 0) {
+                                                float rr, float rd, const RowState& r) {
+  int ds = r.ds;
+  if (r.prev >= 0) {
     p.rew_prev[m] = rr;
     int d = 0;
     if (p.use_done) {
@@ -44,13 +58,12 @@ __device__ __forceinline__ void ctrl_row_commit(const CtrlArgs& p, const Rng& rn
     if (d) ds = 1;
   }
   if (p.mode == 1) {
-    const bool pad = p.lengths && p.t >= p.lengths[m];
-    if (ds || pad) a = -1;
+    if (ds || r.pad) a = -1;
     else if (a < 0) ds = 1;
     p.act_t[m] = a;
     if (a < 0) {
       p.rew_t[m] = 0.f;
-      p.done_t[m] = pad ? 0 : 1;
+      p.done_t[m] = r.pad ? 0 : 1;
     }
   }
   p.done_state[m] = ds;
@@ -143,14 +156,86 @@ __device__ __forceinline__ int two_level_pick(const CtrlArgs& p, const Rng& rng,
   return l < 0 ? -1 : x * p.Lc + l;
 }
 
-// The two-level controller from stored logits (k_ctrl_wide with logits_out),
+// One lane's share of a pick by a whole wave over n scores: the blocks of
+// four consecutive indices lane, lane + 64, ... (one Philox block each), whose
+// logits and biases are all loaded before the first is used.
+constexpr int kRowsMax = 1024;          // N + 1 and Lc at most this
+constexpr int kRowBlk = kRowsMax / 256;  // blocks of four per lane
+struct RowLogits {
+  float v[kRowBlk][4];
+};
+
+// logits + biases of indices [0, n) at byte offset o0 of both rows
+__device__ __forceinline__ void row_logits(RowLogits& r, rsrc_t rl, rsrc_t rb, uint32_t o0, int n, int lane) {
+  float b[kRowBlk][4];
+#pragma unroll
+  for (int k = 0; k < kRowBlk; ++k)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int i = 4 * (lane + 64 * k) + v;
+      const uint32_t o = i < n ? o0 + 4u * (uint32_t)i : kOffNone;
+      r.v[k][v] = __uint_as_float(bload4(rl, o));
+      b[k][v] = __uint_as_float(bload4(rb, o));
+    }
+#pragma unroll
+  for (int k = 0; k < kRowBlk; ++k)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) r.v[k][v] += b[k][v];
+}
+
+// mask bytes m[o0 .. o0 + n) of the lane's blocks, one bit per index
+__device__ __forceinline__ uint32_t row_mask(rsrc_t rm, uint32_t o0, int n, int lane) {
+  uint32_t by[kRowBlk][4], bits = 0;
+#pragma unroll
+  for (int k = 0; k < kRowBlk; ++k)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int i = 4 * (lane + 64 * k) + v;
+      by[k][v] = bload1(rm, i < n ? o0 + (uint32_t)i : kOffNone);
+    }
+#pragma unroll
+  for (int k = 0; k < kRowBlk; ++k)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) bits |= by[k][v] ? 1u << (4 * k + v) : 0u;
+  return bits;
+}
+
+// Gumbel-max over the valid indices, lowest index on ties; the wave's lanes
+// all return it (-1: none valid).
+__device__ __forceinline__ int row_pick(const RowLogits& r, uint32_t bits, const Rng& rng, uint32_t step,
+                                        uint32_t traj, uint32_t stream, int lane) {
+  float best = -INFINITY;
+  int bi = -1;
+#pragma unroll
+  for (int k = 0; k < kRowBlk; ++k) {
+    const uint32_t m4 = (bits >> (4 * k)) & 15u;
+    if (!m4) continue;
+    const uint32_t blk = (uint32_t)(lane + 64 * k);
+    const uint4 w = rng.block(blk, step, traj, stream);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      if ((m4 >> v) & 1u) {
+        const float sc = r.v[k][v] + gumbel(word_to_uniform(word_of(w, v)));
+        if (sc > best) { best = sc; bi = (int)(4 * blk) + v; }
+      }
+    }
+  }
+  row_argmax<64>(best, bi);
+  return bi;
+}
+
+// The two-level controller from stored logits (k_ctrl_logits, k_ctrl_wide),
 // one wave per row, for controllers too wide for the staged tiles and for
 // the controller step.  Rollout modes: the pick and the row's commit (the
 // reward and done logits are columns Ac, Ac + 1).  Mode 0: the action and,
 // over the row's logits in place, the probabilities: the softmax of the
 // valid xfers' logits [N+1], then the softmax of the valid locations of the
 // picked xfer [Lc] (0 after a NO-OP or when nothing is valid).
-constexpr int kRowsMax = 1024;  // N + 1 and Lc at most this
+// Bound by the latency of its loads: everything but the chosen xfer's
+// location mask is in flight before the first value is used, and a lane
+// takes four consecutive indices per Philox block.  (One xfer index per
+// block and a load at a time before: 11.8 us per step at B 4096, N 288,
+// L 200.)
 __global__ void __launch_bounds__(256) k_ctrl_rows(const CtrlArgs p) {
   const int lane = threadIdx.x & 63;
   const int m = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -158,40 +243,47 @@ __global__ void __launch_bounds__(256) k_ctrl_rows(const CtrlArgs p) {
   float* lg = p.logits_out + (long)m * p.ldl;
   const Rng rng{p.k0, p.k1};
   const uint32_t traj = p.traj0 + (uint32_t)m;
-  const int N = p.N, NX = N + 1, Lc = p.Lc;
+  const int N = p.N, NX = N + 1, Lc = p.Lc, Ar = NX + Lc;
+  const int ncol = p.mode == 0 ? Ar : Ar + 2;
+  const rsrc_t rl = make_rsrc(lg, (uint32_t)ncol * 4u);
+  const rsrc_t rb = make_rsrc(p.bc, (uint32_t)p.Nc * 4u);
+  const rsrc_t rx = make_rsrc(p.mask + (long)m * NX, (uint32_t)NX);
+  // location masks of the row's xfers (N Lc bytes; below 2^20)
+  const rsrc_t rlm = make_rsrc(p.mask + (long)p.M * NX + (long)m * N * Lc, (uint32_t)(N * Lc));
+  int x = -1, a = -1;
+  RowLogits lx, ll;
+  uint32_t mx = 0, ml = 0;
+  float rr = 0.f, rd = 0.f;
+  RowState rs{};
   if (p.mode != 0) {
-    int a = -1;
-    if (p.mode == 1) {
-      const int x = two_level_xfer<64>(p, rng, lg, m, true, lane, traj);
-      if (x == N) a = -2;
-      else if (x >= 0) {
-        const int l = two_level_loc<64, kRowsMax>(p, rng, lg, m, true, lane, traj, x);
-        a = l < 0 ? -1 : x * Lc + l;
-      }
+    rs = row_state(p, m);
+    rr = __uint_as_float(bload4(rl, 4u * (uint32_t)Ar)) + __uint_as_float(bload4(rb, 4u * (uint32_t)Ar));
+    rd = __uint_as_float(bload4(rl, 4u * (uint32_t)(Ar + 1))) + __uint_as_float(bload4(rb, 4u * (uint32_t)(Ar + 1)));
+  }
+  if (p.mode != 2) {
+    mx = row_mask(rx, 0u, NX, lane);
+    row_logits(lx, rl, rb, 0u, NX, lane);
+    row_logits(ll, rl, rb, 4u * (uint32_t)NX, Lc, lane);
+    x = row_pick(lx, mx, rng, p.step, traj, STREAM_CONTROLLER, lane);
+    if (x == N) a = -2;
+    else if (x >= 0) {
+      ml = row_mask(rlm, (uint32_t)(x * Lc), Lc, lane);
+      const int l = row_pick(ll, ml, rng, p.step, traj, STREAM_LOCATION, lane);
+      a = l < 0 ? -1 : x * Lc + l;
     }
-    const int Ar = NX + Lc;
-    if (lane == 0) ctrl_row_commit(p, rng, m, a, lg[Ar] + p.bc[Ar], lg[Ar + 1] + p.bc[Ar + 1]);
+  }
+  if (p.mode != 0) {
+    if (lane == 0) ctrl_row_commit(p, rng, m, a, rr, rd, rs);
     return;
   }
-  const int x = two_level_xfer<64>(p, rng, lg, m, true, lane, traj);
-  const bool locs = x >= 0 && x < N;
-  const int l = locs ? two_level_loc<64, kRowsMax>(p, rng, lg, m, true, lane, traj, x) : -1;
-  const int a = x < 0 ? -1 : x == N ? -2 : l < 0 ? -1 : x * Lc + l;
-  // every logit this lane needs, read before any probability is written
-  constexpr int PER = kRowsMax / 64;
-  const uint8_t* lm = p.mask + (long)p.M * NX + ((long)m * N + (locs ? x : 0)) * Lc;
-  float vx[PER], vl[PER];
   float mxx = -INFINITY, mxl = -INFINITY;
 #pragma unroll
-  for (int k = 0; k < PER; ++k) {
-    const int i = lane + 64 * k;
-    const bool okx = i < NX && p.mask[(long)m * NX + i];
-    vx[k] = okx ? lg[i] + p.bc[i] : -INFINITY;
-    mxx = fmaxf(mxx, vx[k]);
-    const bool okl = locs && i < Lc && lm[i];
-    vl[k] = okl ? lg[NX + i] + p.bc[NX + i] : -INFINITY;
-    mxl = fmaxf(mxl, vl[k]);
-  }
+  for (int k = 0; k < kRowBlk; ++k)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      if ((mx >> (4 * k + v)) & 1u) mxx = fmaxf(mxx, lx.v[k][v]);
+      if ((ml >> (4 * k + v)) & 1u) mxl = fmaxf(mxl, ll.v[k][v]);
+    }
 #pragma unroll
   for (int off = 1; off < 64; off <<= 1) {
     mxx = fmaxf(mxx, __shfl_xor(mxx, off));
@@ -199,12 +291,14 @@ __global__ void __launch_bounds__(256) k_ctrl_rows(const CtrlArgs p) {
   }
   float sx = 0.f, sl = 0.f;
 #pragma unroll
-  for (int k = 0; k < PER; ++k) {
-    vx[k] = vx[k] == -INFINITY ? 0.f : expf(vx[k] - mxx);
-    vl[k] = vl[k] == -INFINITY ? 0.f : expf(vl[k] - mxl);
-    sx += vx[k];
-    sl += vl[k];
-  }
+  for (int k = 0; k < kRowBlk; ++k)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      lx.v[k][v] = (mx >> (4 * k + v)) & 1u ? expf(lx.v[k][v] - mxx) : 0.f;
+      ll.v[k][v] = (ml >> (4 * k + v)) & 1u ? expf(ll.v[k][v] - mxl) : 0.f;
+      sx += lx.v[k][v];
+      sl += ll.v[k][v];
+    }
 #pragma unroll
   for (int off = 1; off < 64; off <<= 1) {
     sx += __shfl_xor(sx, off);
@@ -212,11 +306,13 @@ __global__ void __launch_bounds__(256) k_ctrl_rows(const CtrlArgs p) {
   }
   const float ix = sx > 0.f ? 1.0f / sx : 0.f, il = sl > 0.f ? 1.0f / sl : 0.f;
 #pragma unroll
-  for (int k = 0; k < PER; ++k) {
-    const int i = lane + 64 * k;
-    if (i < NX) lg[i] = vx[k] * ix;
-    if (i < Lc) lg[NX + i] = vl[k] * il;
-  }
+  for (int k = 0; k < kRowBlk; ++k)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int i = 4 * (lane + 64 * k) + v;
+      if (i < NX) lg[i] = lx.v[k][v] * ix;
+      if (i < Lc) lg[NX + i] = ll.v[k][v] * il;
+    }
   if (lane == 0) p.action[m] = a;
 }
 
@@ -226,6 +322,37 @@ __device__ __forceinline__ S ctrl_src(const CtrlArgs& p, int m0, int rows) {
   using DT = typename S::DT;
   if constexpr (S::kTwo) return S(p.z, p.h, p.Z, p.H, m0, rows, p.M);
   else return S(reinterpret_cast<const DT*>(p.x), p.ldx, p.ldx, m0, rows, p.M);
+}
+
+// Logits of a rollout's wide two-level controller (more rows than the staged
+// tiles hold): lg[m][n] = W_c row n . X_t row m, bias not added, for
+// k_ctrl_rows.  One many-tile GEMM launch: every W_c row block is read once
+// per 64 or 128 trajectories (k_ctrl_wide, which ran here before, read all of
+// W_c once per 16 or 32: 50.6 us per step at B 4096, 489 logits, bf16).
+template <class C>
+__global__ void __launch_bounds__(C::NT) k_ctrl_logits(const CtrlArgs p) {
+  using DT = typename C::DT;
+  __shared__ __attribute__((aligned(16))) char lds_raw[C::LDS_BYTES];
+  int nt, mt;
+  if (!tile_of(p.map, nt, mt)) return;
+  const int n0 = nt * C::BN, m0 = mt * C::BM;
+  const SrcX<DT> w(reinterpret_cast<const DT*>(p.Wc), p.ldk, p.ldk, n0, C::BN, p.Nc);
+  const SrcX<DT> x(reinterpret_cast<const DT*>(p.x), p.ldx, p.ldx, m0, C::BM, p.M);
+  f32x4 acc[C::NBW][C::MBW];
+  C::run(acc, w, x, (int)p.ldk, reinterpret_cast<DT*>(lds_raw));
+  const int lane = threadIdx.x & 63, r16 = lane & 15, g = lane >> 4;
+  const int wn = C::wn(), wmi = C::wm();
+#pragma unroll
+  for (int j = 0; j < C::MBW; ++j) {
+    const int m = m0 + (wmi * C::MBW + j) * 16 + r16;
+    if (m >= p.M) continue;
+#pragma unroll
+    for (int i = 0; i < C::NBW; ++i) {
+      const int n = n0 + (wn * C::NBW + i) * 16 + 4 * g;
+      if (n < p.Nc)  // Nc and ldl are multiples of 16
+        *reinterpret_cast<f32x4*>(p.logits_out + (long)m * p.ldl + n) = acc[i][j];
+    }
+  }
 }
 
 template <class S, int NBW, int MBW, int BKC>
@@ -464,7 +591,7 @@ __global__ void __launch_bounds__(256) k_ctrl_wide(const CtrlArgs p) {
         const int oi = s_idx[w][tid];
         if (oi >= 0 && (a < 0 || ob > best || (ob == best && oi < a))) { best = ob; a = oi; }
       }
-      ctrl_row_commit(p, rng, m, a, s_rho[tid][0], s_rho[tid][1]);
+      ctrl_row_commit(p, rng, m, a, s_rho[tid][0], s_rho[tid][1], row_state(p, m));
     }
   }
 }
@@ -621,7 +748,8 @@ __global__ void __launch_bounds__(C::NT) k_ctrl(const CtrlArgs p) {
   }
   if (p.N > 0) bidx = two_level_pick<TPR>(p, rng, lg, m, want_action && row_ok, q, traj);
   const int Ar = p.N > 0 ? p.N + 1 + p.Lc : A;  // the reward and done logit rows
-  if (row_ok && q == 0) ctrl_row_commit(p, rng, m, bidx, lg[Ar] + p.bc[Ar], lg[Ar + 1] + p.bc[Ar + 1]);
+  if (row_ok && q == 0)
+    ctrl_row_commit(p, rng, m, bidx, lg[Ar] + p.bc[Ar], lg[Ar + 1] + p.bc[Ar + 1], row_state(p, m));
 }
 
 // Controller on the register-direct core: all Nc outputs x 16 rows.  Each row
@@ -700,7 +828,8 @@ __global__ void __launch_bounds__(R::MAXT) k_ctrl_rd(const CtrlArgs p) {
     }
     return;
   }
-  if (row_ok && sub == 0) ctrl_row_commit(p, rng, m, bidx, lg[A] + p.bc[A], lg[A + 1] + p.bc[A + 1]);
+  if (row_ok && sub == 0)
+    ctrl_row_commit(p, rng, m, bidx, lg[A] + p.bc[A], lg[A + 1] + p.bc[A + 1], row_state(p, m));
 }
 
 namespace {
@@ -754,6 +883,23 @@ hipError_t launch_ctrl_rd(const CtrlArgs& a, int nw, hipStream_t s) {
   return launch("ctrl", k_ctrl_rd<R, S>, dim3((a.M + R::BM - 1) / R::BM), dim3(64 * nw), lds, s, a);
 }
 
+template <class C>
+hipError_t launch_ctrl_logits_cfg(CtrlArgs a, hipStream_t s) {
+  a.map = tile_map((a.Nc + C::BN - 1) / C::BN, (a.M + C::BM - 1) / C::BM,
+                   (size_t)a.Nc * a.ldk * sizeof(typename C::DT));
+  return launch("ctrl", k_ctrl_logits<C>, dim3(grid_of(a.map)), dim3(C::NT), 0, s, a);
+}
+
+// The largest tile that still gives every CU one, else the smallest (the
+// same product shape as the gates', whose tiles' times per CU order so).
+template <typename DT>
+hipError_t launch_ctrl_logits(const CtrlArgs& a, hipStream_t s) {
+  auto tiles = [&](int bn, int bm) { return (long)((a.Nc + bn - 1) / bn) * ((a.M + bm - 1) / bm); };
+  if (tiles(128, 128) >= kCUs) return launch_ctrl_logits_cfg<GemmD<DT, 4, 2, 2, 4, 2>>(a, s);
+  if (tiles(128, 64) >= kCUs) return launch_ctrl_logits_cfg<GemmD<DT, 4, 2, 2, 2, 2>>(a, s);
+  return launch_ctrl_logits_cfg<GemmD<DT, 4, 1, 1, 4, 4>>(a, s);
+}
+
 }  // namespace
 
 // S: activation source (SrcX for the rollout's X_t, SrcZH for the step).
@@ -773,7 +919,8 @@ hipError_t launch_ctrl(const CtrlArgs& a, hipStream_t s) {
     g.ncol = a.mode == 0 ? a.N + 1 + a.Lc : a.Nc;
     if (!g.logits_out) return hipErrorInvalidValue;
     hipError_t e;
-    if (nbw <= 8) e = launch_ctrl_wide<S, 8, 2>(g, s);
+    if constexpr (!S::kTwo) e = launch_ctrl_logits<DT>(g, s);
+    else if (nbw <= 8) e = launch_ctrl_wide<S, 8, 2>(g, s);
     else if (nbw <= 12) e = launch_ctrl_wide<S, 12, 2>(g, s);
     else if (nbw <= 17) e = launch_ctrl_wide<S, 17, 1>(g, s);
     else if (nbw <= 24) e = launch_ctrl_wide<S, 24, 1>(g, s);

@@ -82,12 +82,13 @@ struct CtrlArgs {
   // followed by the location masks [M, N, Lc]; the logits are the N+1 xfer
   // rows then the Lc location rows
   int N, Lc;
-  // logits stored instead of picked (k_ctrl_wide): columns [0, ncol) of each
+  // logits stored instead of picked (k_ctrl_logits, k_ctrl_wide): columns [0, ncol) of each
   // row, bias not added, at logits_out + m ldl; k_ctrl_rows then picks
   float* logits_out;
   long ldl;
   int ncol;
   float* lg_ws;  // rollout workspace [M, Nc] for those logits (wide two-level controllers)
+  TileMap map;   // of k_ctrl_logits
 };
 
 // One launch each on `s`, the tile chosen from the call's sizes; defined for
