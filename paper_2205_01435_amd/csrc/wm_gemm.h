@@ -9,6 +9,7 @@
 #include <type_traits>
 
 #include "wm_device.h"
+#include "wm_split.h"
 
 namespace wm {
 
@@ -182,7 +183,13 @@ struct NoWork {
   __device__ __forceinline__ void operator()() const {}
 };
 
-template <typename DT_, int NBW_, int MBW_, int WAVES_N_, int WAVES_M_, int STAGES_>
+// SPLIT (fp32): the fragments are split into three bf16 terms as they leave
+// LDS and multiplied on the bf16 matrix unit (split3).  The split costs 5.5
+// VALU instructions per fragment value, so it pays with at least four 16-row
+// blocks a side per wave: 65536 x 1040 x 512 on 128 x 128 tiles of four waves
+// 446 us (156 TFLOP/s) against 671 us for the fp32 MFMA on its best tile,
+// 539 us on 128 x 64.
+template <typename DT_, int NBW_, int MBW_, int WAVES_N_, int WAVES_M_, int STAGES_, bool SPLIT_ = false>
 struct GemmD {
   using DT = DT_;
   static constexpr int NBW = NBW_, MBW = MBW_, WAVES_N = WAVES_N_, WAVES_M = WAVES_M_;
@@ -201,6 +208,7 @@ struct GemmD {
   static_assert(NQ % NWAVES == 0 && BN % 8 == 0, "whole DMA instructions per wave");
   static_assert(STAGES >= 2 && (STAGES - 2) * QW < 64, "vmcnt range");
   static_assert(2 * Mfma<DT>::KSLICE == BK, "two MFMA K slices per chunk");
+  static_assert(!SPLIT_ || sizeof(DT) == 4, "the split serves fp32 operands");
 
   __device__ static int kw() { return 0; }
   __device__ static int wn() { return (threadIdx.x >> 6) % WAVES_N; }
@@ -274,20 +282,40 @@ struct GemmD {
       asm volatile("" : : : "memory");
       if (kc + STAGES - 1 < nk) issue(kc + STAGES - 1);
       const char* buf = reinterpret_cast<const char*>(lds) + (kc % STAGES) * STAGE_BYTES;
+      if constexpr (SPLIT_) {
+        Split3 a[NBW];
 #pragma unroll
-      for (int sl = 0; sl < 2; ++sl) {
-        const uint32_t col = sl ? col1 : col0;
-        uint4 a[NBW], b[MBW];
+        for (int i = 0; i < NBW; ++i) {
+          const char* r = buf + ((wni * NBW + i) * 16 + r16) * 128;
+          a[i] = split3(*reinterpret_cast<const uint4*>(r + col0), *reinterpret_cast<const uint4*>(r + col1));
+        }
 #pragma unroll
-        for (int i = 0; i < NBW; ++i)
-          a[i] = *reinterpret_cast<const uint4*>(buf + ((wni * NBW + i) * 16 + r16) * 128 + col);
+        for (int j = 0; j < MBW; ++j) {
+          const char* r = buf + (BN + (wmi * MBW + j) * 16 + r16) * 128;
+          const Split3 b = split3(*reinterpret_cast<const uint4*>(r + col0), *reinterpret_cast<const uint4*>(r + col1));
+          f32x4 c[NBW];
 #pragma unroll
-        for (int j = 0; j < MBW; ++j)
-          b[j] = *reinterpret_cast<const uint4*>(buf + (BN + (wmi * MBW + j) * 16 + r16) * 128 + col);
+          for (int i = 0; i < NBW; ++i) c[i] = acc[i][j];
+          mfma_split(c, a, b);
 #pragma unroll
-        for (int i = 0; i < NBW; ++i)
+          for (int i = 0; i < NBW; ++i) acc[i][j] = c[i];
+        }
+      } else {
 #pragma unroll
-          for (int j = 0; j < MBW; ++j) Mfma<DT>::step(acc[i][j], a[i], b[j]);
+        for (int sl = 0; sl < 2; ++sl) {
+          const uint32_t col = sl ? col1 : col0;
+          uint4 a[NBW], b[MBW];
+#pragma unroll
+          for (int i = 0; i < NBW; ++i)
+            a[i] = *reinterpret_cast<const uint4*>(buf + ((wni * NBW + i) * 16 + r16) * 128 + col);
+#pragma unroll
+          for (int j = 0; j < MBW; ++j)
+            b[j] = *reinterpret_cast<const uint4*>(buf + (BN + (wmi * MBW + j) * 16 + r16) * 128 + col);
+#pragma unroll
+          for (int i = 0; i < NBW; ++i)
+#pragma unroll
+            for (int j = 0; j < MBW; ++j) Mfma<DT>::step(acc[i][j], a[i], b[j]);
+        }
       }
     }
     __syncthreads();  // LDS free for the caller's epilogue
@@ -295,8 +323,8 @@ struct GemmD {
 };
 
 template <class C> struct IsGemmD : std::false_type {};
-template <typename DT, int NBW, int MBW, int WN, int WM, int ST>
-struct IsGemmD<GemmD<DT, NBW, MBW, WN, WM, ST>> : std::true_type {};
+template <typename DT, int NBW, int MBW, int WN, int WM, int ST, bool SP>
+struct IsGemmD<GemmD<DT, NBW, MBW, WN, WM, ST, SP>> : std::true_type {};
 
 // Work-group -> tile mapping.  Work-groups are dispatched round-robin over
 // the eight XCDs, each with its own L2.  The XCDs form a gn x (8 / gn) grid

@@ -282,6 +282,7 @@ template <typename DT> struct Cfgs;
 template <> struct Cfgs<float> {
   template <int Q> using Mdn16 = Gemm<float, Q, 1, 2, 1, 2, 32, 4>;  // 32Q x 16, K split 2
   template <int Q> using Mdn32 = GemmD<float, Q, 1, 2, 2, 2>;
+  template <int Q> using Mdn128 = GemmD<float, Q, 4, 2, 2, 2, true>;  // split products
 };
 template <> struct Cfgs<bf16_t> {
   template <int Q> using Mdn32 = GemmD<bf16_t, Q, 1, 2, 2, 2>;
@@ -331,6 +332,8 @@ hipError_t launch_mdn_q(const MdnArgs& a, int ntiles, hipStream_t s) {
     return n == 1 ? one : fixed + per * (float)n;
   };
   if constexpr (sizeof(DT) == 4) {
+    if (cost(128, 40.0f, 5.0f, 28.0f) <= cost(32, 18.7f, 3.5f, 14.2f))
+      return launch_mdn_cfg<typename Cf::template Mdn128<Q>, DT, KC>(a, ntiles, s);
     if (cost(16, 17.0f, 3.0f, 10.6f) <= cost(32, 18.7f, 3.5f, 14.2f))
       return launch_mdn_cfg<typename Cf::template Mdn16<Q>, DT, KC>(a, ntiles, s);
   } else {

@@ -36,7 +36,7 @@ import sys
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
-HEADERS = ["wm_device.h", "wm_gemm.h", "wm_kernels.h", "wm_layout.h", "wm_steps.h"]
+HEADERS = ["wm_device.h", "wm_gemm.h", "wm_kernels.h", "wm_layout.h", "wm_split.h", "wm_steps.h"]
 CALIB_BYTES = 256 << 20
 XCDS, SIMDS = 8, 1024  # MI355X: 8 XCDs, 256 CUs x 4 SIMDs
 

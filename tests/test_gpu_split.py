@@ -1,0 +1,48 @@
+"""GPU parity of the products that run on the bf16 matrix unit from three-term
+splits, where their tiles and K slices have remainders: the training gradient
+over rows that do not fill the last slice or chunk, and the likelihood pass on
+128-row mixture tiles."""
+
+import numpy as np
+import pytest
+import torch
+
+import parity
+from oracle import wm as owm
+from paper_2205_01435_amd import _lib as wmlib
+from paper_2205_01435_amd import workloads as wl
+from test_gpu_grad import _case, _check
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def gpu():
+    assert torch.cuda.is_available(), "GPU tests need a ROCm GPU"
+    wmlib.load()
+    yield
+
+
+@pytest.mark.parametrize("seed,B,T,Z,H,A,K", [
+    (31, 97, 23, 24, 272, 70, 8),   # 2231 rows: several slices, the last short of a chunk
+    (32, 33, 31, 40, 144, 9, 5),    # 1023 rows; 192 and 592 product columns
+    (33, 5, 3, 8, 16, 3, 1),        # fewer rows than one chunk
+])
+def test_grad_slices(seed, B, T, Z, H, A, K):
+    ln = np.random.default_rng(seed).integers(0, T + 1, size=B).astype(np.int32)
+    ln[0] = T
+    w, d = _case(seed, B, T, Z, H, A, K, ln)
+    _check(w, d, f"slices {B * T} rows")
+
+
+@pytest.mark.parametrize("K", [1, 3, 5, 8])
+def test_nll_large_tiles(K):
+    w = wl.Workload("s", "nll", B=301, T=41, Z=40, H=80, A=7, K=K, dtype="fp32", seed=50 + K)
+    d = wl.make_nll_inputs(w)
+    m = wmlib.pack(d["weights"], w.Z, w.H, w.A, w.K, "fp32")
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    b = wmlib.nll(m, t(d["z"]), t(d["actions"]), t(d["rewards"]), t(d["dones"]))
+    torch.cuda.synchronize()
+    ref = owm.nll(d["weights"], w.dims, d["z"], d["actions"], d["rewards"], d["dones"], dtype="fp32")
+    for k in ("loglik", "reward_se", "done_bce", "means"):
+        parity.close(getattr(b, k).cpu().numpy(), ref[k], parity.RTOL["fp32"], k)
