@@ -14,7 +14,7 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libwm.so")
-SOURCES = ["wm_mdn.hip", "wm_ctrl.hip", "wm_kernels.hip", "wm_persist.hip", "wm_grad.hip", "wm_returns.hip",
+SOURCES = ["wm_mdn.hip", "wm_ctrl.hip", "wm_kernels.hip", "wm_persist.hip", "wm_grad.hip", "wm_recur.hip", "wm_returns.hip",
            "wm_optim.hip", "wm_noalloc.hip", "wm_api.cpp", "wm_profile.cpp"]
 HEADERS = ["wm_device.h", "wm_gemm.h", "wm_kernels.h", "wm_layout.h", "wm_profile.h", "wm_split.h",
            "wm_steps.h"]

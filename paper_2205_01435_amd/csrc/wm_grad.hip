@@ -40,7 +40,7 @@ static constexpr float kHalfLn2Pi = 0.91893853320467274178f;
 namespace {
 
 using GradGemm = GemmD<float, 4, 4, 2, 2, 2, true>;   // 128 x 128 tiles: the products over all rows
-using GradGemmS = GemmD<float, 2, 2, 2, 2, 2, true>;  // 64 x 64 tiles: the same over few, dG_t . W_h per step
+using GradGemmS = GemmD<float, 2, 2, 2, 2, 2, true>;  // 64 x 64 tiles: the same over few
 
 // out[m][n] = sum_{k < Kpad} A[m][k] B[n][k] for m < M, n < N (Kpad a
 // multiple of 32; columns of A and B up to Kpad must be readable, zero
@@ -93,32 +93,6 @@ __global__ void k_len_sum(const int32_t* lengths, int B, int T, float* nout) {
 }
 
 __device__ __forceinline__ float sig_(float x) { return 1.0f / (1.0f + expf(-x)); }
-
-// forward scan of one (row b, unit u): pre-activations G (packed gate
-// order, row r = t B + b, column 4u + q) plus bias and the action's column
-// -> activations i, f, tanh g, o in place; c_t into Cs [T+1, B, H]
-__global__ void __launch_bounds__(256) k_grad_fwd_scan(float* G, const float* bg, const float* WaT,
-                                                       const int32_t* actions, float* Cs, int B, int T, int H,
-                                                       int A) {
-  const long idx = (long)blockIdx.x * 256 + threadIdx.x;
-  if (idx >= (long)B * H) return;
-  const int b = (int)(idx / H), u = (int)(idx % H);
-  const float4 bias = reinterpret_cast<const float4*>(bg)[u];
-  float c = 0.f;
-  Cs[(long)b * H + u] = 0.f;
-  for (int t = 0; t < T; ++t) {
-    const long r = (long)t * B + b;
-    float4 g = reinterpret_cast<float4*>(G + r * 4 * H)[u];
-    const int a = actions[r];
-    float4 w = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (a >= 0 && a < A) w = reinterpret_cast<const float4*>(WaT + (long)a * 4 * H)[u];
-    const float i = sig_(g.x + bias.x + w.x), f = sig_(g.y + bias.y + w.y);
-    const float gg = tanhf(g.z + bias.z + w.z), o = sig_(g.w + bias.w + w.w);
-    c = f * c + i * gg;
-    reinterpret_cast<float4*>(G + r * 4 * H)[u] = make_float4(i, f, gg, o);
-    Cs[((long)(t + 1) * B + b) * H + u] = c;
-  }
-}
 
 // d loss / d head output of one row r = t B + b: for each latent dim j the
 // mixture features of packed rows 16 Q J + 16 q + 4 g + v (j = 4J + g,
@@ -200,36 +174,6 @@ __global__ void __launch_bounds__(256) k_grad_heads(float* M, long ldm, const fl
   for (int q = 0; q < Q; ++q)
 #pragma unroll
     for (int v = 0; v < 4; ++v) row[16 * Q * J + 16 * q + 4 * g + v] = d[4 * q + v];
-}
-
-// LSTM backward of step t for (row b, unit u): with dh = d loss / d h_{t+1}
-// (heads + the later steps) and dc = d loss / d c_{t+1} from the later steps,
-// writes dG_t (pre-activation gradients, packed gate order) and the new dc
-// (dhr: S slices [S, B, H] of the later step's dG . W_h, summed in order)
-__global__ void __launch_bounds__(256) k_grad_lstm_back(const float* G, const float* Cs, const float* dhh,
-                                                        const float* dhr, int S, float* dc, float* dG, int B,
-                                                        int H, int t, int last) {
-  const long idx = (long)blockIdx.x * 256 + threadIdx.x;
-  if (idx >= (long)B * H) return;
-  const int b = (int)(idx / H), u = (int)(idx % H);
-  const long r = (long)t * B + b;
-  const float4 a = reinterpret_cast<const float4*>(G + r * 4 * H)[u];  // i, f, g, o
-  const float c1 = Cs[((long)(t + 1) * B + b) * H + u], c0 = Cs[((long)t * B + b) * H + u];
-  float dh = dhh[r * H + u];
-  if (!last) {
-    float sum = 0.f;
-    for (int k = 0; k < S; ++k) sum += dhr[(long)k * B * H + (long)b * H + u];
-    dh += sum;
-  }
-  const float dcn = last ? 0.f : dc[(long)b * H + u];
-  const float th = tanhf(c1);
-  const float d_o = dh * th;
-  const float dcc = dcn + dh * a.w * (1.0f - th * th);
-  const float d_i = dcc * a.z, d_f = dcc * c0, d_g = dcc * a.x;
-  dc[(long)b * H + u] = dcc * a.y;
-  reinterpret_cast<float4*>(dG + r * 4 * H)[u] =
-      make_float4(d_i * a.x * (1.0f - a.x), d_f * a.y * (1.0f - a.y), d_g * (1.0f - a.z * a.z),
-                  d_o * a.w * (1.0f - a.w));
 }
 
 // one-hot columns: dWa[a][j] = sum over rows r with action a of dG[r][j].
@@ -359,10 +303,6 @@ int split_of(int M, int N, int Kpad, long target = 512) {
   while (S < kGradMaxSplit && tiles * S < target && chunks % (2 * S) == 0 && chunks / (2 * S) >= 4) S *= 2;
   return S;
 }
-
-// the per-step product: its tile shape and K slices
-using BpttGemm = GradGemmS;
-int bptt_split(int B, int H) { return split_of<BpttGemm>(B, H, 4 * H, 256); }
 
 // out (ldo) = A . B^T in S K-slices; S > 1 writes slice y to out + y oslice
 template <class C = GradGemm>
@@ -635,30 +575,30 @@ size_t grad_workspace(const Layout& L, int B, int T, char* ws, GradWs* G) {
   auto take = [&](size_t bytes) { const size_t at = o; o = wm_align256(o + bytes); return at; };
   const size_t oG = take((size_t)TB * H4 * 4), oC = take((size_t)(T + 1) * B * H * 4);
   const size_t oM = take((size_t)TB * NmP * 4), odG = take((size_t)TB * H4 * 4);
-  const size_t odhh = take((size_t)TB * H * 4), odh = take((size_t)B * H * 4), odc = take((size_t)B * H * 4);
+  const size_t odhh = take((size_t)TB * H * 4), odc = take((size_t)B * H * 4);
   const size_t odWgT = take((size_t)L.ldk * H4 * 4), odWa = take((size_t)L.A * H4 * 4);
   const size_t odWm = take((size_t)NmP * H * 4), odbg = take((size_t)H4 * 4), odbm = take((size_t)NmP * 4);
   const int Sg = tn_slices(L.ldk, H4, TB), Sm = tn_slices(NmP, H, TB);  // K slices of dW_g, dW_m
   const size_t opart = take((size_t)std::max({kFlatBlocks, Sg, Sm}) * std::max(H4, NmP) * 4);
   const size_t oapart = take((size_t)act_chunks(L) * L.A * H4 * 4);
-  // split-K partials: the largest of the products that split, and the
-  // per-step slices of dG_t . W_h (always)
+  // split-K partials: the largest of the products that split
   auto split_need = [](int M, int N, int Kpad) {
     const int S = split_nt(M, N, Kpad);
     return S > 1 ? (size_t)S * M * N : (size_t)0;
   };
-  const size_t nsplit = std::max({(size_t)bptt_split(B, H) * B * H, split_need((int)TB, H4, L.ldk),
-                                  split_need((int)TB, L.Nm, L.ldh), split_need((int)TB, H, NmP),
-                                  (size_t)Sg * L.ldk * H4, (size_t)Sm * NmP * H});
+  const size_t nsplit = std::max({split_need((int)TB, L.Nm, L.ldh),
+                                  split_need((int)TB, H, NmP), (size_t)Sg * L.ldk * H4, (size_t)Sm * NmP * H});
   const size_t osplit = take(nsplit * 4);
   const size_t on = take(16);
   const size_t ofwd = take((size_t)TB * (L.Z + 1) * 4);  // loss terms [TB, Z+1]
+  const size_t opl = take(recur_bwd_bytes(L, B));        // operand planes of the reverse-time chain
   if (ws && G) {
     auto f = [&](size_t at) { return reinterpret_cast<float*>(ws + at); };
-    G->G = f(oG); G->Cs = f(oC); G->M = f(oM); G->dG = f(odG); G->dhh = f(odhh); G->dh = f(odh);
+    G->G = f(oG); G->Cs = f(oC); G->M = f(oM); G->dG = f(odG); G->dhh = f(odhh);
     G->dc = f(odc);
     G->dWgT = f(odWgT); G->dWa = f(odWa); G->dWm = f(odWm); G->dbg = f(odbg); G->dbm = f(odbm);
     G->part = f(opart); G->apart = f(oapart); G->split = f(osplit); G->nsum = f(on); G->fwd = f(ofwd);
+    G->planes = ws + opl;
   }
   return o;
 }
@@ -669,35 +609,21 @@ hipError_t launch_nll_grad(const Packed& P, NllBufs N, const GradWs& G, const Gr
   const long TB = (long)T * B;
   const int NmP = (L.Nm + 31) / 32 * 32;
   const char* base = reinterpret_cast<const char*>(P.base);
-  const float* Wg = reinterpret_cast<const float*>(base + L.off_Wg);
-  const float* WaT = reinterpret_cast<const float*>(base + L.off_WaT);
-  const float* bg = reinterpret_cast<const float*>(base + L.off_bg);
   const float* Wm = reinterpret_cast<const float*>(base + L.off_Wm);
   const float* bm = reinterpret_cast<const float*>(base + L.off_bm);
-  const float* WhT = reinterpret_cast<const float*>(base + L.off_WhT);  // [H, 4H]
   const float* WmT = reinterpret_cast<const float*>(base + L.off_WmT);  // [H, NmP]
   const float* X = reinterpret_cast<const float*>(N.x);
   const float* Hn = X + (long)B * L.ldx + Z;  // h_1 .. h_T: rows of X_1 .. X_T from column Z
   hipError_t e;
 #define WM_TRY(x) do { e = (x); if (e != hipSuccess) return e; } while (0)
-  // forward recurrence: X (z_t | h_t) for every step. Where the persistent
-  // kernel serves it, it also leaves the gate activations and c_{t+1} of
-  // every step; otherwise they are recomputed from X (pre-activations of
-  // every step in one GEMM, then a scan that applies the gates and records
-  // c_t).
-  const bool traced = persist_usable(L, B, true);
-  N.g_trace = traced ? G.G : nullptr;
-  N.c_trace = traced ? G.Cs : nullptr;
+  // forward recurrence: X (z_t | h_t) for every step, with the gate
+  // activations and c_{t+1} of every step
+  N.g_trace = G.G;
+  N.c_trace = G.Cs;
   WM_TRY(launch_nll_recurrence(P, N, s));
   WM_TRY(launch("grad_len", k_len_sum, dim3(1), dim3(256), 0, s, N.lengths, B, T, G.nsum));
-  if (traced) {
-    WM_TRY(launch("grad_zero", k_zero, dim3((unsigned)(((long)B * H + 255) / 256)), dim3(256), 0, s, G.Cs,
-                  (long)B * H));  // c_0
-  } else {
-    WM_TRY(gemm_nt(X, L.ldx, (int)TB, Wg, L.ldk, H4, L.ldk, G.G, H4, G.split, s));
-    WM_TRY(launch("grad_scan", k_grad_fwd_scan, dim3((unsigned)(((long)B * H + 255) / 256)), dim3(256), 0, s,
-                  G.G, bg, WaT, N.actions, G.Cs, B, T, H, A));
-  }
+  WM_TRY(launch("grad_zero", k_zero, dim3((unsigned)(((long)B * H + 255) / 256)), dim3(256), 0, s, G.Cs,
+                (long)B * H));  // c_0
   // head outputs of every h_{t+1}, then d loss / d output in place
   WM_TRY(gemm_nt(Hn, L.ldx, (int)TB, Wm, L.ldh, L.Nm, L.ldh, G.M, NmP, G.split, s));
   switch (L.K) {
@@ -720,15 +646,7 @@ hipError_t launch_nll_grad(const Packed& P, NllBufs N, const GradWs& G, const Gr
   // W_m^T [H, NmP], zero columns past Nm)
   WM_TRY(gemm_nt(G.M, NmP, (int)TB, WmT, NmP, H, NmP, G.dhh, H, G.split, s));
   // back through time (the packed W_h^T [H, 4H])
-  const unsigned eg = (unsigned)(((long)B * H + 255) / 256);
-  const int Sb = bptt_split(B, H);  // K slices of dG_t . W_h, summed by the next step's kernel
-  for (int t = T - 1; t >= 0; --t) {
-    WM_TRY(launch("grad_lstm", k_grad_lstm_back, dim3(eg), dim3(256), 0, s, G.G, G.Cs, G.dhh, G.split, Sb, G.dc,
-                  G.dG, B, H, t, t == T - 1 ? 1 : 0));
-    if (t > 0)
-      WM_TRY(gemm_nt_slices<BpttGemm>("grad_gemm_bptt", G.dG + (long)t * B * H4, H4, B, WhT, H4, H, H4, Sb, G.split, H,
-                            (long)B * H, s));
-  }
+  WM_TRY(launch_recur_bwd(P, B, T, G.G, G.Cs, G.dhh, G.dc, G.dG, G.planes, s));
   // dW_g^T [ldk, 4H] = X^T . dG over all rows, read as stored; the bias
   // gradient (dG's column sums) from the same pass
   WM_TRY(gemm_tn(X, L.ldx, L.ldk, G.dG, H4, H4, TB, G.split, G.dWgT, H4, false, true, G.part, G.dbg, s));

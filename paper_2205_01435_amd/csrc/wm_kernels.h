@@ -61,6 +61,7 @@ struct NllBufs {
   // c_{t+1} at [t+1] of [T+1, B, H]
   float* g_trace;
   float* c_trace;
+  void* planes;  // operand planes of the per-step recurrence (fp32; recur_fwd_bytes)
 };
 
 // Barrier and status words (zeroed by the init kernels) at offset 0 of the
@@ -108,6 +109,15 @@ bool persist_usable(const Layout& L, int B, bool nll);
 hipError_t launch_rollout_persist(const Packed& P, const RolloutBufs& R, hipStream_t s);
 hipError_t launch_nll_persist(const Packed& P, const NllBufs& N, hipStream_t s);
 
+// The fp32 recurrence and its reverse-time chain, one launch per step
+// (wm_recur.hip): the bytes of their operand planes, and the launches.
+// G, Cs, dhh, dc, dG as in GradWs.
+size_t recur_fwd_bytes(const Layout& L, int B, int T);
+hipError_t launch_recur_fwd(const Packed& P, const NllBufs& N, hipStream_t s);
+size_t recur_bwd_bytes(const Layout& L, int B);
+hipError_t launch_recur_bwd(const Packed& P, int B, int T, const float* G, const float* Cs, const float* dhh,
+                            float* dc, float* dG, void* planes, hipStream_t s);
+
 // The static device scratch of wm_rollout_noalloc (wm_noalloc.hip): its
 // device address on the current device, looked up once per device.
 constexpr size_t kStaticScratchBytes = (size_t)64 << 20;
@@ -127,8 +137,9 @@ hipError_t launch_returns(const ReturnsBufs& R, hipStream_t s);
 
 // World-model training step: gradient of the summed NLL means (fp32).
 struct GradWs {  // workspace after the NLL pass's own
-  float *G, *Cs, *M, *dG, *dhh, *dh, *dc;
+  float *G, *Cs, *M, *dG, *dhh, *dc;
   float *dWgT, *dWa, *dWm, *dbg, *dbm, *part, *apart, *split, *nsum, *fwd;
+  void* planes;
 };
 struct GradOut {  // canonical gradients; loss (nullable): the summed means
   float *loss, *W_g, *b_g, *W_m, *b_m, *w_r, *b_r, *w_d, *b_d;

@@ -899,6 +899,20 @@ hipError_t rollout_impl(const Packed& P, const RolloutBufs& R, hipStream_t s) {
   return rollout_tail<DT>(L, R, X + (long)(T & 1) * BX, s);
 }
 
+// Which fp32 recurrences run one launch per step on split products
+// (wm_recur.hip): those the persistent kernel does not serve, and of those it
+// does, the batches whose rows per XCD (above 32) make its fp32 MFMAs the
+// longer part, over enough steps to pay for splitting the weights (15 us, four
+// steps' gain).  Whole likelihood passes, T 32, Z 64, K 1, persistent and per
+// step, us:
+//   B             128        200        256        384        512
+//   H 256     144, 197   197, 210   203, 206   326, 262   337, 254
+//   H 512     211, 254   310, 344   319, 309   587, 443   531, 471
+// While the persistent kernels' phases are being timed they serve all they can.
+bool recur_serves(const Layout& L, int B, int T) {
+  return !persist_usable(L, B, true) || (B > 256 && T >= 8 && !phases_timed());
+}
+
 // heads = false: the recurrence only (X_1 .. X_T), for the training gradient
 template <typename DT>
 hipError_t nll_impl(const Packed& P, const NllBufs& N, hipStream_t s, bool heads = true) {
@@ -920,8 +934,11 @@ hipError_t nll_impl(const Packed& P, const NllBufs& N, hipStream_t s, bool heads
   ga.H = H; ga.A = L.A; ga.Z = Z; ga.M = B;
   ga.nll_mode = 1;
   ga.c = N.c;
-  // the recurrence: one persistent launch when the batch and dims allow it
-  e = launch_nll_persist(P, N, s);
+  // the recurrence: one persistent launch for small batches, else one launch
+  // per step, in fp32 on split products (recur_serves)
+  e = hipErrorNotSupported;
+  if (sizeof(DT) == 2 || !recur_serves(L, B, T)) e = launch_nll_persist(P, N, s);
+  else e = launch_recur_fwd(P, N, s);
   if (e != hipSuccess && e != hipErrorNotSupported) return e;
   for (int t = 0; e == hipErrorNotSupported && t < T; ++t) {
     ga.x_in = X + (long)t * BX;
@@ -1000,6 +1017,8 @@ size_t nll_workspace(const Layout& L, int B, int T, char* ws, NllBufs* N) {
   o = wm_align256(o + M * 2 * 4);  // reward / done logits
   const size_t og = o;
   o = wm_align256(o + ((M + 255) / 256) * 4 * 4);  // block sums
+  const size_t opl = o;
+  if (L.dt == 0) o = wm_align256(o + recur_fwd_bytes(L, B, T));  // operand planes of the recurrence
   if (ws && N) {
     N->sync = reinterpret_cast<unsigned*>(ws + os);
     N->x = ws + ox;
@@ -1007,6 +1026,7 @@ size_t nll_workspace(const Layout& L, int B, int T, char* ws, NllBufs* N) {
     N->part = reinterpret_cast<float*>(ws + op);
     N->head = reinterpret_cast<float*>(ws + oh);
     N->wgsum = reinterpret_cast<float*>(ws + og);
+    N->planes = ws + opl;
   }
   return o;
 }

@@ -96,6 +96,11 @@ unsigned long long* phase_buffer(size_t words, hipStream_t s) {
   return g_pbuf;
 }
 
+bool phases_timed() {
+  std::lock_guard<std::mutex> lk(g_pmu);
+  return g_phases;
+}
+
 void phase_layout(int groups, int nst, int T, bool nll) {
   std::lock_guard<std::mutex> lk(g_pmu);
   g_pgroups = groups;

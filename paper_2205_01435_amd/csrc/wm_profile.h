@@ -39,6 +39,8 @@ void arg_ptrs(Tup& t, void** p, std::index_sequence<I...>) {
 // first use, grown as needed) for the stamps of the next launch; null while
 // it is off.
 unsigned long long* phase_buffer(size_t words, hipStream_t s);
+// Whether phase timing is on.
+bool phases_timed();
 // Layout of the launch that takes the stamps: `groups` work-groups of `nst`
 // stamps each, T steps, the NLL recurrence or the rollout.
 void phase_layout(int groups, int nst, int T, bool nll);

@@ -46,3 +46,37 @@ def test_nll_large_tiles(K):
     ref = owm.nll(d["weights"], w.dims, d["z"], d["actions"], d["rewards"], d["dones"], dtype="fp32")
     for k in ("loglik", "reward_se", "done_bce", "means"):
         parity.close(getattr(b, k).cpu().numpy(), ref[k], parity.RTOL["fp32"], k)
+
+
+@pytest.mark.parametrize("B,T,Z,H,A", [
+    (37, 3, 40, 48, 5),     # 16-row tiles; H and Z end inside a slice of 32 columns
+    (1, 2, 8, 16, 1),       # the smallest of everything
+    (300, 4, 24, 272, 7),   # 16-row tiles, the last row block short
+    (530, 3, 136, 528, 9),  # 32-row tiles; five slices of z
+    (512, 9, 64, 512, 64),  # a batch that the persistent kernel also serves
+])
+def test_recurrence_per_step(B, T, Z, H, A):
+    """The recurrence of one launch per step, forward (with actions outside
+    [0, A): no column) and, through the gradient, in reverse."""
+    w = wl.Workload("r", "nll", B=B, T=T, Z=Z, H=H, A=A, K=2, dtype="fp32", seed=60 + B)
+    d = wl.make_nll_inputs(w)
+    a = d["actions"].copy()
+    a[0, 0], a[-1, -1] = -1, A
+    d["actions"] = a
+    t = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()  # noqa: E731
+    m = wmlib.pack(d["weights"], Z, H, A, 2, "fp32")
+    wmlib.profile_reset()
+    wmlib.profile_enable("")
+    try:
+        b = wmlib.nll(m, t(d["z"]), t(a), t(d["rewards"]), t(d["dones"]))
+        torch.cuda.synchronize()
+        assert wmlib.profile_read("nll_step")[1] == T
+    finally:
+        wmlib.profile_enable(None)
+        wmlib.profile_reset()
+    ref = owm.nll(d["weights"], w.dims, d["z"], a, d["rewards"], d["dones"], dtype="fp32")
+    for k in ("loglik", "reward_se", "done_bce", "means"):
+        parity.close(getattr(b, k).cpu().numpy(), ref[k], parity.RTOL["fp32"], k)
+    if T * B <= 2000:
+        d["lengths"] = None
+        _check(w, d, f"per-step B {B} H {H}")
