@@ -755,8 +755,12 @@ __global__ void __launch_bounds__(C::NT) k_ctrl(const CtrlArgs p) {
 // Controller on the register-direct core: all Nc outputs x 16 rows.  Each row
 // is handled by 16 lanes of one wave (four waves, four rows per wave), each
 // lane taking the action blocks sub + 16 h, h < 4 (four actions and one
-// Philox block each); their Gumbel noise and mask bits are drawn before the
-// GEMM.  Requires A <= 256.
+// Philox block each).  Requires A <= 256.  A small call is one chain of
+// latencies, so everything the epilogue needs (mask bytes, biases, the row's
+// bookkeeping) is loaded unconditionally before the product's operands, and
+// the noise is drawn while those are in flight.  (Mask bytes read one at a
+// time behind their range checks, and again with the biases for the
+// probabilities, made a step for one state take 11.3 us.)
 template <class R, class S>
 __global__ void __launch_bounds__(R::MAXT) k_ctrl_rd(const CtrlArgs p) {
   using DT = typename R::DT;
@@ -767,42 +771,61 @@ __global__ void __launch_bounds__(R::MAXT) k_ctrl_rd(const CtrlArgs p) {
   const int m = m0 + ml;
   const bool row_ok = wave < 4 && m < p.M;
   const int A = p.A;
-  const Rng rng{p.k0, p.k1};
-  float gn[16];
-  unsigned valid = 0;
-  if (row_ok && p.mode != 2) {
+  constexpr int NH = (R::BN + 63) / 64;  // blocks of four actions per lane
+  const rsrc_t rm = make_rsrc(p.mask + (long)m0 * A, (uint32_t)(min(R::BM, p.M - m0) * A));
+  const rsrc_t rb = make_rsrc(p.bc, (uint32_t)p.Nc * 4u);
+  const bool pick = row_ok && p.mode != 2;
+  uint32_t mb[NH][4];
+  float4 bias[NH];
 #pragma unroll
-    for (int h = 0; h < 4; ++h) {
+  for (int h = 0; h < NH; ++h) {
+    const int a = 4 * (sub + 16 * h);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) mb[h][v] = bload1(rm, pick && a + v < A ? (uint32_t)(ml * A + a + v) : kOffNone);
+    bias[h] = as_float4(bload16(rb, pick ? 4u * (uint32_t)a : kOffNone));
+  }
+  RowState rs{};
+  float br = 0.f, bd = 0.f;
+  if (p.mode != 0 && row_ok && sub == 0) {
+    rs = row_state(p, m);
+    br = p.bc[A];
+    bd = p.bc[A + 1];
+  }
+  const Rng rng{p.k0, p.k1};
+  float gn[NH][4];
+  auto noise = [&]() {
+#pragma unroll
+    for (int h = 0; h < NH; ++h) {
       const int b = sub + 16 * h;
-      if (4 * b < A) {
+      if (pick && 4 * b < A) {
         const uint4 w = rng.block((uint32_t)b, p.step, p.traj0 + (uint32_t)m, STREAM_CONTROLLER);
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int a = 4 * b + v;
-          gn[4 * h + v] = gumbel(word_to_uniform(word_of(w, v)));
-          if (a < A && p.mask[(long)m * A + a]) valid |= 1u << (4 * h + v);
-        }
+        for (int v = 0; v < 4; ++v) gn[h][v] = gumbel(word_to_uniform(word_of(w, v)));
       }
     }
-  }
+  };
   const SrcX<DT> w(reinterpret_cast<const DT*>(p.Wc), p.ldk, p.ldk, 0, R::BN, p.Nc);
-  R::run(lds_dyn, w, ctrl_src<S>(p, m0, R::BM), (int)p.ldk);
+  R::run(lds_dyn, w, ctrl_src<S>(p, m0, R::BM), (int)p.ldk, noise);
   if (wave >= 4) return;  // rows live in the first four waves; no barrier below
   const float* lg = R::E(lds_dyn) + ml * R::ELD;
   float best = -INFINITY, mx = -INFINITY;
   int bidx = -1;
+  float l[NH][4];
 #pragma unroll
-  for (int h = 0; h < 4; ++h)
+  for (int h = 0; h < NH; ++h) {
+    const float bv[4] = {bias[h].x, bias[h].y, bias[h].z, bias[h].w};
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-      if (valid & (1u << (4 * h + v))) {
-        const int a = 4 * (sub + 16 * h) + v;
-        const float l = lg[a] + p.bc[a];
-        mx = fmaxf(mx, l);
-        const float sc = l + gn[4 * h + v];
+      const int a = 4 * (sub + 16 * h) + v;
+      l[h][v] = -INFINITY;
+      if (mb[h][v]) {
+        l[h][v] = lg[a] + bv[v];
+        mx = fmaxf(mx, l[h][v]);
+        const float sc = l[h][v] + gn[h][v];
         if (sc > best) { best = sc; bidx = a; }
       }
     }
+  }
   // reduce over the 16 lanes of the row, lowest index on ties
 #pragma unroll
   for (int off = 8; off >= 1; off >>= 1) {
@@ -816,20 +839,27 @@ __global__ void __launch_bounds__(R::MAXT) k_ctrl_rd(const CtrlArgs p) {
     if (row_ok && sub == 0) p.action[m] = bidx;
     if (p.probs) {
       float se = 0.f;
-      if (row_ok)
-        for (int a = sub; a < A; a += 16)
-          if (p.mask[(long)m * A + a]) se += expf(lg[a] + p.bc[a] - mx);
+#pragma unroll
+      for (int h = 0; h < NH; ++h)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          l[h][v] = mb[h][v] ? expf(l[h][v] - mx) : 0.f;
+          se += l[h][v];
+        }
 #pragma unroll
       for (int off = 8; off >= 1; off >>= 1) se += __shfl_xor(se, off);
       const float inv = se > 0.f ? 1.0f / se : 0.f;
-      if (row_ok)
-        for (int a = sub; a < A; a += 16)
-          p.probs[(long)m * A + a] = p.mask[(long)m * A + a] ? expf(lg[a] + p.bc[a] - mx) * inv : 0.f;
+#pragma unroll
+      for (int h = 0; h < NH; ++h)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int a = 4 * (sub + 16 * h) + v;
+          if (row_ok && a < A) p.probs[(long)m * A + a] = l[h][v] * inv;
+        }
     }
     return;
   }
-  if (row_ok && sub == 0)
-    ctrl_row_commit(p, rng, m, bidx, lg[A] + p.bc[A], lg[A + 1] + p.bc[A + 1], row_state(p, m));
+  if (row_ok && sub == 0) ctrl_row_commit(p, rng, m, bidx, lg[A] + br, lg[A + 1] + bd, rs);
 }
 
 namespace {
@@ -933,8 +963,10 @@ hipError_t launch_ctrl(const CtrlArgs& a, hipStream_t s) {
   if (a.M <= kRdCtrlRows && nbtot <= 9 && a.N == 0) {
     const int nb = nbtot <= 1 ? 1 : nbtot <= 2 ? 2 : nbtot <= 3 ? 3 : nbtot <= 5 ? 5 : 9;
     const int smax = nb <= 5 ? 8 : 4;  // register budget
-    const int nw = rd_waves((int)a.ldk, Mfma<DT>::KSLICE, smax, 4);
-    if (nw <= 8 && GemmRD<DT, 9, 1, 4, 512>::lds_bytes(nw) <= kRdLdsMax) {
+    // eight waves where their partial tiles fit the LDS: the K slices of a
+    // wave are a serial chain (a step for one state, K 288: 9.3 us on four)
+    const int nw = rd_waves((int)a.ldk, Mfma<DT>::KSLICE, smax, nb <= 5 ? 8 : 4);
+    if (nw <= 8 && (nb <= 5 || GemmRD<DT, 9, 1, 4, 512>::lds_bytes(nw) <= kRdLdsMax)) {
       switch (nb) {
         case 1: return launch_ctrl_rd<GemmRD<DT, 1, 1, 8, 512>, S>(a, nw, s);
         case 2: return launch_ctrl_rd<GemmRD<DT, 2, 1, 8, 512>, S>(a, nw, s);

@@ -374,9 +374,11 @@ struct GemmRD {
   }
   __device__ static float* E(float* lds) { return lds + (blockDim.x >> 6) * TILE; }
 
-  // w: weight rows n0 .. n0+BN-1; x: activation rows m0 .. m0+BM-1.
-  template <class S>
-  __device__ __forceinline__ static void run(float* lds, const SrcX<DT>& w, const S& x, int Kpad) {
+  // w: weight rows n0 .. n0+BN-1; x: activation rows m0 .. m0+BM-1;
+  // pre(): caller work that does not depend on the product, run while the
+  // operands are in flight
+  template <class S, class Pre = NoWork>
+  __device__ __forceinline__ static void run(float* lds, const SrcX<DT>& w, const S& x, int Kpad, Pre&& pre = Pre{}) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
     const int g = lane >> 4, r16 = lane & 15;
     const int nsl = (Kpad + KSLICE - 1) / KSLICE;
@@ -405,6 +407,7 @@ struct GemmRD {
         for (int j = 0; j < MBW; ++j) xf[j][s] = make_uint4(0, 0, 0, 0);
       }
     }
+    pre();
     f32x4 acc[NBW][MBW];
 #pragma unroll
     for (int i = 0; i < NBW; ++i)
