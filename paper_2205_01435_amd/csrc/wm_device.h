@@ -207,8 +207,16 @@ template <> struct Mfma<bf16_t> {
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
 constexpr uint32_t kOffNone = 0x80000000u;
 
+// The resource's words are made uniform here: p and bytes are the same in every
+// active lane, but the compiler computes some of them (minima, divisions, tile
+// indexes) on the vector unit, and a resource in vector registers is read
+// through a loop over the distinct values of its lanes, one load at a time.
 __device__ __forceinline__ rsrc_t make_rsrc(const void* p, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, 0x00020000);
+  const uint64_t a = reinterpret_cast<uint64_t>(p);
+  const uint64_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a);
+  const uint64_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32));
+  return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(hi << 32 | lo), (short)0,
+                                           __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000);
 }
 __device__ __forceinline__ uint4 bload16(rsrc_t r, uint32_t off) {
   return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));

@@ -108,6 +108,7 @@ __global__ void __launch_bounds__(C::NT) k_mdn(const MdnArgs p) {
   const int J = ntile * WAVES_N + wn;  // dim group of this wave
   const int j = 4 * J + g;             // latent dim of this lane
   const bool head_tile = p.nll_mode && ntile == p.ntd;
+  const bool ctl = p.lh && 2 * ntile >= p.zt;  // a tile of the controller's h part
   // rollout: the actions of this lane's rows and their previous latents
   // (kept by frozen rows), fetched ahead of the GEMM
   int actp[MBW];
@@ -119,12 +120,14 @@ __global__ void __launch_bounds__(C::NT) k_mdn(const MdnArgs p) {
 #pragma unroll
     for (int jj = 0; jj < MBW; ++jj) {
       const int ml = (wmi * MBW + jj) * 16 + (lane & 15);
-      const bool ok = m0 + ml < p.M && j < Z;
+      const bool ok = !ctl && m0 + ml < p.M && j < Z;  // (a call for the h part alone has neither)
       actp[jj] = (int)bload4(ra, ok ? (uint32_t)ml * 4u : kOffNone);
       zpv[jj] = __uint_as_float(bload4(rz, ok ? (uint32_t)(ml * Z + j) * 4u : kOffNone));
     }
   }
-  const SrcX<DT> w(reinterpret_cast<const DT*>(p.Wm), p.ldh, p.ldh, n0, C::BN, p.Nm);
+  const int nc0 = ctl ? n0 - p.zt / 2 * C::BN : 0;  // its first row of W_c
+  const SrcX<DT> w(ctl ? reinterpret_cast<const DT*>(p.Wc) + Z : reinterpret_cast<const DT*>(p.Wm),
+                   ctl ? p.ldk : p.ldh, ctl ? p.ldk - Z : p.ldh, ctl ? nc0 : n0, C::BN, ctl ? p.Nc : p.Nm);
   const SrcX<DT> x(reinterpret_cast<const DT*>(p.x) + p.Z, p.ldx, p.ldx - p.Z, m0, C::BM, p.M);
   const Rng rng{p.k0, p.k1};
   // The four lanes of a row (lane groups g, dims 4J + g) need the same
@@ -149,7 +152,7 @@ __global__ void __launch_bounds__(C::NT) k_mdn(const MdnArgs p) {
     }
   };
   auto pre = [&]() {
-    if (!p.nll_mode) draw_eps();
+    if (!p.nll_mode && !ctl) draw_eps();
   };
   f32x4 acc[Q][MBW];
   if constexpr (kPre)
@@ -158,6 +161,20 @@ __global__ void __launch_bounds__(C::NT) k_mdn(const MdnArgs p) {
     C::run(acc, w, x, (int)p.ldh, reinterpret_cast<DT*>(lds_raw));
   const bool owner = C::kw() == 0;  // holds the summed tile
 
+  if (ctl) {
+    if (!owner) return;  // no barrier below
+#pragma unroll
+    for (int jj = 0; jj < MBW; ++jj) {
+      const int m = m0 + (wmi * MBW + jj) * 16 + (lane & 15);
+      if (m >= p.M) continue;
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        const int n = nc0 + (wn * Q + q) * 16 + 4 * g;
+        if (n < p.Nc) *reinterpret_cast<f32x4*>(p.lh + (long)m * p.Nc + n) = acc[q][jj];
+      }
+    }
+    return;
+  }
   if (head_tile) {
     // Rows 0 and 1 of the block are the reward and done logits.
     if (owner && wn == 0 && g == 0) {
@@ -245,7 +262,9 @@ __global__ void __launch_bounds__(R::MAXT) k_mdn_rd(const MdnArgs p) {
   const int t = threadIdx.x;
   const int d = t & 3, ml = t >> 2;
   const int m = m0 + ml, j = 4 * J + d;
-  const bool mine = t < 4 * R::BM && m < p.M && j < p.Z;
+  const bool ctl = p.lh && J >= p.zt;  // a tile of the controller's h part
+  const int nc0 = (J - p.zt) * R::BN;
+  const bool mine = !ctl && t < 4 * R::BM && m < p.M && j < p.Z;
   const Rng rng{p.k0, p.k1};
   bool live = false;
   float zprev = 0.f;
@@ -255,9 +274,19 @@ __global__ void __launch_bounds__(R::MAXT) k_mdn_rd(const MdnArgs p) {
     if (live) noise = mdn_noise(p, rng, m, j, p.K);
     else zprev = p.z_prev[(long)m * p.Z + j];
   }
-  const SrcX<DT> w(reinterpret_cast<const DT*>(p.Wm), p.ldh, p.ldh, n0, R::BN, p.Nm);
+  const SrcX<DT> w(ctl ? reinterpret_cast<const DT*>(p.Wc) + p.Z : reinterpret_cast<const DT*>(p.Wm),
+                   ctl ? p.ldk : p.ldh, ctl ? p.ldk - p.Z : p.ldh, ctl ? nc0 : n0, R::BN, ctl ? p.Nc : p.Nm);
   const SrcX<DT> x(reinterpret_cast<const DT*>(p.x) + p.Z, p.ldx, p.ldx - p.Z, m0, R::BM, p.M);
   R::run(lds_dyn, w, x, (int)p.ldh);
+  if (ctl) {
+    for (int e = t; e < R::BM * R::BN / 4; e += (int)blockDim.x) {
+      const int r = e / (R::BN / 4), n = 4 * (e % (R::BN / 4));
+      if (m0 + r < p.M && nc0 + n < p.Nc)
+        *reinterpret_cast<float4*>(p.lh + (long)(m0 + r) * p.Nc + nc0 + n) =
+            *reinterpret_cast<const float4*>(R::E(lds_dyn) + r * R::ELD + n);
+    }
+    return;
+  }
   if (!mine) return;
   if (!live) {
     mdn_commit<DT>(p, m, j, zprev);
@@ -291,9 +320,9 @@ template <> struct Cfgs<bf16_t> {
 };
 
 template <class C, typename DT, int KC>
-hipError_t launch_mdn_cfg(MdnArgs a, int ntiles, hipStream_t s) {
+hipError_t launch_mdn_cfg(const char* name, MdnArgs a, int ntiles, hipStream_t s) {
   a.map = tile_map(ntiles, (a.M + C::BM - 1) / C::BM, (size_t)a.Nm * a.ldh * sizeof(DT));
-  return launch("mdn", k_mdn<C, KC>, dim3(grid_of(a.map)), dim3(C::NT), 0, s, a);
+  return launch(name, k_mdn<C, KC>, dim3(grid_of(a.map)), dim3(C::NT), 0, s, a);
 }
 
 // Mixture tile of a call, chosen as the gate tiles are (launch_gates): the
@@ -310,62 +339,90 @@ hipError_t launch_mdn_cfg(MdnArgs a, int ntiles, hipStream_t s) {
 // The tiles of eight waves need whole DMA instructions per wave: an even Q.
 // Register-direct tiles (one dim group x 16 rows) serve rollouts while every
 // CU gets at most one (9.9 us at 256 rows, Z 64; 17.5 at 512).
+struct MdnCost {
+  float c16, c32, c64, c128;  // the tiles of that many rows; INFINITY: none
+  float best() const { return std::min(std::min(c16, c32), std::min(c64, c128)); }
+};
+MdnCost mdn_cost(bool bf16, int Q, int M, int ntiles) {
+  auto cost = [&](int bm, float one, float fixed, float per) {
+    const long n = ((long)ntiles * ((M + bm - 1) / bm) + kCUs - 1) / kCUs;
+    return n == 1 ? one : fixed + per * (float)n;
+  };
+  if (!bf16)
+    return MdnCost{cost(16, 17.0f, 3.0f, 10.6f), cost(32, 18.7f, 3.5f, 14.2f), INFINITY, cost(128, 40.0f, 5.0f, 28.0f)};
+  return MdnCost{INFINITY, cost(32, 10.2f, 2.5f, 6.1f), cost(64, 13.8f, 2.2f, 8.1f),
+                 Q % 2 == 0 ? cost(128, 18.5f, 2.6f, 13.3f) : INFINITY};
+}
+
 template <typename DT, int Q, int KC>
-hipError_t launch_mdn_q(const MdnArgs& a, int ntiles, hipStream_t s) {
+hipError_t launch_mdn_q(const char* name, const MdnArgs& a, int ntiles, hipStream_t s) {
   if (!a.nll_mode) {
     using R = GemmRD<DT, Q, 1, 4, 640>;
     const int nw = rd_waves((int)a.ldh, R::KSLICE, R::SMAX, 4);
     const size_t lds = R::lds_bytes(nw);
-    const long tiles = (long)(a.Z / 4) * ((a.M + R::BM - 1) / R::BM);
+    const int nt = (a.lh ? a.zt + (a.Nc + R::BN - 1) / R::BN : a.Z / 4);  // one dim group per tile
+    const long tiles = (long)nt * ((a.M + R::BM - 1) / R::BM);
     if (tiles <= kCUs && 64 * nw <= R::MAXT && lds <= kRdLdsMax) {
       hipError_t e = allow_lds(k_mdn_rd<R>, lds);
       if (e != hipSuccess) return e;
       MdnArgs b = a;
-      // one dim group per tile
-      b.map = tile_map(a.Z / 4, (a.M + R::BM - 1) / R::BM, (size_t)a.Nm * a.ldh * sizeof(DT));
-      return launch("mdn", k_mdn_rd<R>, dim3(grid_of(b.map)), dim3(64 * nw), lds, s, b);
+      b.map = tile_map(nt, (a.M + R::BM - 1) / R::BM, (size_t)a.Nm * a.ldh * sizeof(DT));
+      return launch(name, k_mdn_rd<R>, dim3(grid_of(b.map)), dim3(64 * nw), lds, s, b);
     }
   }
   using Cf = Cfgs<DT>;
-  auto cost = [&](int bm, float one, float fixed, float per) {
-    const long n = ((long)ntiles * ((a.M + bm - 1) / bm) + kCUs - 1) / kCUs;
-    return n == 1 ? one : fixed + per * (float)n;
-  };
-  if constexpr (sizeof(DT) == 4) {
-    if (cost(128, 40.0f, 5.0f, 28.0f) <= cost(32, 18.7f, 3.5f, 14.2f))
-      return launch_mdn_cfg<typename Cf::template Mdn128<Q>, DT, KC>(a, ntiles, s);
-    if (cost(16, 17.0f, 3.0f, 10.6f) <= cost(32, 18.7f, 3.5f, 14.2f))
-      return launch_mdn_cfg<typename Cf::template Mdn16<Q>, DT, KC>(a, ntiles, s);
-  } else {
-    const float c32 = cost(32, 10.2f, 2.5f, 6.1f), c64 = cost(64, 13.8f, 2.2f, 8.1f);
-    if constexpr (Q % 2 == 0) {
-      if (cost(128, 18.5f, 2.6f, 13.3f) < std::min(c32, c64))
-        return launch_mdn_cfg<typename Cf::template Mdn128<Q>, DT, KC>(a, ntiles, s);
-    }
-    if (c64 <= c32) return launch_mdn_cfg<typename Cf::template Mdn64<Q>, DT, KC>(a, ntiles, s);
+  if (a.lh) ntiles = a.zt / 2 + (a.Nc + 32 * Q - 1) / (32 * Q);
+  const MdnCost c = mdn_cost(sizeof(DT) == 2, Q, a.M, ntiles);
+  if constexpr (Q % 2 == 0 || sizeof(DT) == 4) {
+    if (c.c128 <= c.best()) return launch_mdn_cfg<typename Cf::template Mdn128<Q>, DT, KC>(name, a, ntiles, s);
   }
-  return launch_mdn_cfg<typename Cf::template Mdn32<Q>, DT, KC>(a, ntiles, s);
+  if constexpr (sizeof(DT) == 2) {
+    if (c.c64 <= c.c32) return launch_mdn_cfg<typename Cf::template Mdn64<Q>, DT, KC>(name, a, ntiles, s);
+  } else {
+    if (c.c16 <= c.c32) return launch_mdn_cfg<typename Cf::template Mdn16<Q>, DT, KC>(name, a, ntiles, s);
+  }
+  return launch_mdn_cfg<typename Cf::template Mdn32<Q>, DT, KC>(name, a, ntiles, s);
+}
+
+// one instantiation per component count K (which fixes Q = ceil(3K / 4))
+template <typename DT>
+hipError_t launch_mdn_k(const char* name, const MdnArgs& a, int Q, int ntiles, hipStream_t s) {
+  if (a.K < 1 || a.K > 8 || Q != (3 * a.K + 3) / 4) return hipErrorInvalidValue;
+  switch (a.K) {
+    case 1: return launch_mdn_q<DT, 1, 1>(name, a, ntiles, s);
+    case 2: return launch_mdn_q<DT, 2, 2>(name, a, ntiles, s);
+    case 3: return launch_mdn_q<DT, 3, 3>(name, a, ntiles, s);
+    case 4: return launch_mdn_q<DT, 3, 4>(name, a, ntiles, s);
+    case 5: return launch_mdn_q<DT, 4, 5>(name, a, ntiles, s);
+    case 6: return launch_mdn_q<DT, 5, 6>(name, a, ntiles, s);
+    case 7: return launch_mdn_q<DT, 6, 7>(name, a, ntiles, s);
+    default: return launch_mdn_q<DT, 6, 8>(name, a, ntiles, s);
+  }
 }
 
 }  // namespace
 
-// one instantiation per component count K (which fixes Q = ceil(3K / 4))
 template <typename DT>
 hipError_t launch_mdn(const MdnArgs& a, int Q, int ntiles, hipStream_t s) {
-  if (a.K < 1 || a.K > 8 || Q != (3 * a.K + 3) / 4) return hipErrorInvalidValue;
-  switch (a.K) {
-    case 1: return launch_mdn_q<DT, 1, 1>(a, ntiles, s);
-    case 2: return launch_mdn_q<DT, 2, 2>(a, ntiles, s);
-    case 3: return launch_mdn_q<DT, 3, 3>(a, ntiles, s);
-    case 4: return launch_mdn_q<DT, 3, 4>(a, ntiles, s);
-    case 5: return launch_mdn_q<DT, 4, 5>(a, ntiles, s);
-    case 6: return launch_mdn_q<DT, 5, 6>(a, ntiles, s);
-    case 7: return launch_mdn_q<DT, 6, 7>(a, ntiles, s);
-    default: return launch_mdn_q<DT, 6, 8>(a, ntiles, s);
-  }
+  return launch_mdn_k<DT>("mdn", a, Q, ntiles, s);
+}
+
+bool ctrl_h_wanted(const Layout& L, int B) {
+  if (L.Z + L.ldh > L.ldk) return false;
+  if (L.N > 0 && L.Nc / 16 > 20) return false;
+  const float with = mdn_cost(L.dt == 1, L.Q, B, L.Z / 8 + (L.Nc + 32 * L.Q - 1) / (32 * L.Q)).best();
+  return with <= mdn_cost(L.dt == 1, L.Q, B, L.Z / 8).best() + 5.0f;
+}
+
+template <typename DT>
+hipError_t launch_ctrl_h(MdnArgs a, int Q, hipStream_t s) {
+  a.zt = 0;
+  return launch_mdn_k<DT>("lh", a, Q, 0, s);
 }
 
 template hipError_t launch_mdn<float>(const MdnArgs&, int, int, hipStream_t);
 template hipError_t launch_mdn<bf16_t>(const MdnArgs&, int, int, hipStream_t);
+template hipError_t launch_ctrl_h<float>(MdnArgs, int, hipStream_t);
+template hipError_t launch_ctrl_h<bf16_t>(MdnArgs, int, hipStream_t);
 
 }  // namespace wm

@@ -91,17 +91,6 @@ __global__ void __launch_bounds__(256) k_planes_zero(uint4* p, long n) {
 // ---------------------------------------------------------------------------
 // the product: acc[i][j] += sum over this wave's slices of A block i . B block j
 // ---------------------------------------------------------------------------
-// A resource whose words are uniform by construction: the tile indexes come
-// out of a division on the vector unit, and a resource built from them as they
-// are is read through a loop over the distinct values of its lanes, one load
-// at a time (20.4 against 9.5 us per reverse step at B = H = 512).
-__device__ __forceinline__ rsrc_t uniform_rsrc(const char* base, uint32_t bytes) {
-  const uint64_t a = reinterpret_cast<uint64_t>(base);
-  const uint64_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a);
-  const uint64_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32));
-  return make_rsrc(reinterpret_cast<const char*>(hi << 32 | lo), (uint32_t)__builtin_amdgcn_readfirstlane((int)bytes));
-}
-
 // One operand's planes of a tile: row blocks R0 .. (those at or past `rb`
 // read as zero) of a matrix of S slices.
 struct PlaneSrc {
@@ -111,7 +100,7 @@ struct PlaneSrc {
   __device__ PlaneSrc(const char* base, int S, int R0, int rb) {
     stride = (uint32_t)S * kFrag;
     left = max(0, rb - R0);
-    r = uniform_rsrc(base + (long)R0 * stride, (uint32_t)min(left, 8) * stride);
+    r = make_rsrc(base + (long)R0 * stride, (uint32_t)min(left, 8) * stride);
   }
   // term p of row block i, slice s (uniform), 16 bytes at lane offset lo
   // (kOffNone: zeros)

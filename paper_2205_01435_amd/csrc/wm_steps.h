@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include "wm_gemm.h"
+#include "wm_layout.h"
 
 namespace wm {
 
@@ -47,6 +48,14 @@ struct MdnArgs {
   float* head;         // [M, 2]
   int ntd;
   int nll_mode;
+  // rollout, with lh: tiles past the zt groups of four latent dims compute the
+  // next step's controller logits' h part, lh[m][n] = W_c[n][Z ..] . h_t+1
+  // (bias not added), [M, Nc] fp32; zt = 0: only those
+  int zt;
+  const void* Wc;
+  long ldk;
+  int Nc;
+  float* lh;
   TileMap map;
 };
 
@@ -87,6 +96,7 @@ struct CtrlArgs {
   float* logits_out;
   long ldl;
   int ncol;
+  const float* lh;  // rollout: the logits' h part [M, Nc] (k_ctrl_z), null: zero
   float* lg_ws;  // rollout workspace [M, Nc] for those logits (wide two-level controllers)
   TileMap map;   // of k_ctrl_logits
 };
@@ -100,5 +110,18 @@ template <typename DT>
 hipError_t launch_mdn(const MdnArgs& a, int Q, int ntiles, hipStream_t s);
 template <class S>
 hipError_t launch_ctrl(const CtrlArgs& a, hipStream_t s);
+// Whether a rollout computes the controller's h part beside the mixture: the
+// matrix rows of W_c then need to be readable Z + ldh wide, the two-level
+// controller's logits to fit k_ctrl_z's staged rows, and the extra tiles to
+// cost the mixture launch less than the deeper product costs the controller
+// (about 6 us; at B 4096, where they would start a second round of tiles, they
+// cost 10).
+bool ctrl_h_wanted(const Layout& L, int B);
+// The controller's h part alone (MdnArgs::lh, zt = 0), and the rollout's
+// decision from it.
+template <typename DT>
+hipError_t launch_ctrl_h(MdnArgs a, int Q, hipStream_t s);
+template <typename DT>
+hipError_t launch_ctrl_z(const CtrlArgs& a, hipStream_t s);
 
 }  // namespace wm

@@ -12,6 +12,7 @@ import torch
 import parity
 from paper_2205_01435_amd import _lib as wmlib
 from test_gpu_edges import _case
+from test_gpu_two_level import _inputs as two_level_inputs
 
 pytestmark = pytest.mark.gpu
 
@@ -65,3 +66,54 @@ def test_tiles(B, Z, H, A, K, dtype, monkeypatch):
     ties, live = parity.reanchored(w.dims, inp["weights"], inp["mask"][rows], g, seed=41, tau=1.2, done_flag=True,
                                    dtype=dtype, traj=rows, done0=done0[rows])
     assert live > 0
+
+
+# B, Z, H, A (or N, L), K, dtype: controllers whose h part comes from the
+# mixture launches
+H_PART = [
+    (1, 8, 64, 1, 0, 0, 1, "fp32"),          # one row, one action
+    (33, 40, 64, 61, 0, 0, 3, "fp32"),       # Z ends inside a K slice; reward row in the next block
+    (100, 72, 192, 62, 0, 0, 8, "bf16"),     # three K slices of z; A + 2 = 64
+    (301, 128, 256, 300, 0, 0, 5, "bf16"),   # two rounds of blocks per wave
+    (45, 16, 64, 1500, 0, 0, 2, "bf16"),     # many rounds
+    (77, 24, 128, 0, 9, 30, 3, "fp32"),      # two levels
+    (130, 64, 256, 0, 80, 200, 8, "bf16"),
+]
+
+
+@pytest.mark.parametrize("B,Z,H,A,N,L,K,dtype", H_PART)
+def test_controller_h_part(B, Z, H, A, N, L, K, dtype, monkeypatch):
+    """Per-step rollouts with the controller's h part beside the mixture, from
+    a given state, against the oracle, and against the same call in a
+    workspace that has no room for it."""
+    print("[gpu-tiles] h part", B, Z, H, A, N, L, K, dtype, flush=True)
+    monkeypatch.setenv("WM_PERSISTENT", "0")
+    cuda = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    T = 3
+    if N:
+        A = N * L
+        w, z0, xm, lm = two_level_inputs(B, T, Z, H, N, L, K, seed=B)
+        mask, dmask, dims = (xm, lm), (cuda(xm), cuda(lm)), dict(Z=Z, H=H, A=A, K=K)
+        kw = dict(two_level=(N, L))
+    else:
+        wk, inp = _case(B, T, Z, H, A, K, dtype)
+        w, z0, mask, dims, kw = inp["weights"], inp["z0"], inp["mask"], wk.dims, {}
+        dmask = cuda(mask)
+    m = wmlib.pack(w, Z, H, A, K, dtype, N=N, L=L)
+    rng = np.random.default_rng(B)
+    h0 = np.tanh(rng.standard_normal((B, H))).astype(np.float32)
+    done0 = (np.arange(B) % 5 == 2).astype(np.uint8)
+    args = dict(T=T, seed=43, tau=1.0, done=True, trace=True, h0=cuda(h0))
+    out = []
+    ac = N + 1 + L if N else A
+    part = (B * ((ac + 2 + 15) // 16 * 16) * 4 + 255) // 256 * 256
+    for less in (0, part):
+        b = wmlib.RolloutBuffers(m, B, T, trace=True)
+        b.ws_bytes -= less
+        wmlib.rollout(m, cuda(z0), dmask, bufs=b, done_io=cuda(done0), **args)
+        torch.cuda.synchronize()
+        out.append({k: getattr(b, k).cpu().numpy()
+                    for k in ("z_out", "actions", "rewards", "dones", "h_trace", "c_trace")})
+        parity.reanchored(dims, w, mask, out[-1], seed=43, tau=1.0, done_flag=True, dtype=dtype, done0=done0, **kw)
+    same = np.all(out[0]["actions"] == out[1]["actions"], axis=0)
+    assert same.mean() >= 0.97
