@@ -512,6 +512,7 @@ hipError_t gemm_nt(const float* A, long lda, int M, const float* Bm, long ldb, i
 // twice the CUs, two work-groups each.  (A slice of 2048 rows whatever the
 // product left 4500-row products on 84 to 144 of the CUs: 197 us each.)
 int tn_rows(int M, int N, long K) {
+  K = std::max(K, 1L);  // (a size query over no steps)
   const long tiles = (long)((M + kTnBM - 1) / kTnBM) * ((N + kTnBN - 1) / kTnBN);
   long S = (K + kMaxSliceK - 1) / kMaxSliceK;
   while (S * tiles < 2 * kCUs && K / (2 * S) >= 256) S *= 2;
