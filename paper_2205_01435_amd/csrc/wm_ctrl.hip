@@ -245,11 +245,11 @@ __global__ void __launch_bounds__(256) k_ctrl_rows(const CtrlArgs p) {
   const uint32_t traj = p.traj0 + (uint32_t)m;
   const int N = p.N, NX = N + 1, Lc = p.Lc, Ar = NX + Lc;
   const int ncol = p.mode == 0 ? Ar : Ar + 2;
-  const rsrc_t rl = make_rsrc(lg, (uint32_t)ncol * 4u);
-  const rsrc_t rb = make_rsrc(p.bc, (uint32_t)p.Nc * 4u);
-  const rsrc_t rx = make_rsrc(p.mask + (long)m * NX, (uint32_t)NX);
+  const rsrc_t rl = uniform_rsrc(lg, (uint32_t)ncol * 4u);
+  const rsrc_t rb = uniform_rsrc(p.bc, (uint32_t)p.Nc * 4u);
+  const rsrc_t rx = uniform_rsrc(p.mask + (long)m * NX, (uint32_t)NX);
   // location masks of the row's xfers (N Lc bytes; below 2^20)
-  const rsrc_t rlm = make_rsrc(p.mask + (long)p.M * NX + (long)m * N * Lc, (uint32_t)(N * Lc));
+  const rsrc_t rlm = uniform_rsrc(p.mask + (long)p.M * NX + (long)m * N * Lc, (uint32_t)(N * Lc));
   int x = -1, a = -1;
   RowLogits lx, ll;
   uint32_t mx = 0, ml = 0;
@@ -626,7 +626,7 @@ __global__ void __launch_bounds__(C::NT) k_ctrl(const CtrlArgs p) {
 
   // mask words of this thread's actions, ahead of the GEMM
   uint32_t mk[MAXB];
-  const rsrc_t rmask = make_rsrc(p.mask + (long)m0 * A, (uint32_t)(max(0, min(BM, p.M - m0)) * A));
+  const rsrc_t rmask = uniform_rsrc(p.mask + (long)m0 * A, (uint32_t)(max(0, min(BM, p.M - m0)) * A));
   const bool words = (A & 3) == 0 && (reinterpret_cast<uintptr_t>(p.mask) & 3) == 0;
 #pragma unroll
   for (int b = 0; b < MAXB; ++b) {
@@ -772,8 +772,8 @@ __global__ void __launch_bounds__(R::MAXT) k_ctrl_rd(const CtrlArgs p) {
   const bool row_ok = wave < 4 && m < p.M;
   const int A = p.A;
   constexpr int NH = (R::BN + 63) / 64;  // blocks of four actions per lane
-  const rsrc_t rm = make_rsrc(p.mask + (long)m0 * A, (uint32_t)(min(R::BM, p.M - m0) * A));
-  const rsrc_t rb = make_rsrc(p.bc, (uint32_t)p.Nc * 4u);
+  const rsrc_t rm = uniform_rsrc(p.mask + (long)m0 * A, (uint32_t)(min(R::BM, p.M - m0) * A));
+  const rsrc_t rb = uniform_rsrc(p.bc, (uint32_t)p.Nc * 4u);
   const bool pick = row_ok && p.mode != 2;
   uint32_t mb[NH][4];
   float4 bias[NH];
@@ -890,9 +890,9 @@ __global__ void __launch_bounds__(256) k_ctrl_z(const CtrlArgs p) {
   if (tid < 16 && m < p.M) rs = row_state(p, m);
   const SrcX<DT> w(reinterpret_cast<const DT*>(p.Wc), p.ldk, p.ldk, 0, p.Nc, p.Nc);
   const SrcX<DT> x(reinterpret_cast<const DT*>(p.x), p.ldx, p.ldx, m0, 16, p.M);
-  const rsrc_t rl = make_rsrc(p.lh ? p.lh + (long)m0 * p.Nc : nullptr, p.lh ? (uint32_t)(rows * p.Nc) * 4u : 0u);
-  const rsrc_t rb = make_rsrc(p.bc, (uint32_t)p.Nc * 4u);
-  const rsrc_t rm = make_rsrc(p.mask + (long)m0 * A, (uint32_t)(rows * A));
+  const rsrc_t rl = uniform_rsrc(p.lh ? p.lh + (long)m0 * p.Nc : nullptr, p.lh ? (uint32_t)(rows * p.Nc) * 4u : 0u);
+  const rsrc_t rb = uniform_rsrc(p.bc, (uint32_t)p.Nc * 4u);
+  const rsrc_t rm = uniform_rsrc(p.mask + (long)m0 * A, (uint32_t)(rows * A));
   const Rng rng{p.k0, p.k1};
   const uint32_t traj = p.traj0 + (uint32_t)m;
   const int ns = (p.Z + KS - 1) / KS;

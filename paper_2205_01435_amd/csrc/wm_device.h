@@ -207,16 +207,20 @@ template <> struct Mfma<bf16_t> {
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
 constexpr uint32_t kOffNone = 0x80000000u;
 
-// The resource's words are made uniform here: p and bytes are the same in every
+__device__ __forceinline__ rsrc_t make_rsrc(const void* p, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, 0x00020000);
+}
+// The same with its words made uniform: p and bytes are the same in every
 // active lane, but the compiler computes some of them (minima, divisions, tile
 // indexes) on the vector unit, and a resource in vector registers is read
 // through a loop over the distinct values of its lanes, one load at a time.
-__device__ __forceinline__ rsrc_t make_rsrc(const void* p, uint32_t bytes) {
+// (Where the compiler keeps them in scalar registers by itself, as in the
+// persistent kernels, the moves only cost: tiny rollout 219 -> 223 us.)
+__device__ __forceinline__ rsrc_t uniform_rsrc(const void* p, uint32_t bytes) {
   const uint64_t a = reinterpret_cast<uint64_t>(p);
   const uint64_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a);
   const uint64_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32));
-  return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(hi << 32 | lo), (short)0,
-                                           __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000);
+  return make_rsrc(reinterpret_cast<void*>(hi << 32 | lo), (uint32_t)__builtin_amdgcn_readfirstlane((int)bytes));
 }
 __device__ __forceinline__ uint4 bload16(rsrc_t r, uint32_t off) {
   return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));
@@ -300,7 +304,7 @@ struct SrcX {
     ldb = (uint32_t)(ld * (long)sizeof(DT));
     base = x + (long)m0 * ld;
     bytes = mval ? (uint32_t)(((mval - 1) * ld + span) * (long)sizeof(DT)) : 0u;
-    r = make_rsrc(base, bytes);
+    r = uniform_rsrc(base, bytes);
   }
   __device__ Row row(int i) const { return (uint32_t)i * ldb; }
   __device__ uint4 load(Row ro, int k, int Kpad) const {
@@ -322,8 +326,8 @@ struct SrcZH {
     Kx = Z_ + H;
     zb = (uint32_t)Z_ * 4u;
     hb = (uint32_t)H * 4u;
-    rz = make_rsrc(z + (long)m0 * Z_, (uint32_t)(mval * Z_ * 4));
-    rh = make_rsrc(h + (long)m0 * H, (uint32_t)(mval * H * 4));
+    rz = uniform_rsrc(z + (long)m0 * Z_, (uint32_t)(mval * Z_ * 4));
+    rh = uniform_rsrc(h + (long)m0 * H, (uint32_t)(mval * H * 4));
   }
   __device__ Row row(int i) const { return make_uint2((uint32_t)i * zb, (uint32_t)i * hb); }
   __device__ uint4 load(Row ro, int k, int /*Kpad*/) const {

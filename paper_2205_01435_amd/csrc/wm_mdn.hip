@@ -115,8 +115,8 @@ __global__ void __launch_bounds__(C::NT) k_mdn(const MdnArgs p) {
   float zpv[MBW];
   if (!p.nll_mode) {
     const long mval = max(0, min(C::BM, p.M - m0));
-    const rsrc_t ra = make_rsrc(p.act + m0, (uint32_t)(mval * 4));
-    const rsrc_t rz = make_rsrc(p.z_prev + (long)m0 * Z, (uint32_t)(mval * Z * 4));
+    const rsrc_t ra = uniform_rsrc(p.act + m0, (uint32_t)(mval * 4));
+    const rsrc_t rz = uniform_rsrc(p.z_prev + (long)m0 * Z, (uint32_t)(mval * Z * 4));
 #pragma unroll
     for (int jj = 0; jj < MBW; ++jj) {
       const int ml = (wmi * MBW + jj) * 16 + (lane & 15);

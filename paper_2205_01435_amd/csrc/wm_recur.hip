@@ -100,7 +100,7 @@ struct PlaneSrc {
   __device__ PlaneSrc(const char* base, int S, int R0, int rb) {
     stride = (uint32_t)S * kFrag;
     left = max(0, rb - R0);
-    r = make_rsrc(base + (long)R0 * stride, (uint32_t)min(left, 8) * stride);
+    r = uniform_rsrc(base + (long)R0 * stride, (uint32_t)min(left, 8) * stride);
   }
   // term p of row block i, slice s (uniform), 16 bytes at lane offset lo
   // (kOffNone: zeros)
@@ -192,8 +192,8 @@ __global__ void __launch_bounds__(256, 1) k_recur_fwd(const FwdArgs p) {
   const int H = p.H, m = 16 * (mt * MB + wave) + r16, u0 = 16 * nt + 4 * g;
   const bool ok = wave < MB && m < p.B;
   // the epilogue's inputs, ahead of the product
-  const rsrc_t rb = make_rsrc(p.bg, (uint32_t)(16 * H));
-  const rsrc_t rw = make_rsrc(p.WaT, (uint32_t)((long)p.A * 16 * H));
+  const rsrc_t rb = uniform_rsrc(p.bg, (uint32_t)(16 * H));
+  const rsrc_t rw = uniform_rsrc(p.WaT, (uint32_t)((long)p.A * 16 * H));
   const int a = ok ? p.act[m] : -1;
   float4 bias[4], wa[4];
 #pragma unroll
