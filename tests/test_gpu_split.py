@@ -27,6 +27,7 @@ def gpu():
     (31, 97, 23, 24, 272, 70, 8),   # 2231 rows: several slices, the last short of a chunk
     (32, 33, 31, 40, 144, 9, 5),    # 1023 rows; 192 and 592 product columns
     (33, 5, 3, 8, 16, 3, 1),        # fewer rows than one chunk
+    (34, 700, 25, 8, 16, 1, 1),     # one action: every row of a block in its list, a second block in each chunk
 ])
 def test_grad_slices(seed, B, T, Z, H, A, K):
     ln = np.random.default_rng(seed).integers(0, T + 1, size=B).astype(np.int32)
