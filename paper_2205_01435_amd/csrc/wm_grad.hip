@@ -176,6 +176,23 @@ __global__ void __launch_bounds__(256) k_grad_heads(float* M, long ldm, const fl
     for (int v = 0; v < 4; ++v) row[16 * Q * J + 16 * q + 4 * g + v] = d[4 * q + v];
 }
 
+// add(part[k n]) for k = 0 .. S - 1 in order, eight loads in flight (the sums
+// over slices are bound by reading them, and have too few threads to hide the
+// latency of one load after the other: the four sums of a training step at
+// 65536 rows, H 512 took 102 us so, 49 us now)
+template <class F>
+__device__ __forceinline__ void each_slice(const float* part, long n, int S, F&& add) {
+  int k = 0;
+  for (; k + 8 <= S; k += 8) {
+    float v[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] = part[(long)(k + q) * n];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) add(v[q]);
+  }
+  for (; k < S; ++k) add(part[(long)k * n]);
+}
+
 // one-hot columns: dWa[a][j] = sum over rows r with action a of dG[r][j].
 // Block (256-column tile, row chunk, group of 64 actions): each thread owns
 // one column and accumulates the chunk's rows in row order into an LDS slot
@@ -247,7 +264,7 @@ __global__ void __launch_bounds__(256) k_grad_actions_sum(const float* part, lon
   const long i = (long)blockIdx.x * 256 + threadIdx.x;
   if (i >= n) return;
   float s = 0.f;
-  for (int ch = 0; ch < nchunk; ++ch) s += part[(long)ch * n + i];
+  each_slice(part + i, n, nchunk, [&](float v) { s += v; });
   out[i] = s;
 }
 
@@ -513,7 +530,7 @@ __global__ void __launch_bounds__(256) k_sum_slices(const float* part, int S, in
   if (i >= (long)M * N) return;
   const long mn = (long)M * N;
   double acc = 0.0;
-  for (int k = 0; k < S; ++k) acc += (double)part[k * mn + i];
+  each_slice(part + i, mn, S, [&](float v) { acc += (double)v; });
   out[(i / N) * ldo + i % N] = (float)acc;
 }
 
