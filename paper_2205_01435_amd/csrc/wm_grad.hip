@@ -39,8 +39,8 @@ static constexpr float kHalfLn2Pi = 0.91893853320467274178f;
 // ===========================================================================
 namespace {
 
-using GradGemm = GemmD<float, 4, 4, 2, 2, 2, true>;   // 128 x 128 tiles: the products over all rows
-using GradGemmS = GemmD<float, 2, 2, 2, 2, 2, true>;  // 64 x 64 tiles: the same over few
+using GradGemm = GemmD<float, 4, 2, 2, 2, 2>;   // 128 x 64 tiles: the products over all rows
+using GradGemmS = GemmD<float, 2, 2, 2, 2, 2>;  // 64 x 64 tiles: the per-step product dG_t . W_h
 
 // out[m][n] = sum_{k < Kpad} A[m][k] B[n][k] for m < M, n < N (Kpad a
 // multiple of 32; columns of A and B up to Kpad must be readable, zero
@@ -93,6 +93,32 @@ __global__ void k_len_sum(const int32_t* lengths, int B, int T, float* nout) {
 }
 
 __device__ __forceinline__ float sig_(float x) { return 1.0f / (1.0f + expf(-x)); }
+
+// forward scan of one (row b, unit u): pre-activations G (packed gate
+// order, row r = t B + b, column 4u + q) plus bias and the action's column
+// -> activations i, f, tanh g, o in place; c_t into Cs [T+1, B, H]
+__global__ void __launch_bounds__(256) k_grad_fwd_scan(float* G, const float* bg, const float* WaT,
+                                                       const int32_t* actions, float* Cs, int B, int T, int H,
+                                                       int A) {
+  const long idx = (long)blockIdx.x * 256 + threadIdx.x;
+  if (idx >= (long)B * H) return;
+  const int b = (int)(idx / H), u = (int)(idx % H);
+  const float4 bias = reinterpret_cast<const float4*>(bg)[u];
+  float c = 0.f;
+  Cs[(long)b * H + u] = 0.f;
+  for (int t = 0; t < T; ++t) {
+    const long r = (long)t * B + b;
+    float4 g = reinterpret_cast<float4*>(G + r * 4 * H)[u];
+    const int a = actions[r];
+    float4 w = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (a >= 0 && a < A) w = reinterpret_cast<const float4*>(WaT + (long)a * 4 * H)[u];
+    const float i = sig_(g.x + bias.x + w.x), f = sig_(g.y + bias.y + w.y);
+    const float gg = tanhf(g.z + bias.z + w.z), o = sig_(g.w + bias.w + w.w);
+    c = f * c + i * gg;
+    reinterpret_cast<float4*>(G + r * 4 * H)[u] = make_float4(i, f, gg, o);
+    Cs[((long)(t + 1) * B + b) * H + u] = c;
+  }
+}
 
 // d loss / d head output of one row r = t B + b: for each latent dim j the
 // mixture features of packed rows 16 Q J + 16 q + 4 g + v (j = 4J + g,
@@ -174,6 +200,36 @@ __global__ void __launch_bounds__(256) k_grad_heads(float* M, long ldm, const fl
   for (int q = 0; q < Q; ++q)
 #pragma unroll
     for (int v = 0; v < 4; ++v) row[16 * Q * J + 16 * q + 4 * g + v] = d[4 * q + v];
+}
+
+// LSTM backward of step t for (row b, unit u): with dh = d loss / d h_{t+1}
+// (heads + the later steps) and dc = d loss / d c_{t+1} from the later steps,
+// writes dG_t (pre-activation gradients, packed gate order) and the new dc
+// (dhr: S slices [S, B, H] of the later step's dG . W_h, summed in order)
+__global__ void __launch_bounds__(256) k_grad_lstm_back(const float* G, const float* Cs, const float* dhh,
+                                                        const float* dhr, int S, float* dc, float* dG, int B,
+                                                        int H, int t, int last) {
+  const long idx = (long)blockIdx.x * 256 + threadIdx.x;
+  if (idx >= (long)B * H) return;
+  const int b = (int)(idx / H), u = (int)(idx % H);
+  const long r = (long)t * B + b;
+  const float4 a = reinterpret_cast<const float4*>(G + r * 4 * H)[u];  // i, f, g, o
+  const float c1 = Cs[((long)(t + 1) * B + b) * H + u], c0 = Cs[((long)t * B + b) * H + u];
+  float dh = dhh[r * H + u];
+  if (!last) {
+    float sum = 0.f;
+    for (int k = 0; k < S; ++k) sum += dhr[(long)k * B * H + (long)b * H + u];
+    dh += sum;
+  }
+  const float dcn = last ? 0.f : dc[(long)b * H + u];
+  const float th = tanhf(c1);
+  const float d_o = dh * th;
+  const float dcc = dcn + dh * a.w * (1.0f - th * th);
+  const float d_i = dcc * a.z, d_f = dcc * c0, d_g = dcc * a.x;
+  dc[(long)b * H + u] = dcc * a.y;
+  reinterpret_cast<float4*>(dG + r * 4 * H)[u] =
+      make_float4(d_i * a.x * (1.0f - a.x), d_f * a.y * (1.0f - a.y), d_g * (1.0f - a.z * a.z),
+                  d_o * a.w * (1.0f - a.w));
 }
 
 // add(part[k n]) for k = 0 .. S - 1 in order, eight loads in flight (the sums
@@ -352,6 +408,10 @@ int split_of(int M, int N, int Kpad, long target = 512) {
   return S;
 }
 
+// the per-step product: its tile shape and K slices
+using BpttGemm = GradGemmS;
+int bptt_split(int B, int H) { return split_of<BpttGemm>(B, H, 4 * H, 256); }
+
 // out (ldo) = A . B^T in S K-slices; S > 1 writes slice y to out + y oslice
 template <class C = GradGemm>
 hipError_t gemm_nt_slices(const char* name, const float* A, long lda, int M, const float* Bm, long ldb, int N,
@@ -373,21 +433,19 @@ __global__ void __launch_bounds__(256) k_zero(float* x, long n) {
 // row-major with the reduction over their rows (the weight-gradient products
 // over the T B rows read their activation and gradient matrices as stored,
 // no transposed copies).  K slice s covers rows [s Ks, (s+1) Ks) and writes
-// its own partial [M, N] (summed in fp64 afterwards).  128 x 128 tiles, four
-// waves of 64 x 64; chunks of 32 rows reach LDS by LDS-DMA, double buffered
-// (64 KB, so that two work-groups share a CU).  The products run on the bf16
-// matrix unit from three-term splits (split3): lane group g of a fragment
-// takes rows 4g + j and 16 + 4g + j, j < 4, of a chunk.  The 16-byte pieces of
-// staged row k are XOR-permuted by ((k/4) mod 4) * 4, so that the four lane
-// groups read four distinct 64-byte bank windows.  SUMA / SUMB: the
-// work-groups of the first tile column / row also sum A's / B's columns over
-// their rows (extra products against ones) into colsum partials [S, M] /
-// [S, N].  Bound by the VALU work of the splits next to the MFMAs.
-// Work-group -> tile: XCD x takes the x-th eighth of (slice, tile) pairs,
-// slice by slice with m fastest, so that a slice's rows are shared in one L2.
+// its own partial [M, N] (summed in fp64 afterwards).  128 x 64 tiles, four
+// waves of 64 x 32; chunks of 16 rows reach LDS by LDS-DMA in a ring of four
+// stages.  A fragment read takes rows 4g + j, j < 4, of a chunk (one MFMA
+// each): the 16-byte pieces of staged row k are XOR-permuted by ((k/4) mod 4)
+// * 4, so that the four lane groups g read four distinct 64-byte bank
+// windows.  SUMA / SUMB: the work-groups of the first tile column / row also
+// sum A's / B's columns over their rows (an extra MFMA block against ones)
+// into colsum partials [S, M] / [S, N].  Work-group -> tile: XCD x takes
+// the slices s = x mod 8, each slice's tiles m fastest, so that a slice's
+// rows are shared in one L2.
 // ===========================================================================
-constexpr int kTnBM = 128, kTnBN = 128, kTnBK = 32, kTnStages = 2;
-constexpr int kTnStageBytes = (kTnBM + kTnBN) * kTnBK * 4;  // 32 KB: A rows, then B rows
+constexpr int kTnBM = 128, kTnBN = 64, kTnBK = 16, kTnStages = 4;
+constexpr int kTnStageBytes = (kTnBM + kTnBN) * kTnBK * 4;  // 12 KB: A rows, then B rows
 
 struct TnArgs {
   const float* A;
@@ -403,11 +461,11 @@ __global__ void __launch_bounds__(256) k_gemm_tn(const TnArgs p) {
   __shared__ __attribute__((aligned(1024))) char lds[kTnStages * kTnStageBytes];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 4, r16 = lane & 15;
-  const int per = p.ntm * p.ntn, total = p.S * per;
-  const int idx = (int)(blockIdx.x & 7) * ((total + 7) / 8) + (int)(blockIdx.x >> 3);
-  if (idx >= total) return;
-  const int sl = idx / per;
-  const int nt = (idx % per) / p.ntm, mt = (idx % per) % p.ntm;
+  const int x = blockIdx.x & 7, r = blockIdx.x >> 3;
+  const int per = p.ntm * p.ntn;
+  const int sl = x + 8 * (r / per);
+  if (sl >= p.S) return;
+  const int nt = (r % per) / p.ntm, mt = (r % per) % p.ntm;
   const int m0 = mt * kTnBM, n0 = nt * kTnBN;
   const long k0 = (long)sl * p.Ks;
   const long k1 = min(p.K, k0 + (long)p.Ks);
@@ -416,74 +474,76 @@ __global__ void __launch_bounds__(256) k_gemm_tn(const TnArgs p) {
   const u32x4 ra = rsrc_words(p.A + k0 * p.lda, (uint32_t)((k1 - k0) * p.lda * 4));
   const u32x4 rb = rsrc_words(p.Bm + k0 * p.ldb, (uint32_t)((k1 - k0) * p.ldb * 4));
   const uint32_t lds0 = (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) char*)lds);
-  // this wave's eight DMA instructions per chunk, two rows of 32 pieces each:
-  // waves 0 and 1 stage A's rows, 2 and 3 B's
-  const bool isa = wave < 2;
-  const long ld = isa ? p.lda : p.ldb;
-  uint32_t off[8];
+  // this wave's three DMA instructions per chunk: q < 8 stage A rows 2q, 2q+1
+  // (32 pieces each), q >= 8 B rows 4(q-8) .. +3 (16 pieces each)
+  bool isa[3];
+  uint32_t off[3];
 #pragma unroll
-  for (int t = 0; t < 8; ++t) {
-    const int row = 2 * ((wave & 1) * 8 + t) + (lane >> 5), pc = (lane & 31) ^ (((row >> 2) & 3) << 2);
-    off[t] = (uint32_t)(row * ld + (isa ? m0 : n0)) * 4u + 16u * (uint32_t)pc;
+  for (int t = 0; t < 3; ++t) {
+    const int q = wave * 3 + t;
+    isa[t] = q < 8;
+    if (isa[t]) {
+      const int row = 2 * q + (lane >> 5), pc = (lane & 31) ^ (((row >> 2) & 3) << 2);
+      off[t] = (uint32_t)(row * p.lda + m0) * 4u + 16u * (uint32_t)pc;
+    } else {
+      const int row = 4 * (q - 8) + (lane >> 4), pc = (lane & 15) ^ (((row >> 2) & 3) << 2);
+      off[t] = (uint32_t)(row * p.ldb + n0) * 4u + 16u * (uint32_t)pc;
+    }
   }
-  const uint32_t step = (uint32_t)(kTnBK * ld) * 4u;
+  const uint32_t stepa = (uint32_t)(kTnBK * p.lda) * 4u, stepb = (uint32_t)(kTnBK * p.ldb) * 4u;
   auto issue = [&](int kc) {
-    const uint32_t base = lds0 + (uint32_t)(kc % kTnStages) * kTnStageBytes + (uint32_t)wave * 8u * 1024u;
+    const uint32_t base = lds0 + (uint32_t)(kc % kTnStages) * kTnStageBytes + (uint32_t)wave * 3u * 1024u;
 #pragma unroll
-    for (int t = 0; t < 8; ++t) dma16(isa ? ra : rb, off[t] + (uint32_t)kc * step, base + 1024u * t);
+    for (int t = 0; t < 3; ++t)
+      dma16(isa[t] ? ra : rb, off[t] + (uint32_t)kc * (isa[t] ? stepa : stepb), base + 1024u * t);
   };
-  issue(0);
+#pragma unroll
+  for (int c = 0; c < kTnStages - 1; ++c)
+    if (c < nk) issue(c);
 
   const int wm = wave >> 1, wn = wave & 1;
   const bool suma = p.csA && nt == 0 && wn == 0;  // wave-uniform
   const bool sumb = p.csB && mt == 0 && wm == 0;
-  f32x4 acc[4][4], cs[4];
+  f32x4 acc[4][2], cs[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    cs[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    acc[i][0] = acc[i][1] = cs[i] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
-  bf16x8 ones;
-#pragma unroll
-  for (int v = 0; v < 8; ++v) ones[v] = (__bf16)1.0f;
   // lane byte offsets inside a stage: A element (4g + j, (wm 4 + i) 16 + r16),
-  // B element (4g + j, (wn 4 + i) 16 + r16); row 16 + 4g + j lies 16 rows on,
-  // under the same permutation
-  uint32_t oa[4], ob[4];
+  // B element (4g + j, (wn 2 + jb) 16 + r16)
+  uint32_t oa[4], ob[2];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    oa[i] = (uint32_t)(4 * g * 512 + (((wm * 4 + i) ^ g) & 7) * 64 + r16 * 4);
-    ob[i] = (uint32_t)(kTnBM * kTnBK * 4 + 4 * g * 512 + (((wn * 4 + i) ^ g) & 7) * 64 + r16 * 4);
-  }
-  auto frag = [&](const char* p0) {
-    float x[8];
+  for (int i = 0; i < 4; ++i) oa[i] = (uint32_t)(4 * g * 512 + (((wm * 4 + i) ^ g) & 7) * 64 + r16 * 4);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      x[j] = *reinterpret_cast<const float*>(p0 + j * 512);
-      x[4 + j] = *reinterpret_cast<const float*>(p0 + (16 + j) * 512);
-    }
-    return split3(x);
-  };
+  for (int jb = 0; jb < 2; ++jb) ob[jb] = (uint32_t)(kTnBM * kTnBK * 4 + 4 * g * 256 + (((wn * 2 + jb) ^ g) & 3) * 64 + r16 * 4);
   for (int kc = 0; kc < nk; ++kc) {
-    vm_wait<0>();
+    const int young = min(kTnStages - 2, nk - 1 - kc);
+    if (young >= 2) vm_wait<6>();
+    else if (young == 1) vm_wait<3>();
+    else vm_wait<0>();
     __builtin_amdgcn_s_barrier();
     asm volatile("" : : : "memory");
-    if (kc + 1 < nk) issue(kc + 1);
+    if (kc + kTnStages - 1 < nk) issue(kc + kTnStages - 1);
     const char* buf = lds + (kc % kTnStages) * kTnStageBytes;
-    Split3 a[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) a[i] = frag(buf + oa[i]);
-    if (suma) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        cs[i] = mfma_bf16(a[i].h, ones, mfma_bf16(a[i].m, ones, mfma_bf16(a[i].l, ones, cs[i])));
-    }
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const Split3 b = frag(buf + ob[j]);
-      mfma_split(acc[j], a, b);
-      if (sumb) cs[j] = mfma_bf16(ones, b.h, mfma_bf16(ones, b.m, mfma_bf16(ones, b.l, cs[j])));
+      float a[4], b[2];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) a[i] = *reinterpret_cast<const float*>(buf + oa[i] + j * 512);
+#pragma unroll
+      for (int jb = 0; jb < 2; ++jb) b[jb] = *reinterpret_cast<const float*>(buf + ob[jb] + j * 256);
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int jb = 0; jb < 2; ++jb) acc[i][jb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[jb], acc[i][jb], 0, 0, 0);
+      if (suma) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) cs[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], 1.0f, cs[i], 0, 0, 0);
+      }
+      if (sumb) {
+#pragma unroll
+        for (int jb = 0; jb < 2; ++jb) cs[jb] = __builtin_amdgcn_mfma_f32_16x16x4f32(1.0f, b[jb], cs[jb], 0, 0, 0);
+      }
     }
   }
   // lane (g, r16) holds C[4g + v][r16]: rows m, columns n
@@ -491,12 +551,12 @@ __global__ void __launch_bounds__(256) k_gemm_tn(const TnArgs p) {
 #pragma unroll
   for (int i = 0; i < 4; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int n = n0 + (wn * 4 + j) * 16 + r16;
+    for (int jb = 0; jb < 2; ++jb) {
+      const int n = n0 + (wn * 2 + jb) * 16 + r16;
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int m = m0 + (wm * 4 + i) * 16 + 4 * g + v;
-        if (m < p.M && n < p.N) part[(long)m * p.N + n] = acc[j][i][v];
+        if (m < p.M && n < p.N) part[(long)m * p.N + n] = acc[i][jb][v];
       }
     }
   if (suma && r16 == 0) {  // every column of C holds A's column sums
@@ -510,9 +570,9 @@ __global__ void __launch_bounds__(256) k_gemm_tn(const TnArgs p) {
   }
   if (sumb && g == 0) {  // every row of C holds B's column sums
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int n = n0 + (wn * 4 + j) * 16 + r16;
-      if (n < p.N) p.csB[(long)sl * p.N + n] = cs[j][0];
+    for (int jb = 0; jb < 2; ++jb) {
+      const int n = n0 + (wn * 2 + jb) * 16 + r16;
+      if (n < p.N) p.csB[(long)sl * p.N + n] = cs[jb][0];
     }
   }
 }
@@ -523,6 +583,11 @@ __global__ void __launch_bounds__(256) k_gemm_tn(const TnArgs p) {
 // most kMaxSliceK rows and summed in fp64 (relative error of the product
 // then ~ 1e-5 of the terms' magnitude at T B = 65536).
 constexpr int kMaxSliceK = 2048;
+int split_long(int M, int N, int Kpad) {
+  int S = split_of(M, N, Kpad);
+  while (Kpad / S > kMaxSliceK && (Kpad / 32) % (2 * S) == 0) S *= 2;
+  return S;
+}
 
 // out[m][n] = sum_s part[s][m][n] in slice order, accumulated in fp64
 __global__ void __launch_bounds__(256) k_sum_slices(const float* part, int S, int M, int N, float* out, long ldo) {
@@ -535,42 +600,19 @@ __global__ void __launch_bounds__(256) k_sum_slices(const float* part, int S, in
 }
 
 // out (ldo) = A . B^T, split over K through `part` ([S, M, N]) when that
-// fills the chip better; 64 x 64 tiles where the 128 x 128 ones would leave
-// CUs without one (65536 x 1040 x 512: 446 us on 128 x 128, 604 us on 64 x 64).
-bool nt_large(int M, int N) { return (long)((N + 127) / 128) * ((M + 127) / 128) >= kCUs; }
-int split_nt(int M, int N, int Kpad) {
-  return nt_large(M, N) ? split_of<GradGemm>(M, N, Kpad) : split_of<GradGemmS>(M, N, Kpad);
-}
+// fills the chip better, or (long_k) to bound the fp32 accumulation chains
 hipError_t gemm_nt(const float* A, long lda, int M, const float* Bm, long ldb, int N, int Kpad, float* out,
-                   long ldo, float* part, hipStream_t s) {
-  const int S = part ? split_nt(M, N, Kpad) : 1;
-  auto run = [&](float* o, long ld, long oslice) {
-    return nt_large(M, N) ? gemm_nt_slices<GradGemm>("grad_gemm", A, lda, M, Bm, ldb, N, Kpad, S, o, ld, oslice, s)
-                          : gemm_nt_slices<GradGemmS>("grad_gemm", A, lda, M, Bm, ldb, N, Kpad, S, o, ld, oslice, s);
-  };
-  if (S == 1) return run(out, ldo, 0);
-  const hipError_t e = run(part, N, (long)M * N);
+                   long ldo, float* part, hipStream_t s, bool long_k = false) {
+  const int S = part ? (long_k ? split_long(M, N, Kpad) : split_of(M, N, Kpad)) : 1;
+  if (S == 1) return gemm_nt_slices("grad_gemm", A, lda, M, Bm, ldb, N, Kpad, 1, out, ldo, 0, s);
+  const hipError_t e = gemm_nt_slices("grad_gemm", A, lda, M, Bm, ldb, N, Kpad, S, part, N, (long)M * N, s);
   if (e != hipSuccess) return e;
   return launch("grad_sum", k_sum_slices, dim3((unsigned)(((long)M * N + 255) / 256)), dim3(256), 0, s, part, S, M,
                 N, out, ldo);
 }
 
-// Rows per K slice of a product over K rows: at most kMaxSliceK, and fewer
-// (down to 256, a multiple of the chunk) until its slices and tiles number
-// twice the CUs, two work-groups each.  (A slice of 2048 rows whatever the
-// product left 4500-row products on 84 to 144 of the CUs: 197 us each.)
-int tn_rows(int M, int N, long K) {
-  K = std::max(K, 1L);  // (a size query over no steps)
-  const long tiles = (long)((M + kTnBM - 1) / kTnBM) * ((N + kTnBN - 1) / kTnBN);
-  long S = (K + kMaxSliceK - 1) / kMaxSliceK;
-  while (S * tiles < 2 * kCUs && K / (2 * S) >= 256) S *= 2;
-  const long rows = (K + S - 1) / S;
-  return (int)((rows + kTnBK - 1) / kTnBK * kTnBK);
-}
-inline int tn_slices(int M, int N, long K) {
-  const int ks = tn_rows(M, N, K);
-  return (int)((K + ks - 1) / ks);
-}
+// K slices of a product over K rows (kMaxSliceK rows each)
+inline int tn_slices(long K) { return (int)((K + kMaxSliceK - 1) / kMaxSliceK); }
 
 // out (ldo) = A^T B over the K rows of both (A [K, lda] with M used columns,
 // B [K, ldb] with N), through the slice partials `part` ([S, M, N]) summed in
@@ -581,15 +623,15 @@ hipError_t gemm_tn(const float* A, long lda, int M, const float* Bm, long ldb, i
   if (sum_a && sum_b) return hipErrorInvalidValue;  // one colsum register set per wave
   TnArgs a{};
   a.A = A; a.Bm = Bm; a.lda = lda; a.ldb = ldb; a.K = K;
-  a.Ks = tn_rows(M, N, K);
-  a.S = tn_slices(M, N, K);
+  a.Ks = kMaxSliceK;
+  a.S = tn_slices(K);
   a.M = M; a.N = N;
   a.ntm = (M + kTnBM - 1) / kTnBM;
   a.ntn = (N + kTnBN - 1) / kTnBN;
   a.part = part;
   a.csA = sum_a ? cpart : nullptr;
   a.csB = sum_b ? cpart : nullptr;
-  const long nwg = 8 * (((long)a.S * a.ntm * a.ntn + 7) / 8);
+  const long nwg = (long)((a.S + 7) / 8) * 8 * a.ntm * a.ntn;
   hipError_t e = launch("grad_gemm_tn", k_gemm_tn, dim3((unsigned)nwg), dim3(256), 0, s, a);
   if (e != hipSuccess) return e;
   e = launch("grad_sum", k_sum_slices, dim3((unsigned)(((long)M * N + 255) / 256)), dim3(256), 0, s,
@@ -624,30 +666,29 @@ size_t grad_workspace(const Layout& L, int B, int T, char* ws, GradWs* G) {
   auto take = [&](size_t bytes) { const size_t at = o; o = wm_align256(o + bytes); return at; };
   const size_t oG = take((size_t)TB * H4 * 4), oC = take((size_t)(T + 1) * B * H * 4);
   const size_t oM = take((size_t)TB * NmP * 4), odG = take((size_t)TB * H4 * 4);
-  const size_t odhh = take((size_t)TB * H * 4), odc = take((size_t)B * H * 4);
+  const size_t odhh = take((size_t)TB * H * 4), odh = take((size_t)B * H * 4), odc = take((size_t)B * H * 4);
   const size_t odWgT = take((size_t)L.ldk * H4 * 4), odWa = take((size_t)L.A * H4 * 4);
   const size_t odWm = take((size_t)NmP * H * 4), odbg = take((size_t)H4 * 4), odbm = take((size_t)NmP * 4);
-  const int Sg = tn_slices(L.ldk, H4, TB), Sm = tn_slices(NmP, H, TB);  // K slices of dW_g, dW_m
-  const size_t opart = take((size_t)std::max({kFlatBlocks, Sg, Sm}) * std::max(H4, NmP) * 4);
+  const size_t opart = take((size_t)std::max(kFlatBlocks, tn_slices(TB)) * std::max(H4, NmP) * 4);
   const size_t oapart = take((size_t)act_chunks(L) * L.A * H4 * 4);
-  // split-K partials: the largest of the products that split
-  auto split_need = [](int M, int N, int Kpad) {
-    const int S = split_nt(M, N, Kpad);
+  // split-K partials: the largest of the products that split, and the
+  // per-step slices of dG_t . W_h (always)
+  auto split_need = [](int M, int N, int Kpad, bool long_k = false) {
+    const int S = long_k ? split_long(M, N, Kpad) : split_of(M, N, Kpad);
     return S > 1 ? (size_t)S * M * N : (size_t)0;
   };
-  const size_t nsplit = std::max({split_need((int)TB, L.Nm, L.ldh),
-                                  split_need((int)TB, H, NmP), (size_t)Sg * L.ldk * H4, (size_t)Sm * NmP * H});
+  const size_t nsplit = std::max({(size_t)bptt_split(B, H) * B * H, split_need((int)TB, H4, L.ldk),
+                                  split_need((int)TB, L.Nm, L.ldh), split_need((int)TB, H, NmP),
+                                  (size_t)tn_slices(TB) * L.ldk * H4, (size_t)tn_slices(TB) * NmP * H});
   const size_t osplit = take(nsplit * 4);
   const size_t on = take(16);
   const size_t ofwd = take((size_t)TB * (L.Z + 1) * 4);  // loss terms [TB, Z+1]
-  const size_t opl = take(recur_bwd_bytes(L, B));        // operand planes of the reverse-time chain
   if (ws && G) {
     auto f = [&](size_t at) { return reinterpret_cast<float*>(ws + at); };
-    G->G = f(oG); G->Cs = f(oC); G->M = f(oM); G->dG = f(odG); G->dhh = f(odhh);
+    G->G = f(oG); G->Cs = f(oC); G->M = f(oM); G->dG = f(odG); G->dhh = f(odhh); G->dh = f(odh);
     G->dc = f(odc);
     G->dWgT = f(odWgT); G->dWa = f(odWa); G->dWm = f(odWm); G->dbg = f(odbg); G->dbm = f(odbm);
     G->part = f(opart); G->apart = f(oapart); G->split = f(osplit); G->nsum = f(on); G->fwd = f(ofwd);
-    G->planes = ws + opl;
   }
   return o;
 }
@@ -658,21 +699,35 @@ hipError_t launch_nll_grad(const Packed& P, NllBufs N, const GradWs& G, const Gr
   const long TB = (long)T * B;
   const int NmP = (L.Nm + 31) / 32 * 32;
   const char* base = reinterpret_cast<const char*>(P.base);
+  const float* Wg = reinterpret_cast<const float*>(base + L.off_Wg);
+  const float* WaT = reinterpret_cast<const float*>(base + L.off_WaT);
+  const float* bg = reinterpret_cast<const float*>(base + L.off_bg);
   const float* Wm = reinterpret_cast<const float*>(base + L.off_Wm);
   const float* bm = reinterpret_cast<const float*>(base + L.off_bm);
+  const float* WhT = reinterpret_cast<const float*>(base + L.off_WhT);  // [H, 4H]
   const float* WmT = reinterpret_cast<const float*>(base + L.off_WmT);  // [H, NmP]
   const float* X = reinterpret_cast<const float*>(N.x);
   const float* Hn = X + (long)B * L.ldx + Z;  // h_1 .. h_T: rows of X_1 .. X_T from column Z
   hipError_t e;
 #define WM_TRY(x) do { e = (x); if (e != hipSuccess) return e; } while (0)
-  // forward recurrence: X (z_t | h_t) for every step, with the gate
-  // activations and c_{t+1} of every step
-  N.g_trace = G.G;
-  N.c_trace = G.Cs;
+  // forward recurrence: X (z_t | h_t) for every step. Where the persistent
+  // kernel serves it, it also leaves the gate activations and c_{t+1} of
+  // every step; otherwise they are recomputed from X (pre-activations of
+  // every step in one GEMM, then a scan that applies the gates and records
+  // c_t).
+  const bool traced = persist_usable(L, B, true);
+  N.g_trace = traced ? G.G : nullptr;
+  N.c_trace = traced ? G.Cs : nullptr;
   WM_TRY(launch_nll_recurrence(P, N, s));
   WM_TRY(launch("grad_len", k_len_sum, dim3(1), dim3(256), 0, s, N.lengths, B, T, G.nsum));
-  WM_TRY(launch("grad_zero", k_zero, dim3((unsigned)(((long)B * H + 255) / 256)), dim3(256), 0, s, G.Cs,
-                (long)B * H));  // c_0
+  if (traced) {
+    WM_TRY(launch("grad_zero", k_zero, dim3((unsigned)(((long)B * H + 255) / 256)), dim3(256), 0, s, G.Cs,
+                  (long)B * H));  // c_0
+  } else {
+    WM_TRY(gemm_nt(X, L.ldx, (int)TB, Wg, L.ldk, H4, L.ldk, G.G, H4, G.split, s));
+    WM_TRY(launch("grad_scan", k_grad_fwd_scan, dim3((unsigned)(((long)B * H + 255) / 256)), dim3(256), 0, s,
+                  G.G, bg, WaT, N.actions, G.Cs, B, T, H, A));
+  }
   // head outputs of every h_{t+1}, then d loss / d output in place
   WM_TRY(gemm_nt(Hn, L.ldx, (int)TB, Wm, L.ldh, L.Nm, L.ldh, G.M, NmP, G.split, s));
   switch (L.K) {
@@ -695,7 +750,15 @@ hipError_t launch_nll_grad(const Packed& P, NllBufs N, const GradWs& G, const Gr
   // W_m^T [H, NmP], zero columns past Nm)
   WM_TRY(gemm_nt(G.M, NmP, (int)TB, WmT, NmP, H, NmP, G.dhh, H, G.split, s));
   // back through time (the packed W_h^T [H, 4H])
-  WM_TRY(launch_recur_bwd(P, B, T, G.G, G.Cs, G.dhh, G.dc, G.dG, G.planes, s));
+  const unsigned eg = (unsigned)(((long)B * H + 255) / 256);
+  const int Sb = bptt_split(B, H);  // K slices of dG_t . W_h, summed by the next step's kernel
+  for (int t = T - 1; t >= 0; --t) {
+    WM_TRY(launch("grad_lstm", k_grad_lstm_back, dim3(eg), dim3(256), 0, s, G.G, G.Cs, G.dhh, G.split, Sb, G.dc,
+                  G.dG, B, H, t, t == T - 1 ? 1 : 0));
+    if (t > 0)
+      WM_TRY(gemm_nt_slices<BpttGemm>("grad_gemm_bptt", G.dG + (long)t * B * H4, H4, B, WhT, H4, H, H4, Sb, G.split, H,
+                            (long)B * H, s));
+  }
   // dW_g^T [ldk, 4H] = X^T . dG over all rows, read as stored; the bias
   // gradient (dG's column sums) from the same pass
   WM_TRY(gemm_tn(X, L.ldx, L.ldk, G.dG, H4, H4, TB, G.split, G.dWgT, H4, false, true, G.part, G.dbg, s));

@@ -112,14 +112,10 @@ bool persist_usable(const Layout& L, int B, bool nll);
 hipError_t launch_rollout_persist(const Packed& P, const RolloutBufs& R, hipStream_t s);
 hipError_t launch_nll_persist(const Packed& P, const NllBufs& N, hipStream_t s);
 
-// The fp32 recurrence and its reverse-time chain, one launch per step
-// (wm_recur.hip): the bytes of their operand planes, and the launches.
-// G, Cs, dhh, dc, dG as in GradWs.
+// The fp32 recurrence of the likelihood pass, one launch per step
+// (wm_recur.hip): the bytes of its operand planes, and the launches.
 size_t recur_fwd_bytes(const Layout& L, int B, int T);
 hipError_t launch_recur_fwd(const Packed& P, const NllBufs& N, hipStream_t s);
-size_t recur_bwd_bytes(const Layout& L, int B);
-hipError_t launch_recur_bwd(const Packed& P, int B, int T, const float* G, const float* Cs, const float* dhh,
-                            float* dc, float* dG, void* planes, hipStream_t s);
 
 // The static device scratch of wm_rollout_noalloc (wm_noalloc.hip): its
 // device address on the current device, looked up once per device.
@@ -140,9 +136,8 @@ hipError_t launch_returns(const ReturnsBufs& R, hipStream_t s);
 
 // World-model training step: gradient of the summed NLL means (fp32).
 struct GradWs {  // workspace after the NLL pass's own
-  float *G, *Cs, *M, *dG, *dhh, *dc;
+  float *G, *Cs, *M, *dG, *dhh, *dh, *dc;
   float *dWgT, *dWa, *dWm, *dbg, *dbm, *part, *apart, *split, *nsum, *fwd;
-  void* planes;
 };
 struct GradOut {  // canonical gradients; loss (nullable): the summed means
   float *loss, *W_g, *b_g, *W_m, *b_m, *w_r, *b_r, *w_d, *b_d;

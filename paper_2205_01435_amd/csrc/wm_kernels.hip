@@ -947,9 +947,12 @@ hipError_t nll_impl(const Packed& P, const NllBufs& N, hipStream_t s, bool heads
   ga.nll_mode = 1;
   ga.c = N.c;
   // the recurrence: one persistent launch for small batches, else one launch
-  // per step, in fp32 on split products (recur_serves)
+  // per step, in fp32 on split products (recur_serves).  The training
+  // gradient's (heads = false) keeps to the fp32 products: Adam's first step
+  // divides by |g| + 1e-8, and where a gradient is that small another rounding
+  // of the sums moves the parameter by up to the whole step.
   e = hipErrorNotSupported;
-  if (sizeof(DT) == 2 || !recur_serves(L, B, T)) e = launch_nll_persist(P, N, s);
+  if (sizeof(DT) == 2 || !heads || !recur_serves(L, B, T)) e = launch_nll_persist(P, N, s);
   else e = launch_recur_fwd(P, N, s);
   if (e != hipSuccess && e != hipErrorNotSupported) return e;
   for (int t = 0; e == hipErrorNotSupported && t < T; ++t) {

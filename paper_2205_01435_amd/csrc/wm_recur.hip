@@ -1,9 +1,8 @@
-// The LSTM recurrence of the fp32 likelihood pass and its reverse-time chain,
-// one launch per step, on the bf16 matrix unit from three-term splits
-// (split3).  Both are a product of the step's activations with weights that
-// stay the same for the whole call, and both are bound by the bytes a CU pulls
-// from the L2: every operand is therefore split once, where it is written, and
-// stored as "planes": for 16 rows and 32 columns K, the three bf16 terms as
+// The LSTM recurrence of the fp32 likelihood pass, one launch per step, on the
+// bf16 matrix unit from three-term splits (split3).  A step is a product of its
+// activations with weights that stay the same for the whole call, bound by the
+// bytes a CU pulls from the L2: every operand is therefore split once, where it
+// is written, and stored as "planes": for 16 rows and 32 columns K, the three bf16 terms as
 // three 1 KB pieces, each laid out as one MFMA fragment (lane 16 g + r holds
 // columns 8 g .. 8 g + 7 of row r in 16 bytes), so that a wave's load of a
 // fragment is one contiguous 1 KB and needs neither LDS nor conversion.
@@ -12,8 +11,7 @@
 // A work-group of four waves owns one output tile; the waves take interleaved
 // K slices, loads running ahead of the products in registers, and their
 // partial tiles meet in LDS in a fixed order.  The epilogue applies the LSTM
-// cell (or its backward) and writes the next step's planes beside the fp32
-// results.
+// cell and writes the next step's planes beside the fp32 results.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -173,8 +171,6 @@ struct FwdArgs {
   const int32_t* act;        // [B]
   float* c;                  // [B, H], in place
   float* x_out;              // X_{t+1}: fp32 h at columns Z .. of rows of ldx
-  float* g_trace;            // [B, 4H] gate activations, or null
-  float* c_trace;            // [B, H] c_{t+1}, or null
   int B, H, A, Z, nz, nh;
   long ldx;
   TileMap map;
@@ -242,100 +238,14 @@ __global__ void __launch_bounds__(256, 1) k_recur_fwd(const FwdArgs p) {
     const float gg = ftanh(s[2][t] + (bias[t].z + wa[t].z)), go = fsigmoid(s[3][t] + (bias[t].w + wa[t].w));
     cv[t] = gf * cin[t] + gi * gg;
     hv[t] = go * ftanh(cv[t]);
-    if (p.g_trace)
-      reinterpret_cast<float4*>(p.g_trace + (long)m * 4 * H)[u0 + t] = make_float4(gi, gf, gg, go);
   }
-  const float4 cn = make_float4(cv[0], cv[1], cv[2], cv[3]);
-  *reinterpret_cast<float4*>(p.c + (long)m * H + u0) = cn;
-  if (p.c_trace) *reinterpret_cast<float4*>(p.c_trace + (long)m * H + u0) = cn;
+  *reinterpret_cast<float4*>(p.c + (long)m * H + u0) = make_float4(cv[0], cv[1], cv[2], cv[3]);
   *reinterpret_cast<float4*>(p.x_out + (long)m * p.ldx + p.Z + u0) = make_float4(hv[0], hv[1], hv[2], hv[3]);
   const float x8[8] = {hv[0], hv[1], hv[2], hv[3], 0.f, 0.f, 0.f, 0.f};
   const Terms t8 = terms8(x8);
   char* at = p.hp_out + ((long)(m >> 4) * p.nh + (u0 >> 5)) * kFrag + (((u0 & 31) >> 3) * 16 + r16) * 16 + (u0 & 7) * 2;
 #pragma unroll
   for (int q = 0; q < 3; ++q) *reinterpret_cast<uint2*>(at + q * kPiece) = make_uint2(t8.p[q].x, t8.p[q].y);
-}
-
-// ---------------------------------------------------------------------------
-// reverse step t: dh = dh_heads + dG_{t+1} . W_h for 32 units x 32 rows, the
-// LSTM backward of those, dG_t and its planes
-// ---------------------------------------------------------------------------
-struct BwdArgs {
-  const char *Wp, *gp;  // planes: W_h^T [H rows, 4H], dG_{t+1} [B, 4H]
-  char* gp_out;         // dG_t
-  const float* G;       // [B, 4H] activations of step t
-  const float *c0, *c1; // [B, H] c_t, c_{t+1}
-  const float* dhh;     // [B, H]
-  float* dc;            // [B, H], in place
-  float* dG;            // [B, 4H]
-  int B, H, last;
-  TileMap map;
-};
-
-__global__ void __launch_bounds__(256, 1) k_recur_bwd(const BwdArgs p) {
-  __shared__ __attribute__((aligned(16))) f32x4 red[4][4][64];
-  int nt, mt;
-  if (!tile_of(p.map, nt, mt)) return;
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int g = lane >> 4, r16 = lane & 15;
-  const uint32_t lo = (uint32_t)lane * 16u;
-  const int H = p.H, nks = H / 8, rbs = (p.B + 15) >> 4;
-  // wave = 2 i + j takes block (i, j) of the tile in the epilogue
-  const int u0 = 32 * nt + 16 * (wave >> 1) + 4 * g, m = 32 * mt + 16 * (wave & 1) + r16;
-  const bool ok = u0 < H && m < p.B;
-  const long e = ok ? (long)m * H + u0 : 0;
-  float4 act[4], c0, c1, dh, dc;
-#pragma unroll
-  for (int t = 0; t < 4; ++t) act[t] = reinterpret_cast<const float4*>(p.G)[e + t];
-  c0 = *reinterpret_cast<const float4*>(p.c0 + e);
-  c1 = *reinterpret_cast<const float4*>(p.c1 + e);
-  dh = *reinterpret_cast<const float4*>(p.dhh + e);
-  dc = p.last ? make_float4(0.f, 0.f, 0.f, 0.f) : *reinterpret_cast<const float4*>(p.dc + e);
-  f32x4 s = f32x4{0.f, 0.f, 0.f, 0.f};
-  if (!p.last) {
-    f32x4 acc[2][2];
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int i = 0; i < 2; ++i) acc[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const PlaneSrc W(p.Wp, nks, 2 * nt, H / 16), x(p.gp, nks, 2 * mt, rbs);
-    auto load = [&](Stage<2, 2>& st, int sl) { st.load(W, sl, x, sl, sl < nks ? lo : kOffNone); };
-    PlaneProduct<2, 2, 2> pp;
-    pp.start(wave, load);
-    pp.run(acc, nks, wave, load);
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) red[wave][2 * i + j][lane] = acc[j][i];
-    __syncthreads();
-    s = (red[0][wave][lane] + red[1][wave][lane]) + (red[2][wave][lane] + red[3][wave][lane]);
-  }
-  if (!ok) return;
-  const float c0v[4] = {c0.x, c0.y, c0.z, c0.w}, c1v[4] = {c1.x, c1.y, c1.z, c1.w};
-  const float dhv[4] = {dh.x, dh.y, dh.z, dh.w}, dcv[4] = {dc.x, dc.y, dc.z, dc.w};
-  float dcn[4], d[16];
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    const float4 a = act[t];  // i, f, g, o
-    const float th = tanhf(c1v[t]), dht = dhv[t] + s[t];
-    const float dcc = dcv[t] + dht * a.w * (1.0f - th * th);
-    dcn[t] = dcc * a.y;
-    d[4 * t] = dcc * a.z * a.x * (1.0f - a.x);
-    d[4 * t + 1] = dcc * c0v[t] * a.y * (1.0f - a.y);
-    d[4 * t + 2] = dcc * a.x * (1.0f - a.z * a.z);
-    d[4 * t + 3] = dht * th * a.w * (1.0f - a.w);
-    reinterpret_cast<float4*>(p.dG)[e + t] = make_float4(d[4 * t], d[4 * t + 1], d[4 * t + 2], d[4 * t + 3]);
-  }
-  *reinterpret_cast<float4*>(p.dc + e) = make_float4(dcn[0], dcn[1], dcn[2], dcn[3]);
-  // columns 4 u0 .. 4 u0 + 15 of the row: two lane entries of slice u0 / 8
-  char* at = p.gp_out + ((long)(m >> 4) * nks + (u0 >> 3)) * kFrag + (((u0 & 7) >> 1) * 16 + r16) * 16;
-#pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    float x8[8];
-#pragma unroll
-    for (int v = 0; v < 8; ++v) x8[v] = d[8 * q + v];
-    store_terms(at + q * 256, terms8(x8));
-  }
 }
 
 template <int MB>
@@ -380,55 +290,17 @@ hipError_t launch_recur_fwd(const Packed& P, const NllBufs& N, hipStream_t s) {
   a.c = N.c;
   a.B = B; a.H = H; a.A = L.A; a.Z = Z; a.nz = nz; a.nh = nh;
   a.ldx = L.ldx;
-  const long BX = (long)B * L.ldx, BH = (long)B * H;
+  const long BX = (long)B * L.ldx;
   for (int t = 0; t < T; ++t) {
     a.zp = zp + t * zb;
     a.hp = hp + (t & 1) * hb;
     a.hp_out = hp + ((t + 1) & 1) * hb;
     a.act = N.actions + (long)t * B;
     a.x_out = reinterpret_cast<float*>(N.x) + (long)(t + 1) * BX;
-    a.g_trace = N.g_trace ? N.g_trace + (long)t * BH * 4 : nullptr;
-    a.c_trace = N.c_trace ? N.c_trace + (long)(t + 1) * BH : nullptr;
     // 32-row tiles once they number the CUs, 16-row ones below (launches at
     // B 512, H 512: 16, 32 and 64 rows 14.9, 11.8 and 12.1 us; B 100, H 256:
     // 5.1, 5.9 and 8.1; of these 2.4 are the launch itself)
     e = (long)(H / 16) * ((B + 31) / 32) >= kCUs ? launch_fwd<2>(a, s) : launch_fwd<1>(a, s);
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
-}
-
-size_t recur_bwd_bytes(const Layout& L, int B) {
-  return wm_align256((size_t)(L.H / 16) * (L.H / 8) * kFrag) + wm_align256((size_t)2 * blocks(B) * (L.H / 8) * kFrag);
-}
-
-hipError_t launch_recur_bwd(const Packed& P, int B, int T, const float* G, const float* Cs, const float* dhh,
-                            float* dc, float* dG, void* planes, hipStream_t s) {
-  const Layout& L = P.L;
-  const int H = L.H, nks = H / 8, rbs = blocks(B);
-  char* Wp = reinterpret_cast<char*>(planes);
-  char* gp = Wp + wm_align256((size_t)(H / 16) * nks * kFrag);
-  const long gb = (long)rbs * nks * kFrag;
-  const float* WhT = reinterpret_cast<const float*>(reinterpret_cast<const char*>(P.base) + L.off_WhT);
-  hipError_t e = launch("grad_planes", k_planes_rows, dim3((unsigned)(((long)(H / 16) * nks * 64 + 255) / 256), 1),
-                        dim3(256), 0, s, WhT, (long)4 * H, H, 4 * H, H / 16, nks, 0L, 0L, Wp);
-  if (e != hipSuccess) return e;
-  BwdArgs a{};
-  a.Wp = Wp;
-  a.dc = dc;
-  a.B = B; a.H = H;
-  a.map = tile_map((H + 31) / 32, (B + 31) / 32, (size_t)(H / 16) * nks * kFrag);
-  const long BH = (long)B * H;
-  for (int t = T - 1; t >= 0; --t) {
-    a.gp = gp + ((t + 1) & 1) * gb;
-    a.gp_out = gp + (t & 1) * gb;
-    a.G = G + (long)t * BH * 4;
-    a.c0 = Cs + (long)t * BH;
-    a.c1 = Cs + (long)(t + 1) * BH;
-    a.dhh = dhh + (long)t * BH;
-    a.dG = dG + (long)t * BH * 4;
-    a.last = t == T - 1;
-    e = launch("grad_step", k_recur_bwd, dim3(grid_of(a.map)), dim3(256), 0, s, a);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;

@@ -46,7 +46,7 @@ def kernel_sources(kernel: str) -> list[str]:
     wm_persist.hip, the mixture, controller and gradient kernels of the
     per-step path in files of their own, the others in wm_kernels.hip."""
     for part, name in (("persist", "wm_persist.hip"), ("k_mdn", "wm_mdn.hip"), ("k_ctrl", "wm_ctrl.hip"),
-                       ("k_grad", "wm_grad.hip"), ("k_gemm", "wm_grad.hip")):
+                       ("k_recur", "wm_recur.hip"), ("k_grad", "wm_grad.hip"), ("k_gemm", "wm_grad.hip")):
         if part in kernel:
             return [name, *HEADERS]
     return ["wm_kernels.hip", *HEADERS]

@@ -1,7 +1,7 @@
-"""GPU parity of the products that run on the bf16 matrix unit from three-term
-splits, where their tiles and K slices have remainders: the training gradient
-over rows that do not fill the last slice or chunk, and the likelihood pass on
-128-row mixture tiles."""
+"""GPU parity where tiles and K slices have remainders: the likelihood pass's
+recurrence and 128-row mixture tiles, which run on the bf16 matrix unit from
+three-term splits, and the training gradient over rows that do not fill the
+last slice, chunk or list of rows."""
 
 import numpy as np
 import pytest
@@ -57,8 +57,8 @@ def test_nll_large_tiles(K):
     (512, 9, 64, 512, 64),  # a batch that the persistent kernel also serves
 ])
 def test_recurrence_per_step(B, T, Z, H, A):
-    """The recurrence of one launch per step, forward (with actions outside
-    [0, A): no column) and, through the gradient, in reverse."""
+    """The recurrence of one launch per step (with actions outside [0, A): no
+    column), and the gradient of the same call."""
     w = wl.Workload("r", "nll", B=B, T=T, Z=Z, H=H, A=A, K=2, dtype="fp32", seed=60 + B)
     d = wl.make_nll_inputs(w)
     a = d["actions"].copy()
