@@ -28,7 +28,8 @@ static constexpr float kHalfLn2Pi = 0.91893853320467274178f;
 //   heads     mixture/reward/done outputs of every h_{t+1} in one GEMM; an
 //             element-wise kernel turns them into d loss / d output (dM)
 //   back      dh_heads = dM W_m; per step (backwards) the LSTM backward gives
-//             dG_t and dc_t, and dh_t = dG_t W_h for the step before
+//             dG_t and dc_t, and dh_t = dG_t W_h for the step before (small
+//             batches: both in one launch, k_grad_step)
 //   weights   dW_g^T = X^T dG and dW_m = dM^T H over all T B rows, with the
 //             bias gradients summed in the same pass (k_gemm_tn reads X, dG,
 //             dM and H as stored, K outer), the one-hot columns by a
@@ -230,6 +231,96 @@ __global__ void __launch_bounds__(256) k_grad_lstm_back(const float* G, const fl
   reinterpret_cast<float4*>(dG + r * 4 * H)[u] =
       make_float4(d_i * a.x * (1.0f - a.x), d_f * a.y * (1.0f - a.y), d_g * (1.0f - a.z * a.z),
                   d_o * a.w * (1.0f - a.w));
+}
+
+// The same with the product that feeds it, in one launch per step:
+//   dh = dhh_t + sum over eight slices of (dG_{t+1} . W_h over H / 2 columns)
+// for 16 units x 16 rows per work-group, a wave per slice.  Operands come from
+// the L2 straight into registers, kStepD K slices of 16 ahead of the products;
+// the slices meet in LDS and are summed in order, so that the results are to
+// the bit those of the product in eight launched slices and k_grad_lstm_back.
+// Both are chains of latencies while the tiles fit the CUs: at B 100, H 256
+// the launch takes 7.0 us and a step 4.1 us less than with two launches.
+constexpr int kStepS = 8, kStepD = 4;
+struct StepArgs {
+  const float* Wh;      // W_h^T [H, 4H]
+  const float* dGn;     // [B, 4H] of step t + 1, or null: t is the last
+  const float* G;       // [B, 4H] activations of step t
+  const float *c0, *c1; // [B, H] c_t, c_{t+1}
+  const float* dhh;     // [B, H]
+  float* dc;            // [B, H], in place
+  float* dG;            // [B, 4H]
+  int B, H;
+  TileMap map;
+};
+__global__ void __launch_bounds__(64 * kStepS) k_grad_step(const StepArgs p) {
+  __shared__ __attribute__((aligned(16))) f32x4 red[kStepS][64];
+  int nt, mt;
+  if (!tile_of(p.map, nt, mt)) return;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int g = lane >> 4, r16 = lane & 15;
+  const int H = p.H, H4 = 4 * H, n0 = 16 * nt, m0 = 16 * mt;
+  // wave 0 takes the epilogue: units u0 .. u0 + 3 of row m per lane, their
+  // inputs loaded ahead of the product
+  const int u0 = n0 + 4 * g, m = m0 + r16;
+  const bool ok = wave == 0 && m < p.B;
+  const long e = ok ? (long)m * H + u0 : 0;
+  float4 act[4];
+#pragma unroll
+  for (int t = 0; t < 4; ++t) act[t] = reinterpret_cast<const float4*>(p.G)[e + t];  // i, f, g, o
+  const float4 c0 = *reinterpret_cast<const float4*>(p.c0 + e), c1 = *reinterpret_cast<const float4*>(p.c1 + e);
+  const float4 dh = *reinterpret_cast<const float4*>(p.dhh + e);
+  const float4 dc = p.dGn ? *reinterpret_cast<const float4*>(p.dc + e) : make_float4(0.f, 0.f, 0.f, 0.f);
+  f32x4 sum = f32x4{0.f, 0.f, 0.f, 0.f};
+  if (p.dGn) {
+    const SrcX<float> w(p.Wh, H4, H4, n0, 16, H), x(p.dGn, H4, H4, m0, 16, p.B);
+    const int Ks = H4 / kStepS, k0 = wave * Ks + 4 * g, k1 = (wave + 1) * Ks, n = Ks / 16;
+    const uint32_t wr = w.row(r16), xr = x.row(r16);
+    uint4 a[kStepD], b[kStepD];
+    f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto load = [&](int d, int s) {  // zeros past the slice
+      a[d] = w.load(wr, k0 + 16 * s, k1);
+      b[d] = x.load(xr, k0 + 16 * s, k1);
+    };
+#pragma unroll
+    for (int d = 0; d < kStepD; ++d) load(d, d);
+    __builtin_amdgcn_sched_barrier(0);
+    for (int s = kStepD; s < n; s += kStepD) {
+#pragma unroll
+      for (int d = 0; d < kStepD; ++d) {
+        Mfma<float>::step(acc, a[d], b[d]);
+        load(d, s + d);
+        // keeps each stage's products ahead of the next one's loads
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+#pragma unroll
+    for (int d = 0; d < kStepD; ++d) Mfma<float>::step(acc, a[d], b[d]);
+    red[wave][lane] = acc;
+    __syncthreads();
+    if (wave == 0) {
+#pragma unroll
+      for (int k = 0; k < kStepS; ++k) sum += red[k][lane];
+    }
+  }
+  if (!ok) return;
+  const float c0v[4] = {c0.x, c0.y, c0.z, c0.w}, c1v[4] = {c1.x, c1.y, c1.z, c1.w};
+  const float dhv[4] = {dh.x, dh.y, dh.z, dh.w}, dcv[4] = {dc.x, dc.y, dc.z, dc.w};
+  float dcn[4];
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const float4 q = act[t];
+    const float dht = p.dGn ? dhv[t] + sum[t] : dhv[t];
+    const float th = tanhf(c1v[t]);
+    const float d_o = dht * th;
+    const float dcc = dcv[t] + dht * q.w * (1.0f - th * th);
+    const float d_i = dcc * q.z, d_f = dcc * c0v[t], d_g = dcc * q.x;
+    dcn[t] = dcc * q.y;
+    reinterpret_cast<float4*>(p.dG)[e + t] =
+        make_float4(d_i * q.x * (1.0f - q.x), d_f * q.y * (1.0f - q.y), d_g * (1.0f - q.z * q.z),
+                    d_o * q.w * (1.0f - q.w));
+  }
+  *reinterpret_cast<float4*>(p.dc + e) = make_float4(dcn[0], dcn[1], dcn[2], dcn[3]);
 }
 
 // add(part[k n]) for k = 0 .. S - 1 in order, eight loads in flight (the sums
@@ -751,8 +842,32 @@ hipError_t launch_nll_grad(const Packed& P, NllBufs N, const GradWs& G, const Gr
   WM_TRY(gemm_nt(G.M, NmP, (int)TB, WmT, NmP, H, NmP, G.dhh, H, G.split, s));
   // back through time (the packed W_h^T [H, 4H])
   const unsigned eg = (unsigned)(((long)B * H + 255) / 256);
-  const int Sb = bptt_split(B, H);  // K slices of dG_t . W_h, summed by the next step's kernel
+  const int Sb = bptt_split(B, H);  // K slices of dG_t . W_h
+  const long BH = (long)B * H;
+  // One launch per step while its 16 x 16 tiles fit the CUs, else the product
+  // on 64 x 64 tiles and the cell apart.  Whole training steps, T 40, two
+  // launches and one, us: B 100, 200, 256 at H 256 1139, 1218, 1284 and 977,
+  // 1053, 1091; B 40, 100 at H 512 1582, 1647 and 1500, 1516; B 60 at H 1024
+  // 3877 and 3802; beyond, B 200 at H 512 (416 tiles) 1883 and 2021.  (Tiles of
+  // 32 x 32 were slower throughout: 26.9 us a step at B = H = 512, where the
+  // two launches take 22.)
+  const bool fused = Sb == kStepS && (long)(H / 16) * ((B + 15) / 16) <= kCUs;
   for (int t = T - 1; t >= 0; --t) {
+    if (fused) {
+      StepArgs a{};
+      a.Wh = WhT;
+      a.dGn = t == T - 1 ? nullptr : G.dG + (long)(t + 1) * BH * 4;
+      a.G = G.G + (long)t * BH * 4;
+      a.c0 = G.Cs + (long)t * BH;
+      a.c1 = G.Cs + (long)(t + 1) * BH;
+      a.dhh = G.dhh + (long)t * BH;
+      a.dc = G.dc;
+      a.dG = G.dG + (long)t * BH * 4;
+      a.B = B; a.H = H;
+      a.map = tile_map(H / 16, (B + 15) / 16, (size_t)H * H4 * 4);
+      WM_TRY(launch("grad_step", k_grad_step, dim3(grid_of(a.map)), dim3(64 * kStepS), 0, s, a));
+      continue;
+    }
     WM_TRY(launch("grad_lstm", k_grad_lstm_back, dim3(eg), dim3(256), 0, s, G.G, G.Cs, G.dhh, G.split, Sb, G.dc,
                   G.dG, B, H, t, t == T - 1 ? 1 : 0));
     if (t > 0)

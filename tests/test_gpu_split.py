@@ -27,6 +27,8 @@ def gpu():
     (31, 97, 23, 24, 272, 70, 8),   # 2231 rows: several slices, the last short of a chunk
     (32, 33, 31, 40, 144, 9, 5),    # 1023 rows; 192 and 592 product columns
     (33, 5, 3, 8, 16, 3, 1),        # fewer rows than one chunk
+    (35, 50, 5, 24, 256, 6, 2),     # reverse steps in one launch; a short row block
+    (36, 9, 3, 8, 320, 4, 1),       # ... with slices that end inside a stage of loads
     (34, 700, 25, 8, 16, 1, 1),     # one action: every row of a block in its list, a second block in each chunk
 ])
 def test_grad_slices(seed, B, T, Z, H, A, K):
