@@ -535,7 +535,7 @@ __global__ void __launch_bounds__(256) k_zero(float* x, long n) {
 // the x-th eighth of all tiles, slice by slice, each slice's m fastest, so
 // that a slice's rows are shared in one L2, or a few when slices are fewer
 // than XCDs (whole slices per XCD before: 4500 rows left five XCDs idle, and
-// the two products took 390 us, 320 with this).
+// the two products took 390 us, 320 with this alone).
 // ===========================================================================
 constexpr int kTnBM = 128, kTnBN = 64, kTnBK = 16, kTnStages = 4;
 constexpr int kTnStageBytes = (kTnBM + kTnBN) * kTnBK * 4;  // 12 KB: A rows, then B rows
@@ -617,25 +617,36 @@ __global__ void __launch_bounds__(256) k_gemm_tn(const TnArgs p) {
     asm volatile("" : : : "memory");
     if (kc + kTnStages - 1 < nk) issue(kc + kTnStages - 1);
     const char* buf = lds + (kc % kTnStages) * kTnStageBytes;
+    // all fragments of the chunk first, the column sums last: with their
+    // branches between the rows each row's reads were waited for on their own
+    // (65536 rows, H 512: both products 2463 us, 2142 so; 4500 rows, H 256:
+    // 320 and 223)
+    float fa[4][4], fb[4][2];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      float a[4], b[2];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = *reinterpret_cast<const float*>(buf + oa[i] + j * 512);
+      for (int i = 0; i < 4; ++i) fa[j][i] = *reinterpret_cast<const float*>(buf + oa[i] + j * 512);
 #pragma unroll
-      for (int jb = 0; jb < 2; ++jb) b[jb] = *reinterpret_cast<const float*>(buf + ob[jb] + j * 256);
+      for (int jb = 0; jb < 2; ++jb) fb[j][jb] = *reinterpret_cast<const float*>(buf + ob[jb] + j * 256);
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
 #pragma unroll
       for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int jb = 0; jb < 2; ++jb) acc[i][jb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[jb], acc[i][jb], 0, 0, 0);
-      if (suma) {
+        for (int jb = 0; jb < 2; ++jb)
+          acc[i][jb] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[j][i], fb[j][jb], acc[i][jb], 0, 0, 0);
+    if (suma) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) cs[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], 1.0f, cs[i], 0, 0, 0);
-      }
-      if (sumb) {
+      for (int j = 0; j < 4; ++j)
 #pragma unroll
-        for (int jb = 0; jb < 2; ++jb) cs[jb] = __builtin_amdgcn_mfma_f32_16x16x4f32(1.0f, b[jb], cs[jb], 0, 0, 0);
-      }
+        for (int i = 0; i < 4; ++i) cs[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[j][i], 1.0f, cs[i], 0, 0, 0);
+    }
+    if (sumb) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int jb = 0; jb < 2; ++jb) cs[jb] = __builtin_amdgcn_mfma_f32_16x16x4f32(1.0f, fb[j][jb], cs[jb], 0, 0, 0);
     }
   }
   // lane (g, r16) holds C[4g + v][r16]: rows m, columns n
