@@ -183,6 +183,16 @@ struct NoWork {
   __device__ __forceinline__ void operator()() const {}
 };
 
+// Order of a product's sum over K.  In bf16 it is part of a call's results: h
+// is stored rounded, so another order of the fp32 sums now and then moves an
+// element of h by 2^-9 of its size, and a dream that follows a near-tie the
+// other way from there is another dream.  A call's tile is chosen for speed;
+// the order follows the call's rows alone:
+//   Chain  one chain of MFMA slices over all of K;
+//   Runs   the order of the register-direct core (GemmRD): a chain per wave's
+//          run of consecutive slices, the runs summed in order.
+enum class KSum { Chain, Runs };
+
 // SPLIT (fp32): the fragments are split into three bf16 terms as they leave
 // LDS and multiplied on the bf16 matrix unit (split3).  The split costs 5.5
 // VALU instructions per fragment value, so it pays with at least four 16-row
@@ -232,11 +242,13 @@ struct GemmD {
   // the gates per unit: row 4 u + q)
   // pre(): caller work that does not depend on the product, run once the
   // first chunks' loads are issued, so that it fills their latency
-  template <class S, bool GPERM = false, class Pre = NoWork>
+  // ORD, runs: the order of the sum over K (KSum)
+  template <class S, bool GPERM = false, KSum ORD = KSum::Chain, class Pre = NoWork>
   __device__ __forceinline__ static void run(f32x4 (&acc)[NBW][MBW], const SrcX<DT>& w, const S& x,
-                                             int Kpad, DT* lds, Pre&& pre = Pre{}) {
+                                             int Kpad, DT* lds, Pre&& pre = Pre{}, int runs = 0) {
     static_assert(!S::kTwo, "the direct core reads one activation matrix");
     static_assert(!GPERM || NBW == 4, "the gate permutation needs four blocks per wave");
+    static_assert(!SPLIT_ || ORD == KSum::Chain, "split products are summed in one chain");
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int g = lane >> 4, r16 = lane & 15;
@@ -272,6 +284,16 @@ struct GemmD {
     for (int s = 0; s < STAGES - 1; ++s)
       if (s < nk) issue(s);
     pre();
+
+    constexpr bool kRuns = ORD == KSum::Runs;
+    f32x4 tot[kRuns ? NBW : 1][kRuns ? MBW : 1];  // the sum of the runs before this one
+    int left = runs;                              // slices left in the run
+    if constexpr (kRuns) {
+#pragma unroll
+      for (int i = 0; i < NBW; ++i)
+#pragma unroll
+        for (int j = 0; j < MBW; ++j) tot[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
 
     const int wni = wn(), wmi = wm();
     const int sw = (r16 >> 1) & 7;
@@ -311,12 +333,31 @@ struct GemmD {
 #pragma unroll
           for (int j = 0; j < MBW; ++j)
             b[j] = *reinterpret_cast<const uint4*>(buf + (BN + (wmi * MBW + j) * 16 + r16) * 128 + col);
+          if constexpr (kRuns) {
+            if (left == 0) {
+#pragma unroll
+              for (int i = 0; i < NBW; ++i)
+#pragma unroll
+                for (int j = 0; j < MBW; ++j) {
+                  tot[i][j] += acc[i][j];
+                  acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+                }
+              left = runs;
+            }
+            --left;
+          }
 #pragma unroll
           for (int i = 0; i < NBW; ++i)
 #pragma unroll
             for (int j = 0; j < MBW; ++j) Mfma<DT>::step(acc[i][j], a[i], b[j]);
         }
       }
+    }
+    if constexpr (kRuns) {
+#pragma unroll
+      for (int i = 0; i < NBW; ++i)
+#pragma unroll
+        for (int j = 0; j < MBW; ++j) acc[i][j] = tot[i][j] + acc[i][j];
     }
     __syncthreads();  // LDS free for the caller's epilogue
   }
@@ -451,6 +492,19 @@ inline int rd_waves(int Kpad, int kslice, int smax, int min_waves) {
   const int nsl = (Kpad + kslice - 1) / kslice;
   int nw = (nsl + smax - 1) / smax;
   return nw < min_waves ? min_waves : nw;
+}
+
+// Waves of a launch of the register-direct tile R over Kpad columns (at least
+// four), or 0 where they do not fit its compiled block size or the LDS; and
+// the slices of each wave's run.
+template <class R>
+int rd_fit(int Kpad) {
+  const int nw = rd_waves(Kpad, R::KSLICE, R::SMAX, 4);
+  return 64 * nw <= R::MAXT && R::lds_bytes(nw) <= kRdLdsMax ? nw : 0;
+}
+template <class R>
+int rd_run(int Kpad, int nw) {
+  return ((Kpad + R::KSLICE - 1) / R::KSLICE + nw - 1) / nw;
 }
 
 // Dynamic LDS above the default needs the kernel attribute raised once.

@@ -311,7 +311,10 @@ struct Gate4IO {
     return in;
   }
 
-  // g[t]: GEMM part of the gates (i, f, g, o) of unit u0 + t
+  // g[t]: GEMM part of the gates (i, f, g, o) of unit u0 + t.  FUSED: the bf16
+  // cell over one common denominator (lstm_cell_fused), which clamps its inputs
+  // (a NaN becomes a number); else separate sigmoids and tanhs, as GateIO has.
+  template <bool FUSED>
   __device__ __forceinline__ void commit(int ml, int u0, bool ok, const Gate4In& in, const float4 (&g)[4]) const {
     float cv[4], hv[4];
     const float cin[4] = {in.c.x, in.c.y, in.c.z, in.c.w};
@@ -319,9 +322,10 @@ struct Gate4IO {
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
       float cn, hn;
-      if constexpr (sizeof(DT) == 4) {
-        cn = fsigmoid(g[t].y + in.add[t].y) * cin[t] + fsigmoid(g[t].x + in.add[t].x) * ftanh(g[t].z + in.add[t].z);
-        hn = fsigmoid(g[t].w + in.add[t].w) * ftanh(cn);
+      if constexpr (sizeof(DT) == 4 || !FUSED) {
+        cn = fsigmoid(g[t].y + in.add[t].y) * cin[t] +
+             fsigmoid(g[t].x + in.add[t].x) * ftanh_cell<DT>(g[t].z + in.add[t].z);
+        hn = fsigmoid(g[t].w + in.add[t].w) * ftanh_cell<DT>(cn);
       } else {
         lstm_cell_fused(g[t].x + in.add[t].x, g[t].y + in.add[t].y, g[t].z + in.add[t].z, g[t].w + in.add[t].w,
                         cin[t], cn, hn);
@@ -413,7 +417,7 @@ __global__ void __launch_bounds__(C::NT) k_gates(const GatesArgs p) {
     float4 gsum[4];
 #pragma unroll
     for (int t = 0; t < 4; ++t) gsum[t] = *reinterpret_cast<const float4*>(E + r * ELD + 16 * grp + 4 * t);
-    io.commit(r, u0, uok && m0 + r < p.M, in[k], gsum);
+    io.template commit<true>(r, u0, uok && m0 + r < p.M, in[k], gsum);
   }
 }
 
@@ -423,8 +427,9 @@ __global__ void __launch_bounds__(C::NT) k_gates(const GatesArgs p) {
 // gate q of unit n0/4 + 16 wn + 4 g + v for row (wm MBW + j) 16 + r16 of the
 // tile.  Each lane then runs the LSTM cell of four consecutive units of its
 // MBW rows, with the next row's loads in flight under the current row's
-// cell; no LDS staging, no barrier after the GEMM.
-template <class C>
+// cell; no LDS staging, no barrier after the GEMM.  FEW: the sums (runs of
+// p.runs slices) and the cell of k_gates_rd.
+template <class C, bool FEW>
 __global__ void __launch_bounds__(C::NT) k_gates_direct(const GatesArgs p) {
   using DT = typename C::DT;
   constexpr int MBW = C::MBW;
@@ -446,7 +451,8 @@ __global__ void __launch_bounds__(C::NT) k_gates_direct(const GatesArgs p) {
   const SrcX<DT> w(reinterpret_cast<const DT*>(p.Wg), p.ldk, p.ldk, n0, C::BN, 4 * p.H);
   const SrcX<DT> x(reinterpret_cast<const DT*>(p.x_in), p.ldx, p.ldx, m0, C::BM, p.M);
   f32x4 acc[4][MBW];
-  C::template run<SrcX<DT>, true>(acc, w, x, (int)p.ldk, reinterpret_cast<DT*>(lds_raw));
+  C::template run<SrcX<DT>, true, FEW ? KSum::Runs : KSum::Chain>(acc, w, x, (int)p.ldk,
+                                                                 reinterpret_cast<DT*>(lds_raw), NoWork{}, p.runs);
 
   const Gate4IO<DT> io(p, m0, C::BM);
   const bool uok = u0 < p.H;  // H % 16 == 0: the four units are inside together
@@ -462,7 +468,7 @@ __global__ void __launch_bounds__(C::NT) k_gates_direct(const GatesArgs p) {
     float4 gs[4];
 #pragma unroll
     for (int t = 0; t < 4; ++t) gs[t] = make_float4(acc[0][j][t], acc[1][j][t], acc[2][j][t], acc[3][j][t]);
-    io.commit(row_of(j), u0, ok_of(j), cur, gs);
+    io.template commit<!FEW>(row_of(j), u0, ok_of(j), cur, gs);
     if (j + 1 < MBW) cur = nxt;
   }
 }
@@ -675,23 +681,20 @@ long gate_tiles(const GatesArgs& a) {
 
 // the epilogue from the accumulators where the core has four 16-row blocks
 // per wave, else through the staged tile
-template <class C, typename DT>
+template <class C, typename DT, bool FEW = false>
 hipError_t launch_gates_cfg(GatesArgs a, hipStream_t s) {
   a.map = tile_map((4 * a.H + C::BN - 1) / C::BN, (a.M + C::BM - 1) / C::BM,
                    (size_t)4 * a.H * a.ldk * sizeof(DT));
   if constexpr (IsGemmD<C>::value && C::NBW == 4)
-    return launch("gates", k_gates_direct<C>, dim3(grid_of(a.map)), dim3(C::NT), 0, s, a);
+    return launch("gates", k_gates_direct<C, FEW>, dim3(grid_of(a.map)), dim3(C::NT), 0, s, a);
   else
     return launch("gates", k_gates<C>, dim3(grid_of(a.map)), dim3(C::NT), 0, s, a);
 }
 
-// Register-direct gate launch with tile R; returns hipErrorNotSupported
-// when the K slices do not fit the compiled block size or the LDS budget.
+// Register-direct gate launch with tile R on nw waves (rd_fit).
 template <class R, typename DT>
-hipError_t launch_gates_rd(GatesArgs a, hipStream_t s) {
-  const int nw = rd_waves((int)a.ldk, R::KSLICE, R::SMAX, 4);
+hipError_t launch_gates_rd(GatesArgs a, int nw, hipStream_t s) {
   const size_t lds = R::lds_bytes(nw);
-  if (64 * nw > R::MAXT || lds > kRdLdsMax) return hipErrorNotSupported;
   hipError_t e = allow_lds(k_gates_rd<R>, lds);
   if (e != hipSuccess) return e;
   a.map = tile_map((4 * a.H + R::BN - 1) / R::BN, (a.M + R::BM - 1) / R::BM,
@@ -717,22 +720,34 @@ hipError_t launch_gates_rd(GatesArgs a, hipStream_t s) {
 // The register-direct tiles, which hide the whole K loop in one round trip,
 // are the fastest while every CU gets at most one (16 rows 5.9, 64 rows 7.2)
 // and fall off steeply beyond (128 rows 12.7 against 7.4 for 64 x 32).
+// In bf16 the sums and the cell do not follow the tile: calls of at most
+// kFewRows rows, where K fits the register-direct tiles, have theirs on every
+// tile, larger calls the chain and the fused cell.
+constexpr int kFewRows = 256;
 template <typename DT>
 hipError_t launch_gates(GatesArgs a, hipStream_t s) {
   using RD16 = GemmRD<DT, 2, 1, 4, 640>;
   using RD32 = GemmRD<DT, 2, 2, 4, 640>;
-  hipError_t e = hipErrorNotSupported;
-  if (gate_tiles<RD16>(a) <= kCUs) e = launch_gates_rd<RD16, DT>(a, s);
-  else if (gate_tiles<RD32>(a) <= kCUs) e = launch_gates_rd<RD32, DT>(a, s);
-  if (e != hipErrorNotSupported) return e;
+  constexpr bool bf = sizeof(DT) == 2;
+  const bool few = a.M <= kFewRows && rd_fit<RD32>((int)a.ldk);
+  if (!bf || few) {
+    const int n16 = rd_fit<RD16>((int)a.ldk), n32 = rd_fit<RD32>((int)a.ldk);
+    if (n16 && gate_tiles<RD16>(a) <= kCUs) return launch_gates_rd<RD16, DT>(a, n16, s);
+    if (n32 && gate_tiles<RD32>(a) <= kCUs) return launch_gates_rd<RD32, DT>(a, n32, s);
+  }
   using Cf = Cfgs<DT>;
   auto cost = [](long tiles, float fixed, float per) { return fixed + per * (float)((tiles + kCUs - 1) / kCUs); };
-  constexpr bool bf = sizeof(DT) == 2;
   const float c64x32 = cost(gate_tiles<typename Cf::Gates64x32>(a), bf ? 4.9f : 7.0f, bf ? 2.4f : 5.2f);
   const float c64x64 = cost(gate_tiles<typename Cf::Gates64x64>(a), bf ? 3.8f : 4.0f, bf ? 3.9f : 10.3f);
   const float c128x64 = cost(gate_tiles<typename Cf::Gates128x64>(a), bf ? 4.5f : 6.0f, bf ? 5.6f : 18.0f);
   const float small = std::min({c64x32, c64x64, c128x64});
   if constexpr (bf) {
+    if (few) {
+      a.runs = rd_run<RD32>((int)a.ldk, rd_fit<RD32>((int)a.ldk));
+      if (c128x64 <= small) return launch_gates_cfg<typename Cf::Gates128x64, DT, true>(a, s);
+      if (c64x64 <= small) return launch_gates_cfg<typename Cf::Gates64x64, DT, true>(a, s);
+      return launch_gates_cfg<typename Cf::Gates64x32, DT, true>(a, s);
+    }
     const float c128 = cost(gate_tiles<typename Cf::Gates128>(a), 2.5f, 10.2f);
     const long t256 = gate_tiles<typename Cf::Gates256>(a);
     const float c256 = cost(t256, 0.0f, 38.0f);

@@ -23,6 +23,7 @@ struct GatesArgs {
   float* h_trace;  // [M, H] fp32 or null
   float* c_trace;
   int nll_mode;
+  int runs;  // slices per run of the sum over K (KSum::Runs)
   TileMap map;
 };
 
