@@ -877,12 +877,13 @@ __global__ void __launch_bounds__(R::MAXT) k_ctrl_rd(const CtrlArgs p) {
 // their accumulators.  A chain of latencies: every load of a group of blocks
 // is issued before the first is used, the noise is drawn meanwhile.  TL: the
 // two-level controller, whose picks need whole rows, goes through LDS.
-// At B 256, A 128, H 1024 (bf16) 6.7 us per step, against 11.8 for the whole
-// product in k_ctrl on eight work-groups.
-template <typename DT, int U, bool TL>
+// fp32 only (ctrl_h_wanted).  At B 301, A 50, H 368, Z 40 5.1 us per step,
+// against 9.8 for the whole product.
+template <int U, bool TL>
 __global__ void __launch_bounds__(256) k_ctrl_z(const CtrlArgs p) {
+  using DT = float;
   constexpr int VEC = DType<DT>::VEC, KS = Mfma<DT>::KSLICE;
-  constexpr int SL = sizeof(DT) == 2 ? 2 : 4;  // K slices loaded together
+  constexpr int SL = 4;  // K slices loaded together
   constexpr int ELD = 324;                     // staged row (at most 320 logits)
   __shared__ float s_best[4][16];
   __shared__ int s_idx[4][16];
@@ -1115,9 +1116,13 @@ hipError_t launch_ctrl(const CtrlArgs& a, hipStream_t s) {
     const int nb = nbtot <= 1 ? 1 : nbtot <= 2 ? 2 : nbtot <= 3 ? 3 : nbtot <= 5 ? 5 : 9;
     const int smax = nb <= 5 ? 8 : 4;  // register budget
     // eight waves where their partial tiles fit the LDS: the K slices of a
-    // wave are a serial chain (a step for one state, K 288: 9.3 us on four)
-    const int nw = rd_waves((int)a.ldk, Mfma<DT>::KSLICE, smax, nb <= 5 ? 8 : 4);
-    if (nw <= 8 && (nb <= 5 || GemmRD<DT, 9, 1, 4, 512>::lds_bytes(nw) <= kRdLdsMax)) {
+    // wave are a serial chain (a step for one state, K 288: 9.3 us on four).
+    // A bf16 rollout, whose sums keep one order (KSum), takes four, and where
+    // K needs more than six the staged tiles.
+    constexpr bool kOrder = sizeof(DT) == 2 && !S::kTwo;
+    const int nw = rd_waves((int)a.ldk, Mfma<DT>::KSLICE, smax, nb <= 5 && !kOrder ? 8 : 4);
+    const bool fits9 = GemmRD<DT, 9, 1, 4, 512>::lds_bytes(nw) <= kRdLdsMax;
+    if (nw <= 8 && (fits9 || (nb <= 5 && !kOrder))) {
       switch (nb) {
         case 1: return launch_ctrl_rd<GemmRD<DT, 1, 1, 8, 512>, S>(a, nw, s);
         case 2: return launch_ctrl_rd<GemmRD<DT, 2, 1, 8, 512>, S>(a, nw, s);
@@ -1154,18 +1159,15 @@ hipError_t launch_ctrl(const CtrlArgs& a, hipStream_t s) {
   return hipErrorInvalidValue;
 }
 
-template <typename DT>
 hipError_t launch_ctrl_z(const CtrlArgs& a, hipStream_t s) {
   const dim3 grid((unsigned)((a.M + 15) / 16));
   const int nbw = (a.Nc / 16 + 3) / 4;
-  if (a.N > 0) return launch("ctrl", k_ctrl_z<DT, 3, true>, grid, dim3(256), 0, s, a);
-  if (nbw <= 1) return launch("ctrl", k_ctrl_z<DT, 1, false>, grid, dim3(256), 0, s, a);
-  if (nbw <= 2) return launch("ctrl", k_ctrl_z<DT, 2, false>, grid, dim3(256), 0, s, a);
-  return launch("ctrl", k_ctrl_z<DT, 3, false>, grid, dim3(256), 0, s, a);
+  if (a.N > 0) return launch("ctrl", k_ctrl_z<3, true>, grid, dim3(256), 0, s, a);
+  if (nbw <= 1) return launch("ctrl", k_ctrl_z<1, false>, grid, dim3(256), 0, s, a);
+  if (nbw <= 2) return launch("ctrl", k_ctrl_z<2, false>, grid, dim3(256), 0, s, a);
+  return launch("ctrl", k_ctrl_z<3, false>, grid, dim3(256), 0, s, a);
 }
 
-template hipError_t launch_ctrl_z<float>(const CtrlArgs&, hipStream_t);
-template hipError_t launch_ctrl_z<bf16_t>(const CtrlArgs&, hipStream_t);
 template hipError_t launch_ctrl<SrcX<float>>(const CtrlArgs&, hipStream_t);
 template hipError_t launch_ctrl<SrcX<bf16_t>>(const CtrlArgs&, hipStream_t);
 

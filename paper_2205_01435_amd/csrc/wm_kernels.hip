@@ -882,7 +882,7 @@ hipError_t rollout_impl(const Packed& P, const RolloutBufs& R, hipStream_t s) {
     ma.lh = R.Lh;
     if (R.h0) {
       ma.x = X;
-      if ((e = launch_ctrl_h<DT>(ma, L.Q, s)) != hipSuccess) return e;
+      if ((e = launch_ctrl_h(ma, L.Q, s)) != hipSuccess) return e;
     }
   }
 
@@ -903,7 +903,7 @@ hipError_t rollout_impl(const Packed& P, const RolloutBufs& R, hipStream_t s) {
     ca.rew_prev = t > 0 ? R.rewards + (long)(t - 1) * B : nullptr;
     ca.done_prev = t > 0 ? R.dones + (long)(t - 1) * B : nullptr;
     ca.lh = t > 0 || R.h0 ? R.Lh : nullptr;
-    e = R.Lh ? launch_ctrl_z<DT>(ca, s) : launch_ctrl<SrcX<DT>>(ca, s);
+    e = R.Lh ? launch_ctrl_z(ca, s) : launch_ctrl<SrcX<DT>>(ca, s);
     if (e != hipSuccess) return e;
     if (t == T) break;
 

@@ -108,7 +108,7 @@ __global__ void __launch_bounds__(C::NT) k_mdn(const MdnArgs p) {
   const int J = ntile * WAVES_N + wn;  // dim group of this wave
   const int j = 4 * J + g;             // latent dim of this lane
   const bool head_tile = p.nll_mode && ntile == p.ntd;
-  const bool ctl = p.lh && 2 * ntile >= p.zt;  // a tile of the controller's h part
+  const bool ctl = sizeof(DT) == 4 && p.lh && 2 * ntile >= p.zt;  // a tile of the controller's h part
   // rollout: the actions of this lane's rows and their previous latents
   // (kept by frozen rows), fetched ahead of the GEMM
   int actp[MBW];
@@ -262,7 +262,7 @@ __global__ void __launch_bounds__(R::MAXT) k_mdn_rd(const MdnArgs p) {
   const int t = threadIdx.x;
   const int d = t & 3, ml = t >> 2;
   const int m = m0 + ml, j = 4 * J + d;
-  const bool ctl = p.lh && J >= p.zt;  // a tile of the controller's h part
+  const bool ctl = sizeof(DT) == 4 && p.lh && J >= p.zt;  // a tile of the controller's h part
   const int nc0 = (J - p.zt) * R::BN;
   const bool mine = !ctl && t < 4 * R::BM && m < p.M && j < p.Z;
   const Rng rng{p.k0, p.k1};
@@ -408,21 +408,18 @@ hipError_t launch_mdn(const MdnArgs& a, int Q, int ntiles, hipStream_t s) {
 }
 
 bool ctrl_h_wanted(const Layout& L, int B) {
-  if (L.Z + L.ldh > L.ldk) return false;
+  if (L.dt == 1 || L.Z + L.ldh > L.ldk) return false;
   if (L.N > 0 && L.Nc / 16 > 20) return false;
   const float with = mdn_cost(L.dt == 1, L.Q, B, L.Z / 8 + (L.Nc + 32 * L.Q - 1) / (32 * L.Q)).best();
   return with <= mdn_cost(L.dt == 1, L.Q, B, L.Z / 8).best() + 5.0f;
 }
 
-template <typename DT>
 hipError_t launch_ctrl_h(MdnArgs a, int Q, hipStream_t s) {
   a.zt = 0;
-  return launch_mdn_k<DT>("lh", a, Q, 0, s);
+  return launch_mdn_k<float>("lh", a, Q, 0, s);
 }
 
 template hipError_t launch_mdn<float>(const MdnArgs&, int, int, hipStream_t);
 template hipError_t launch_mdn<bf16_t>(const MdnArgs&, int, int, hipStream_t);
-template hipError_t launch_ctrl_h<float>(MdnArgs, int, hipStream_t);
-template hipError_t launch_ctrl_h<bf16_t>(MdnArgs, int, hipStream_t);
 
 }  // namespace wm

@@ -111,18 +111,18 @@ template <typename DT>
 hipError_t launch_mdn(const MdnArgs& a, int Q, int ntiles, hipStream_t s);
 template <class S>
 hipError_t launch_ctrl(const CtrlArgs& a, hipStream_t s);
-// Whether a rollout computes the controller's h part beside the mixture: the
-// matrix rows of W_c then need to be readable Z + ldh wide, the two-level
-// controller's logits to fit k_ctrl_z's staged rows, and the extra tiles to
+// Whether a rollout computes the controller's h part beside the mixture: fp32
+// only (it sums the logits' h columns before their z columns, and a bf16
+// rollout's sums keep one order, KSum), the matrix rows of W_c need to be
+// readable Z + ldh wide, the two-level controller's logits to fit k_ctrl_z's
+// staged rows, and the extra tiles to
 // cost the mixture launch less than the deeper product costs the controller
 // (about 6 us; at B 4096, where they would start a second round of tiles, they
 // cost 10).
 bool ctrl_h_wanted(const Layout& L, int B);
 // The controller's h part alone (MdnArgs::lh, zt = 0), and the rollout's
 // decision from it.
-template <typename DT>
 hipError_t launch_ctrl_h(MdnArgs a, int Q, hipStream_t s);
-template <typename DT>
 hipError_t launch_ctrl_z(const CtrlArgs& a, hipStream_t s);
 
 }  // namespace wm

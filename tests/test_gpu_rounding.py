@@ -100,3 +100,25 @@ def test_saturated_gates_keep_c():
     # 2^-23: the rounding of the sum
     bound = 1e-6 * np.abs(a) + sig(i) * (1e-6 * np.abs(np.tanh(g)) + 5e-7) + 2.0 ** -23 * np.abs(a + b) + 1e-30
     assert np.all(err <= bound), float((err / bound).max())
+
+
+# B, b, Z, H, A, K: the controller on staged tiles, on register-direct ones
+CTRL = [(256, 48, 64, 1024, 128, 8), (250, 40, 32, 512, 24, 4), (130, 16, 24, 1024, 200, 3)]
+
+
+@pytest.mark.parametrize("B,b,Z,H,A,K", CTRL)
+def test_rewards_do_not_follow_the_batch(B, b, Z, H, A, K):
+    """The reward logits are rows of the controller's product: the bits of a
+    transition's reward are those of its own row."""
+    print("[gpu-rounding] rewards", B, b, Z, H, A, K, flush=True)
+    w, inp = _case(B, 2, Z, H, A, K, "bf16")
+    m = wmlib.pack(inp["weights"], Z, H, A, K, "bf16")
+    h0 = _state(B, H, B)[0]
+    out = []
+    for n in (B, b):
+        r = wmlib.rollout(m, _cuda(inp["z0"][:n]), _cuda(inp["mask"][:n]), T=2, seed=7, done=False,
+                          h0=_cuda(h0[:n]))
+        torch.cuda.synchronize()
+        out.append((r.actions[:, :b], r.rewards[:, :b], r.z_out[:, :b]))
+    for x, y in zip(*out):
+        assert torch.equal(x, y)

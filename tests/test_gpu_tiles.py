@@ -73,11 +73,11 @@ def test_tiles(B, Z, H, A, K, dtype, monkeypatch):
 H_PART = [
     (1, 8, 64, 1, 0, 0, 1, "fp32"),          # one row, one action
     (33, 40, 64, 61, 0, 0, 3, "fp32"),       # Z ends inside a K slice; reward row in the next block
-    (100, 72, 192, 62, 0, 0, 8, "bf16"),     # three K slices of z; A + 2 = 64
-    (301, 128, 256, 300, 0, 0, 5, "bf16"),   # two rounds of blocks per wave
-    (45, 16, 64, 1500, 0, 0, 2, "bf16"),     # many rounds
+    (100, 72, 192, 62, 0, 0, 8, "fp32"),     # three K slices of z; A + 2 = 64
+    (301, 128, 256, 300, 0, 0, 5, "fp32"),   # two rounds of blocks per wave
+    (45, 16, 64, 1500, 0, 0, 2, "fp32"),     # many rounds
     (77, 24, 128, 0, 9, 30, 3, "fp32"),      # two levels
-    (130, 64, 256, 0, 80, 200, 8, "bf16"),
+    (130, 64, 256, 0, 80, 200, 8, "fp32"),
 ]
 
 
