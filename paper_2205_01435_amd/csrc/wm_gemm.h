@@ -190,8 +190,9 @@ struct NoWork {
 // the order follows the call's rows alone:
 //   Chain  one chain of MFMA slices over all of K;
 //   Runs   the order of the register-direct core (GemmRD): a chain per wave's
-//          run of consecutive slices, the runs summed in order.
-enum class KSum { Chain, Runs };
+//          run of consecutive slices, the runs summed in order;
+//   Pairs  that of two waves taking turns: the even slices, plus the odd ones.
+enum class KSum { Chain, Runs, Pairs };
 
 // SPLIT (fp32): the fragments are split into three bf16 terms as they leave
 // LDS and multiplied on the bf16 matrix unit (split3).  The split costs 5.5
@@ -285,10 +286,10 @@ struct GemmD {
       if (s < nk) issue(s);
     pre();
 
-    constexpr bool kRuns = ORD == KSum::Runs;
-    f32x4 tot[kRuns ? NBW : 1][kRuns ? MBW : 1];  // the sum of the runs before this one
-    int left = runs;                              // slices left in the run
-    if constexpr (kRuns) {
+    constexpr bool kRuns = ORD == KSum::Runs, kPairs = ORD == KSum::Pairs, kTwo = kRuns || kPairs;
+    f32x4 tot[kTwo ? NBW : 1][kTwo ? MBW : 1];  // the runs before this one; the odd slices
+    int left = runs;                            // slices left in the run
+    if constexpr (kTwo) {
 #pragma unroll
       for (int i = 0; i < NBW; ++i)
 #pragma unroll
@@ -349,11 +350,14 @@ struct GemmD {
 #pragma unroll
           for (int i = 0; i < NBW; ++i)
 #pragma unroll
-            for (int j = 0; j < MBW; ++j) Mfma<DT>::step(acc[i][j], a[i], b[j]);
+            for (int j = 0; j < MBW; ++j) {
+              if constexpr (kPairs) Mfma<DT>::step(sl ? tot[i][j] : acc[i][j], a[i], b[j]);
+              else Mfma<DT>::step(acc[i][j], a[i], b[j]);
+            }
         }
       }
     }
-    if constexpr (kRuns) {
+    if constexpr (kTwo) {
 #pragma unroll
       for (int i = 0; i < NBW; ++i)
 #pragma unroll

@@ -87,7 +87,8 @@ __device__ __forceinline__ void mdn_commit(const MdnArgs& p, int m, int j, float
 
 // KC: the number of mixture components (the call's K), a compile-time
 // constant so that the feature selections of the epilogue fold away
-template <class C, int KC>
+// ORD: the order of the sum over K (KSum)
+template <class C, int KC, KSum ORD>
 __global__ void __launch_bounds__(C::NT) k_mdn(const MdnArgs p) {
   using DT = typename C::DT;
   constexpr int K = KC;
@@ -155,10 +156,13 @@ __global__ void __launch_bounds__(C::NT) k_mdn(const MdnArgs p) {
     if (!p.nll_mode && !ctl) draw_eps();
   };
   f32x4 acc[Q][MBW];
-  if constexpr (kPre)
-    C::run(acc, w, x, (int)p.ldh, reinterpret_cast<DT*>(lds_raw), pre);
-  else
+  auto none = []() {};
+  if constexpr (!IsGemmD<C>::value)
     C::run(acc, w, x, (int)p.ldh, reinterpret_cast<DT*>(lds_raw));
+  else if constexpr (kPre)
+    C::template run<SrcX<DT>, false, ORD>(acc, w, x, (int)p.ldh, reinterpret_cast<DT*>(lds_raw), pre, p.runs);
+  else
+    C::template run<SrcX<DT>, false, ORD>(acc, w, x, (int)p.ldh, reinterpret_cast<DT*>(lds_raw), none, p.runs);
   const bool owner = C::kw() == 0;  // holds the summed tile
 
   if (ctl) {
@@ -319,10 +323,10 @@ template <> struct Cfgs<bf16_t> {
   template <int Q> using Mdn128 = GemmD<bf16_t, Q, 2, 2, 4, 2>;  // eight waves
 };
 
-template <class C, typename DT, int KC>
+template <class C, typename DT, int KC, KSum ORD = KSum::Chain>
 hipError_t launch_mdn_cfg(const char* name, MdnArgs a, int ntiles, hipStream_t s) {
   a.map = tile_map(ntiles, (a.M + C::BM - 1) / C::BM, (size_t)a.Nm * a.ldh * sizeof(DT));
-  return launch(name, k_mdn<C, KC>, dim3(grid_of(a.map)), dim3(C::NT), 0, s, a);
+  return launch(name, k_mdn<C, KC, ORD>, dim3(grid_of(a.map)), dim3(C::NT), 0, s, a);
 }
 
 // Mixture tile of a call, chosen as the gate tiles are (launch_gates): the
@@ -354,29 +358,49 @@ MdnCost mdn_cost(bool bf16, int Q, int M, int ntiles) {
                  Q % 2 == 0 ? cost(128, 18.5f, 2.6f, 13.3f) : INFINITY};
 }
 
+// In bf16 the sums over K do not follow the tile but the call (KSum): rollouts
+// of at most kRunRows rows, where K fits the register-direct tiles, have the
+// runs of those; other calls of at most kPairRows rows the even and odd slices
+// apart; larger ones a chain.  (128-row tiles are left to the chain: below
+// 2048 rows the 64-row ones are as fast.)
+constexpr int kRunRows = 1024, kPairRows = 2048;
+
 template <typename DT, int Q, int KC>
 hipError_t launch_mdn_q(const char* name, const MdnArgs& a, int ntiles, hipStream_t s) {
-  if (!a.nll_mode) {
-    using R = GemmRD<DT, Q, 1, 4, 640>;
-    const int nw = rd_waves((int)a.ldh, R::KSLICE, R::SMAX, 4);
-    const size_t lds = R::lds_bytes(nw);
+  using R = GemmRD<DT, Q, 1, 4, 640>;
+  constexpr bool bf = sizeof(DT) == 2;
+  const int nw = a.nll_mode ? 0 : rd_fit<R>((int)a.ldh);
+  const bool few = bf && nw && a.M <= kRunRows;
+  MdnArgs b = a;
+  if (nw && (few || !bf)) {
     const int nt = (a.lh ? a.zt + (a.Nc + R::BN - 1) / R::BN : a.Z / 4);  // one dim group per tile
     const long tiles = (long)nt * ((a.M + R::BM - 1) / R::BM);
-    if (tiles <= kCUs && 64 * nw <= R::MAXT && lds <= kRdLdsMax) {
+    if (tiles <= kCUs) {
+      const size_t lds = R::lds_bytes(nw);
       hipError_t e = allow_lds(k_mdn_rd<R>, lds);
       if (e != hipSuccess) return e;
-      MdnArgs b = a;
       b.map = tile_map(nt, (a.M + R::BM - 1) / R::BM, (size_t)a.Nm * a.ldh * sizeof(DT));
       return launch(name, k_mdn_rd<R>, dim3(grid_of(b.map)), dim3(64 * nw), lds, s, b);
     }
+    b.runs = rd_run<R>((int)a.ldh, nw);
   }
   using Cf = Cfgs<DT>;
   if (a.lh) ntiles = a.zt / 2 + (a.Nc + 32 * Q - 1) / (32 * Q);
-  const MdnCost c = mdn_cost(sizeof(DT) == 2, Q, a.M, ntiles);
+  const MdnCost c = mdn_cost(bf, Q, a.M, ntiles);
+  if constexpr (bf) {
+    using T32 = typename Cf::template Mdn32<Q>;
+    using T64 = typename Cf::template Mdn64<Q>;
+    if (few)
+      return c.c64 <= c.c32 ? launch_mdn_cfg<T64, DT, KC, KSum::Runs>(name, b, ntiles, s)
+                            : launch_mdn_cfg<T32, DT, KC, KSum::Runs>(name, b, ntiles, s);
+    if (a.M <= kPairRows)
+      return c.c64 <= c.c32 ? launch_mdn_cfg<T64, DT, KC, KSum::Pairs>(name, b, ntiles, s)
+                            : launch_mdn_cfg<T32, DT, KC, KSum::Pairs>(name, b, ntiles, s);
+  }
   if constexpr (Q % 2 == 0 || sizeof(DT) == 4) {
     if (c.c128 <= c.best()) return launch_mdn_cfg<typename Cf::template Mdn128<Q>, DT, KC>(name, a, ntiles, s);
   }
-  if constexpr (sizeof(DT) == 2) {
+  if constexpr (bf) {
     if (c.c64 <= c.c32) return launch_mdn_cfg<typename Cf::template Mdn64<Q>, DT, KC>(name, a, ntiles, s);
   } else {
     if (c.c16 <= c.c32) return launch_mdn_cfg<typename Cf::template Mdn16<Q>, DT, KC>(name, a, ntiles, s);

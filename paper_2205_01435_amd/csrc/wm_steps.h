@@ -49,6 +49,7 @@ struct MdnArgs {
   float* head;         // [M, 2]
   int ntd;
   int nll_mode;
+  int runs;  // slices per run of the sum over K (KSum::Runs)
   // rollout, with lh: tiles past the zt groups of four latent dims compute the
   // next step's controller logits' h part, lh[m][n] = W_c[n][Z ..] . h_t+1
   // (bias not added), [M, Nc] fp32; zt = 0: only those

@@ -122,3 +122,31 @@ def test_rewards_do_not_follow_the_batch(B, b, Z, H, A, K):
         out.append((r.actions[:, :b], r.rewards[:, :b], r.z_out[:, :b]))
     for x, y in zip(*out):
         assert torch.equal(x, y)
+
+
+# B (64- or 32-row tiles), b (register-direct up to 1024 rows, else 32-row
+# tiles), Z, H, K; h of 257 rows and more comes from the same chain of sums
+MIX = [
+    (1000, 300, 64, 512, 8),    # runs of four slices
+    (1024, 257, 40, 1008, 7),   # an odd block count, ragged rows
+    (600, 260, 128, 80, 3),     # runs of one slice, the last wave's empty
+    (2048, 1030, 64, 512, 8),   # even and odd slices
+    (1500, 1100, 16, 1344, 5),  # K too deep for the register-direct tiles
+    (900, 300, 72, 1344, 2),
+]
+
+
+@pytest.mark.parametrize("B,b,Z,H,K", MIX)
+def test_mixture_sums_do_not_follow_the_tile(B, b, Z, H, K):
+    print("[gpu-rounding] mixture", B, b, Z, H, K, flush=True)
+    w, inp = _case(B, 1, Z, H, 20, K, "bf16")
+    m = wmlib.pack(inp["weights"], Z, H, 20, K, "bf16")
+    h0, c0 = _state(B, H, B)
+    out = []
+    for n in (B, b):
+        r = wmlib.rollout(m, _cuda(inp["z0"][:n]), _cuda(inp["mask"][:n]), T=1, seed=7, done=False, h0=_cuda(h0[:n]),
+                          c0=_cuda(c0[:n]))
+        torch.cuda.synchronize()
+        out.append((r.actions[0, :b], r.h_T[:b], r.z_out[1, :b]))
+    for x, y in zip(*out):
+        assert torch.equal(x, y)
