@@ -129,9 +129,7 @@ wm_status rollout_call(const wm_dims* dims, const void* packed, int32_t B, int32
   if ((int64_t)B * (T + 1) > (int64_t)1 << 30)
     return fail(WM_ERR_UNSUPPORTED, "B*(T+1) too large");
   if (T == 0) return ok();
-  // the least that the call runs in; with the controller logits' h part (what
-  // wm_workspace_bytes asks for) its steps are faster
-  const size_t need = wm::rollout_workspace(L, B, nullptr, nullptr, false);
+  const size_t need = wm::rollout_workspace(L, B, nullptr, nullptr);
   if (noalloc) {
     if (need > wm::kStaticScratchBytes)
       return fail(WM_ERR_UNSUPPORTED, "wm_rollout_noalloc: B=%d needs %zu bytes of workspace, above the "
@@ -164,7 +162,7 @@ wm_status rollout_call(const wm_dims* dims, const void* packed, int32_t B, int32
   R.z0 = z0; R.h0 = h0; R.c0 = c0; R.done_io = done_io; R.lengths = lengths; R.mask = valid_mask;
   R.z_out = z_out; R.actions = actions; R.rewards = rewards; R.dones = dones;
   R.h_T = h_T; R.c_T = c_T; R.h_trace = h_trace; R.c_trace = c_trace;
-  wm::rollout_workspace(L, B, ws, &R, workspace_bytes >= wm::rollout_workspace(L, B, nullptr, nullptr));
+  wm::rollout_workspace(L, B, ws, &R);
   R.preset_err = (flags & WM_FLAG_TEST_ABORT) ? 1u : 0u;
   wm::Packed P{L, packed};
   hipError_t e = wm::launch_rollout(P, R, s);

@@ -899,7 +899,9 @@ __global__ void __launch_bounds__(256) k_ctrl_z(const CtrlArgs p) {
   if (tid < 16 && m < p.M) rs = row_state(p, m);
   const SrcX<DT> w(reinterpret_cast<const DT*>(p.Wc), p.ldk, p.ldk, 0, p.Nc, p.Nc);
   const SrcX<DT> x(reinterpret_cast<const DT*>(p.x), p.ldx, p.ldx, m0, 16, p.M);
-  const rsrc_t rl = uniform_rsrc(p.lh ? p.lh + (long)m0 * p.Nc : nullptr, p.lh ? (uint32_t)(rows * p.Nc) * 4u : 0u);
+  const uint32_t ldl = (uint32_t)p.ldlh;
+  const rsrc_t rl = uniform_rsrc(p.lh ? p.lh + (long)m0 * p.ldlh : nullptr,
+                                 p.lh ? ((uint32_t)(rows - 1) * ldl + (uint32_t)p.Nc) * 4u : 0u);
   const rsrc_t rb = uniform_rsrc(p.bc, (uint32_t)p.Nc * 4u);
   const rsrc_t rm = uniform_rsrc(p.mask + (long)m0 * A, (uint32_t)(rows * A));
   const Rng rng{p.k0, p.k1};
@@ -929,7 +931,7 @@ __global__ void __launch_bounds__(256) k_ctrl_z(const CtrlArgs p) {
     for (int i = 0; i < U; ++i) {
       const int n = (i0 + 4 * i) * 16 + 4 * g;
       const bool in = i0 + 4 * i < nbtot;
-      const uint4 h = bload16(rl, in && m < p.M ? (uint32_t)(r16 * p.Nc + n) * 4u : kOffNone);
+      const uint4 h = bload16(rl, in && m < p.M ? ((uint32_t)r16 * ldl + (uint32_t)n) * 4u : kOffNone);
       acc[i] = f32x4{__uint_as_float(h.x), __uint_as_float(h.y), __uint_as_float(h.z), __uint_as_float(h.w)};
       bias[i] = as_float4(bload16(rb, in ? (uint32_t)n * 4u : kOffNone));
 #pragma unroll

@@ -38,7 +38,6 @@ struct RolloutBufs {
   float* lg;           // [B, Nc] logits of a wide two-level controller, or null
   unsigned* sync;      // kSyncWords barrier and status words, at workspace offset 0
   unsigned preset_err; // initial value of the error word (WM_FLAG_TEST_ABORT)
-  float* Lh;           // [B, Nc] the controller logits' h part (per-step path), or null
 };
 
 struct NllBufs {
@@ -75,9 +74,7 @@ constexpr int kSyncViol = 64 * 16 + 1;
 
 // Workspace sizes; with a non-null `ws` the workspace pointers of the
 // buffer struct are also set (ws must be 256-byte aligned).
-// A rollout also runs, at more time per step, in a workspace without the
-// controller logits' h part (with_lh = false).
-size_t rollout_workspace(const Layout& L, int B, char* ws, RolloutBufs* R, bool with_lh = true);
+size_t rollout_workspace(const Layout& L, int B, char* ws, RolloutBufs* R);
 size_t nll_workspace(const Layout& L, int B, int T, char* ws, NllBufs* N);
 
 hipError_t launch_pack(const Packed& P, void* packed, const float* W_g, const float* b_g,

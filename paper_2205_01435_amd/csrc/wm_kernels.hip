@@ -874,14 +874,20 @@ hipError_t rollout_impl(const Packed& P, const RolloutBufs& R, hipStream_t s) {
   ma.sig = (R.flags & WM_FLAG_SIGMA_TAU) ? sqrtf(R.tau) : 1.0f;
   ma.nll_mode = 0;
   const int mdn_tiles = Z / 8;
-  if (R.Lh) {  // the controller's h part from the mixture launches; step 0's from h0
+  // The controller's h part from the mixture launches (step 0's from h0).  Step
+  // t's waits in the z and h columns of the buffer of X_t+1, whose last reader
+  // was the gate launch of step t - 1 and whose next writer is that of step t.
+  const bool hpart = ctrl_h_wanted(L, B);
+  auto lh_of = [&](int t) { return reinterpret_cast<float*>(X + (long)((t + 1) & 1) * BX); };
+  if (hpart) {
     ma.zt = Z / 4;
     ma.Wc = ca.Wc;
     ma.ldk = L.ldk;
     ma.Nc = L.Nc;
-    ma.lh = R.Lh;
+    ma.ldl = ca.ldlh = L.ldx;
     if (R.h0) {
       ma.x = X;
+      ma.lh = lh_of(0);
       if ((e = launch_ctrl_h(ma, L.Q, s)) != hipSuccess) return e;
     }
   }
@@ -902,8 +908,8 @@ hipError_t rollout_impl(const Packed& P, const RolloutBufs& R, hipStream_t s) {
     ca.act_prev = t > 0 ? R.actions + (long)(t - 1) * B : nullptr;
     ca.rew_prev = t > 0 ? R.rewards + (long)(t - 1) * B : nullptr;
     ca.done_prev = t > 0 ? R.dones + (long)(t - 1) * B : nullptr;
-    ca.lh = t > 0 || R.h0 ? R.Lh : nullptr;
-    e = R.Lh ? launch_ctrl_z(ca, s) : launch_ctrl<SrcX<DT>>(ca, s);
+    ca.lh = hpart && (t > 0 || R.h0) ? lh_of(t) : nullptr;
+    e = hpart ? launch_ctrl_z(ca, s) : launch_ctrl<SrcX<DT>>(ca, s);
     if (e != hipSuccess) return e;
     if (t == T) break;
 
@@ -916,6 +922,7 @@ hipError_t rollout_impl(const Packed& P, const RolloutBufs& R, hipStream_t s) {
     if (e != hipSuccess) return e;
 
     ma.x = Xn;
+    if (hpart) ma.lh = lh_of(t + 1);
     ma.act = R.actions + (long)t * B;
     ma.z_prev = R.z_out + (long)t * BZ;
     ma.z_next = R.z_out + (long)(t + 1) * BZ;
@@ -1004,7 +1011,7 @@ hipError_t nll_impl(const Packed& P, const NllBufs& N, hipStream_t s, bool heads
 
 }  // namespace
 
-size_t rollout_workspace(const Layout& L, int B, char* ws, RolloutBufs* R, bool with_lh) {
+size_t rollout_workspace(const Layout& L, int B, char* ws, RolloutBufs* R) {
   size_t o = 0;
   const size_t os = o;
   o = wm_align256(o + (size_t)kSyncWords * 4);  // barrier and status words
@@ -1021,11 +1028,7 @@ size_t rollout_workspace(const Layout& L, int B, char* ws, RolloutBufs* R, bool 
   const bool wide2 = L.N > 0 && (L.Nc / 16 + 3) / 4 > 5;
   const size_t og = o;
   if (wide2) o = wm_align256(o + (size_t)B * L.Nc * 4);
-  const bool lh = with_lh && ctrl_h_wanted(L, B);
-  const size_t ol = o;
-  if (lh) o = wm_align256(o + (size_t)B * L.Nc * 4);
   if (ws && R) {
-    R->Lh = lh ? reinterpret_cast<float*>(ws + ol) : nullptr;
     R->lg = wide2 ? reinterpret_cast<float*>(ws + og) : nullptr;
     R->x = ws + ox;
     R->c = reinterpret_cast<float*>(ws + oc);

@@ -174,7 +174,7 @@ __global__ void __launch_bounds__(C::NT) k_mdn(const MdnArgs p) {
 #pragma unroll
       for (int q = 0; q < Q; ++q) {
         const int n = nc0 + (wn * Q + q) * 16 + 4 * g;
-        if (n < p.Nc) *reinterpret_cast<f32x4*>(p.lh + (long)m * p.Nc + n) = acc[q][jj];
+        if (n < p.Nc) *reinterpret_cast<f32x4*>(p.lh + (long)m * p.ldl + n) = acc[q][jj];
       }
     }
     return;
@@ -286,7 +286,7 @@ __global__ void __launch_bounds__(R::MAXT) k_mdn_rd(const MdnArgs p) {
     for (int e = t; e < R::BM * R::BN / 4; e += (int)blockDim.x) {
       const int r = e / (R::BN / 4), n = 4 * (e % (R::BN / 4));
       if (m0 + r < p.M && nc0 + n < p.Nc)
-        *reinterpret_cast<float4*>(p.lh + (long)(m0 + r) * p.Nc + nc0 + n) =
+        *reinterpret_cast<float4*>(p.lh + (long)(m0 + r) * p.ldl + nc0 + n) =
             *reinterpret_cast<const float4*>(R::E(lds_dyn) + r * R::ELD + n);
     }
     return;
@@ -432,7 +432,7 @@ hipError_t launch_mdn(const MdnArgs& a, int Q, int ntiles, hipStream_t s) {
 }
 
 bool ctrl_h_wanted(const Layout& L, int B) {
-  if (L.dt == 1 || L.Z + L.ldh > L.ldk) return false;
+  if (L.dt == 1 || L.Z + L.ldh > L.ldk || L.Nc > L.Kx) return false;
   if (L.N > 0 && L.Nc / 16 > 20) return false;
   const float with = mdn_cost(L.dt == 1, L.Q, B, L.Z / 8 + (L.Nc + 32 * L.Q - 1) / (32 * L.Q)).best();
   return with <= mdn_cost(L.dt == 1, L.Q, B, L.Z / 8).best() + 5.0f;

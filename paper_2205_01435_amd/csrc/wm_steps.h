@@ -52,12 +52,13 @@ struct MdnArgs {
   int runs;  // slices per run of the sum over K (KSum::Runs)
   // rollout, with lh: tiles past the zt groups of four latent dims compute the
   // next step's controller logits' h part, lh[m][n] = W_c[n][Z ..] . h_t+1
-  // (bias not added), [M, Nc] fp32; zt = 0: only those
+  // (bias not added), fp32, Nc of each row of ldl; zt = 0: only those
   int zt;
   const void* Wc;
   long ldk;
   int Nc;
   float* lh;
+  long ldl;
   TileMap map;
 };
 
@@ -98,7 +99,8 @@ struct CtrlArgs {
   float* logits_out;
   long ldl;
   int ncol;
-  const float* lh;  // rollout: the logits' h part [M, Nc] (k_ctrl_z), null: zero
+  const float* lh;  // rollout: the logits' h part (k_ctrl_z), Nc of each row of ldlh, null: zero
+  long ldlh;
   float* lg_ws;  // rollout workspace [M, Nc] for those logits (wide two-level controllers)
   TileMap map;   // of k_ctrl_logits
 };
@@ -115,9 +117,9 @@ hipError_t launch_ctrl(const CtrlArgs& a, hipStream_t s);
 // Whether a rollout computes the controller's h part beside the mixture: fp32
 // only (it sums the logits' h columns before their z columns, and a bf16
 // rollout's sums keep one order, KSum), the matrix rows of W_c need to be
-// readable Z + ldh wide, the two-level controller's logits to fit k_ctrl_z's
-// staged rows, and the extra tiles to
-// cost the mixture launch less than the deeper product costs the controller
+// readable Z + ldh wide, the logits to fit the z and h columns of an activation
+// row (where they wait for the next step), the two-level controller's to fit
+// k_ctrl_z's staged rows, and the extra tiles to cost the mixture launch less than the deeper product costs the controller
 // (about 6 us; at B 4096, where they would start a second round of tiles, they
 // cost 10).
 bool ctrl_h_wanted(const Layout& L, int B);

@@ -107,6 +107,15 @@ def test_rollout_argument_checks():
     assert "workspace" in wmlib.load().wm_last_error().decode() or True
 
 
+def test_rollout_refuses_less_than_the_workspace_size():
+    # sizes whose controller has its h part computed beside the mixture (fp32)
+    for B, Z, H, A, dtype in ((300, 40, 368, 50, "fp32"), (4, 8, 16, 4, "fp32"), (300, 40, 368, 50, "bf16")):
+        d = wmlib.make_dims(Z, H, A, 3, dtype)
+        need = wmlib.workspace_bytes(d, B, 3, wmlib.WS_ROLLOUT)
+        for less in (1, 256, B * (A + 2) * 4):
+            assert _rollout_call(dims=ctypes.byref(d), B=B, ws_bytes=need - less) == wmlib.WM_ERR_WORKSPACE, (B, less)
+
+
 def test_nll_argument_checks():
     lib = wmlib.load()
     d = wmlib.make_dims(8, 16, 4, 2)

@@ -68,25 +68,24 @@ def test_tiles(B, Z, H, A, K, dtype, monkeypatch):
     assert live > 0
 
 
-# B, Z, H, A (or N, L), K, dtype: controllers whose h part comes from the
-# mixture launches
+# B, Z, H, A (or N, L), K: fp32 controllers whose h part comes from the mixture
+# launches
 H_PART = [
-    (1, 8, 64, 1, 0, 0, 1, "fp32"),          # one row, one action
-    (33, 40, 64, 61, 0, 0, 3, "fp32"),       # Z ends inside a K slice; reward row in the next block
-    (100, 72, 192, 62, 0, 0, 8, "fp32"),     # three K slices of z; A + 2 = 64
-    (301, 128, 256, 300, 0, 0, 5, "fp32"),   # two rounds of blocks per wave
-    (45, 16, 64, 1500, 0, 0, 2, "fp32"),     # many rounds
-    (77, 24, 128, 0, 9, 30, 3, "fp32"),      # two levels
-    (130, 64, 256, 0, 80, 200, 8, "fp32"),
+    (1, 8, 64, 1, 0, 0, 1),          # one row, one action
+    (33, 40, 64, 61, 0, 0, 3),       # Z ends inside a K slice; reward row in the next block
+    (100, 72, 192, 62, 0, 0, 8),     # three K slices of z; A + 2 = 64
+    (301, 128, 256, 300, 0, 0, 5),   # two rounds of blocks per wave
+    (45, 64, 704, 766, 0, 0, 2),     # many rounds; as many logits as an activation row has columns
+    (77, 24, 128, 0, 9, 30, 3),      # two levels
+    (130, 64, 256, 0, 80, 200, 8),
 ]
 
 
-@pytest.mark.parametrize("B,Z,H,A,N,L,K,dtype", H_PART)
-def test_controller_h_part(B, Z, H, A, N, L, K, dtype, monkeypatch):
+@pytest.mark.parametrize("B,Z,H,A,N,L,K", H_PART)
+def test_controller_h_part(B, Z, H, A, N, L, K, monkeypatch):
     """Per-step rollouts with the controller's h part beside the mixture, from
-    a given state, against the oracle, and against the same call in a
-    workspace that has no room for it."""
-    print("[gpu-tiles] h part", B, Z, H, A, N, L, K, dtype, flush=True)
+    a given state, against the oracle."""
+    print("[gpu-tiles] h part", B, Z, H, A, N, L, K, flush=True)
     monkeypatch.setenv("WM_PERSISTENT", "0")
     cuda = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
     T = 3
@@ -96,24 +95,56 @@ def test_controller_h_part(B, Z, H, A, N, L, K, dtype, monkeypatch):
         mask, dmask, dims = (xm, lm), (cuda(xm), cuda(lm)), dict(Z=Z, H=H, A=A, K=K)
         kw = dict(two_level=(N, L))
     else:
-        wk, inp = _case(B, T, Z, H, A, K, dtype)
+        wk, inp = _case(B, T, Z, H, A, K, "fp32")
         w, z0, mask, dims, kw = inp["weights"], inp["z0"], inp["mask"], wk.dims, {}
         dmask = cuda(mask)
-    m = wmlib.pack(w, Z, H, A, K, dtype, N=N, L=L)
+    m = wmlib.pack(w, Z, H, A, K, "fp32", N=N, L=L)
     rng = np.random.default_rng(B)
     h0 = np.tanh(rng.standard_normal((B, H))).astype(np.float32)
     done0 = (np.arange(B) % 5 == 2).astype(np.uint8)
-    args = dict(T=T, seed=43, tau=1.0, done=True, trace=True, h0=cuda(h0))
-    out = []
-    ac = N + 1 + L if N else A
-    part = (B * ((ac + 2 + 15) // 16 * 16) * 4 + 255) // 256 * 256
-    for less in (0, part):
-        b = wmlib.RolloutBuffers(m, B, T, trace=True)
-        b.ws_bytes -= less
-        wmlib.rollout(m, cuda(z0), dmask, bufs=b, done_io=cuda(done0), **args)
+    wmlib.profile_reset()
+    wmlib.profile_enable("lh")
+    try:
+        b = wmlib.rollout(m, cuda(z0), dmask, T=T, seed=43, tau=1.0, done=True, trace=True, h0=cuda(h0),
+                          done_io=cuda(done0))
         torch.cuda.synchronize()
-        out.append({k: getattr(b, k).cpu().numpy()
-                    for k in ("z_out", "actions", "rewards", "dones", "h_trace", "c_trace")})
-        parity.reanchored(dims, w, mask, out[-1], seed=43, tau=1.0, done_flag=True, dtype=dtype, done0=done0, **kw)
-    same = np.all(out[0]["actions"] == out[1]["actions"], axis=0)
-    assert same.mean() >= 0.97
+        assert wmlib.profile_read("lh")[1] == 1  # step 0's, from h0
+    finally:
+        wmlib.profile_enable(None)
+        wmlib.profile_reset()
+    g = {k: getattr(b, k).cpu().numpy() for k in ("z_out", "actions", "rewards", "dones", "h_trace", "c_trace")}
+    parity.reanchored(dims, w, mask, g, seed=43, tau=1.0, done_flag=True, dtype="fp32", done0=done0, **kw)
+
+
+@pytest.mark.parametrize("B,Z,H,A,h0", [
+    (300, 128, 1024, 400, True),
+    (1300, 128, 4096, 1030, False),  # 65 MB of workspace: what the static scratch just holds
+])
+def test_controller_sums_do_not_follow_the_workspace(B, Z, H, A, h0):
+    """The controller's h part waits in the activation buffers: a call on the
+    static scratch, or in a larger workspace, has the same bits, and wm_rollout
+    refuses a workspace below wm_workspace_bytes."""
+    print("[gpu-tiles] workspace", B, Z, H, A, h0, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(B)
+    shapes = dict(W_g=(4 * H, Z + A + H), b_g=(4 * H,), W_m=(6 * Z, H), b_m=(6 * Z,), w_r=(H,), b_r=(1,), w_d=(H,),
+                  b_d=(1,), W_c=(A, Z + H), b_c=(A,))
+    w = {k: torch.randn(s, generator=g, device="cuda") / H ** 0.5 for k, s in shapes.items()}
+    m = wmlib.pack(w, Z, H, A, 2, "fp32")
+    z0 = torch.randn((B, Z), generator=g, device="cuda")
+    mask = torch.ones((B, A), dtype=torch.uint8, device="cuda")
+    kw = dict(T=2, seed=3, done=False, h0=torch.tanh(torch.randn((B, H), generator=g, device="cuda")) if h0 else None)
+    need = wmlib.workspace_bytes(m.dims, B, 2, wmlib.WS_ROLLOUT)
+    assert need <= 64 << 20
+    big = wmlib.RolloutBuffers(m, B, 2)
+    assert big.ws_bytes == need
+    big.workspace, big.ws_bytes = torch.empty(need + (16 << 20), dtype=torch.uint8, device="cuda"), need + (16 << 20)
+    out = [wmlib.rollout(m, z0, mask, **kw), wmlib.rollout(m, z0, mask, bufs=big, **kw),
+           wmlib.rollout(m, z0, mask, noalloc=True, **kw)]
+    torch.cuda.synchronize()
+    for o in out[1:]:
+        for k in ("actions", "rewards", "z_out", "h_T", "c_T"):
+            assert torch.equal(getattr(o, k), getattr(out[0], k)), k
+    big.ws_bytes = need - 1
+    with pytest.raises(wmlib.WmError) as e:
+        wmlib.rollout(m, z0, mask, bufs=big, **kw)
+    assert e.value.status == wmlib.WM_ERR_WORKSPACE
