@@ -364,6 +364,48 @@ struct GemmD {
         for (int j = 0; j < MBW; ++j) acc[i][j] = tot[i][j] + acc[i][j];
     }
     __syncthreads();  // LDS free for the caller's epilogue
+    if constexpr (SPLIT_) {
+      // An infinity, or a value that rounds to one in bf16, leaves NaN in every
+      // sum it enters (inf - inf in the split's remainder): those sums are
+      // taken again on the fp32 unit, one 16-row block of weights at a time.
+      bool bad = false;
+#pragma unroll
+      for (int i = 0; i < NBW; ++i)
+#pragma unroll
+        for (int j = 0; j < MBW; ++j) bad |= any_nan(acc[i][j]);
+      int* flag = reinterpret_cast<int*>(lds);
+      const uint64_t bal = __ballot(bad);
+      if (lane == 0) flag[wave] = bal != 0;
+      __syncthreads();
+      int any = 0;
+#pragma unroll
+      for (int v = 0; v < NWAVES; ++v) any |= flag[v];
+      __syncthreads();
+      if (!__builtin_amdgcn_readfirstlane(any)) return;
+#pragma unroll
+      for (int ib = 0; ib < NBW; ++ib) {
+        f32x4 c[MBW];
+#pragma unroll
+        for (int j = 0; j < MBW; ++j) c[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int kc = 0; kc < nk; ++kc) {
+          issue(kc);
+          vm_wait<0>();
+          __syncthreads();
+          const char* buf = reinterpret_cast<const char*>(lds) + (kc % STAGES) * STAGE_BYTES;
+#pragma unroll
+          for (int sl = 0; sl < 2; ++sl) {
+            const uint32_t col = sl ? col1 : col0;
+            const uint4 a = *reinterpret_cast<const uint4*>(buf + ((wni * NBW + ib) * 16 + r16) * 128 + col);
+#pragma unroll
+            for (int j = 0; j < MBW; ++j)
+              Mfma<DT>::step(c[j], a, *reinterpret_cast<const uint4*>(buf + (BN + (wmi * MBW + j) * 16 + r16) * 128 + col));
+          }
+          __syncthreads();
+        }
+#pragma unroll
+        for (int j = 0; j < MBW; ++j) acc[ib][j] = nan_to(acc[ib][j], c[j]);
+      }
+    }
   }
 };
 

@@ -88,8 +88,12 @@ __device__ __forceinline__ void mdn_commit(const MdnArgs& p, int m, int j, float
 // KC: the number of mixture components (the call's K), a compile-time
 // constant so that the feature selections of the epilogue fold away
 // ORD: the order of the sum over K (KSum)
+// kMdnWaves: two work-groups per CU where their LDS fits twice, also with the
+// rarely taken second product of a split tile (GemmD)
+template <class C> constexpr int kMdnWaves = 1;
+template <int Q> constexpr int kMdnWaves<GemmD<float, Q, 4, 2, 2, 2, true>> = Q <= 5 ? 2 : 1;
 template <class C, int KC, KSum ORD>
-__global__ void __launch_bounds__(C::NT) k_mdn(const MdnArgs p) {
+__global__ void __launch_bounds__(C::NT, kMdnWaves<C>) k_mdn(const MdnArgs p) {
   using DT = typename C::DT;
   constexpr int K = KC;
   constexpr int Q = C::NBW, MBW = C::MBW, WAVES_N = C::WAVES_N, WAVES_M = C::WAVES_M;

@@ -171,10 +171,39 @@ struct FwdArgs {
   const int32_t* act;        // [B]
   float* c;                  // [B, H], in place
   float* x_out;              // X_{t+1}: fp32 h at columns Z .. of rows of ldx
+  const float *Wg, *x_in;    // row-major: packed gate rows of ldk, X_t = [z_t | h_t] of ldx
+  long ldk;
   int B, H, A, Z, nz, nh;
   long ldx;
   TileMap map;
 };
+
+// The sums of one 16 x 16 tile (units 16 nt .. x rows 16 R ..) over all of K
+// from the row-major operands on the fp32 unit, by one wave, where the split
+// sums came out as NaN: infinities and values that round to one in bf16 do not
+// survive the split (split3).  Rare, so one fragment at a time.
+__device__ __forceinline__ void fwd_fp32(const FwdArgs& p, f32x4 (&s)[4], int nt, int R) {
+  const int lane = threadIdx.x & 63, g = lane >> 4, r16 = lane & 15;
+  const int m = 16 * R + r16, kx = p.Z + p.H;  // a multiple of 4: a piece of four columns is whole
+  const float* x = p.x_in + (long)min(m, p.B - 1) * p.ldx;
+  f32x4 c[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) c[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int k0 = 0; k0 < kx; k0 += Mfma<float>::KSLICE) {
+    const int k = k0 + 4 * g;
+    const bool in = k < kx;
+    uint4 b = *reinterpret_cast<const uint4*>(x + (in ? k : 0));
+    if (!in || m >= p.B) b = make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      uint4 a = *reinterpret_cast<const uint4*>(p.Wg + (long)(4 * (16 * nt + r16) + i) * p.ldk + (in ? k : 0));
+      if (!in) a = make_uint4(0u, 0u, 0u, 0u);
+      Mfma<float>::step(c[i], a, b);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) s[i] = nan_to(s[i], c[i]);
+}
 
 template <int MB>
 __global__ void __launch_bounds__(256, 1) k_recur_fwd(const FwdArgs p) {
@@ -224,7 +253,7 @@ __global__ void __launch_bounds__(256, 1) k_recur_fwd(const FwdArgs p) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) red[wave][j][i][lane] = acc[j][i];
   __syncthreads();
-  if (!ok) return;
+  if (wave >= MB) return;
   // gate i of unit u0 + t of row m is element t of block i
   f32x4 s[4];
 #pragma unroll
@@ -232,13 +261,22 @@ __global__ void __launch_bounds__(256, 1) k_recur_fwd(const FwdArgs p) {
     s[i] = (red[0][wave][i][lane] + red[1][wave][i][lane]) + (red[2][wave][i][lane] + red[3][wave][i][lane]);
   const float cin[4] = {c4.x, c4.y, c4.z, c4.w};
   float cv[4], hv[4];
+  auto cell = [&]() {
 #pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    const float gi = fsigmoid(s[0][t] + (bias[t].x + wa[t].x)), gf = fsigmoid(s[1][t] + (bias[t].y + wa[t].y));
-    const float gg = ftanh(s[2][t] + (bias[t].z + wa[t].z)), go = fsigmoid(s[3][t] + (bias[t].w + wa[t].w));
-    cv[t] = gf * cin[t] + gi * gg;
-    hv[t] = go * ftanh(cv[t]);
+    for (int t = 0; t < 4; ++t) {
+      const float gi = fsigmoid(s[0][t] + (bias[t].x + wa[t].x)), gf = fsigmoid(s[1][t] + (bias[t].y + wa[t].y));
+      const float gg = ftanh(s[2][t] + (bias[t].z + wa[t].z)), go = fsigmoid(s[3][t] + (bias[t].w + wa[t].w));
+      cv[t] = gf * cin[t] + gi * gg;
+      hv[t] = go * ftanh(cv[t]);
+    }
+  };
+  cell();
+  // a NaN in a sum reaches h, and only a NaN does
+  if (__ballot(any_nan(f32x4{hv[0], hv[1], hv[2], hv[3]}))) {
+    fwd_fp32(p, s, nt, mt * MB + wave);
+    cell();
   }
+  if (!ok) return;
   *reinterpret_cast<float4*>(p.c + (long)m * H + u0) = make_float4(cv[0], cv[1], cv[2], cv[3]);
   *reinterpret_cast<float4*>(p.x_out + (long)m * p.ldx + p.Z + u0) = make_float4(hv[0], hv[1], hv[2], hv[3]);
   const float x8[8] = {hv[0], hv[1], hv[2], hv[3], 0.f, 0.f, 0.f, 0.f};
@@ -290,12 +328,15 @@ hipError_t launch_recur_fwd(const Packed& P, const NllBufs& N, hipStream_t s) {
   a.c = N.c;
   a.B = B; a.H = H; a.A = L.A; a.Z = Z; a.nz = nz; a.nh = nh;
   a.ldx = L.ldx;
+  a.Wg = reinterpret_cast<const float*>(base + L.off_Wg);
+  a.ldk = L.ldk;
   const long BX = (long)B * L.ldx;
   for (int t = 0; t < T; ++t) {
     a.zp = zp + t * zb;
     a.hp = hp + (t & 1) * hb;
     a.hp_out = hp + ((t + 1) & 1) * hb;
     a.act = N.actions + (long)t * B;
+    a.x_in = reinterpret_cast<const float*>(N.x) + (long)t * BX;
     a.x_out = reinterpret_cast<float*>(N.x) + (long)(t + 1) * BX;
     // 32-row tiles once they number the CUs, 16-row ones below (launches at
     // B 512, H 512: 16, 32 and 64 rows 14.9, 11.8 and 12.1 us; B 100, H 256:

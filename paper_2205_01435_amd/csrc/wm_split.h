@@ -18,7 +18,9 @@ namespace wm {
 // of the fp32 instruction's time.  Error against 64 bits of a K 512 dot
 // product (uniform operands, fp32 accumulation either way): 3.3e-7 of the
 // result's norm, 4.1e-7 with the fp32 MFMA; K 1056 4.9e-7 and 5.8e-7.
-// Infinities become NaN (inf - inf in the remainder); NaN stays NaN.
+// An infinity, or a finite value above the largest bf16, becomes NaN (inf - inf
+// in the remainder), in every sum that it enters; NaN stays NaN.  The kernels
+// take the sums that came out as NaN again on the fp32 unit (nan_to).
 // ---------------------------------------------------------------------------
 struct Split3 {
   bf16x8 h, m, l;
@@ -43,6 +45,16 @@ __device__ __forceinline__ Split3 split3(uint4 u, uint4 v) {
   const float x[8] = {__uint_as_float(u.x), __uint_as_float(u.y), __uint_as_float(u.z), __uint_as_float(u.w),
                       __uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w)};
   return split3(x);
+}
+
+__device__ __forceinline__ bool any_nan(f32x4 v) {
+  return v[0] != v[0] || v[1] != v[1] || v[2] != v[2] || v[3] != v[3];
+}
+// v with the elements that are NaN from w
+__device__ __forceinline__ f32x4 nan_to(f32x4 v, f32x4 w) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) v[i] = v[i] != v[i] ? w[i] : v[i];
+  return v;
 }
 
 __device__ __forceinline__ f32x4 mfma_bf16(bf16x8 a, bf16x8 b, f32x4 c) {

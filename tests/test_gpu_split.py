@@ -83,3 +83,33 @@ def test_recurrence_per_step(B, T, Z, H, A):
     if T * B <= 2000:
         d["lengths"] = None
         _check(w, d, f"per-step B {B} H {H}")
+
+
+@pytest.mark.parametrize("B,T,Z,H,K", [
+    (300, 6, 24, 272, 2),    # 16-row tiles of the recurrence
+    (530, 3, 136, 528, 3),   # 32-row tiles, several slices per wave
+    (512, 9, 64, 512, 5),    # a batch that the persistent kernel also serves
+])
+def test_infinities_as_fp32_products(B, T, Z, H, K):
+    """Split products multiply infinities, and values that round to one in
+    bf16, as fp32 products do: a latent saturates the gates of its row and the
+    later steps stay finite; a weight moves its own logit."""
+    w = wl.Workload("i", "nll", B=B, T=T, Z=Z, H=H, A=5, K=K, dtype="fp32", seed=70 + K)
+    d = wl.make_nll_inputs(w)
+    d["z"][0, 3, 1], d["z"][0, B - 1, Z - 1] = np.inf, -np.inf
+    d["z"][1, 20, 0], d["z"][0, 33, Z // 2] = 3.4e38, -3.4e38  # above the largest bf16
+    d["z"][0, 40, 2] = np.nan
+    # a mixture weight whose logit (3.4e38 h) swamps the others of its dim
+    d["weights"]["W_m"][0, 7] = 3.4e38
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    m = wmlib.pack(d["weights"], Z, H, 5, K, "fp32")
+    b = wmlib.nll(m, t(d["z"]), t(d["actions"]), t(d["rewards"]), t(d["dones"]))
+    torch.cuda.synchronize()
+    with np.errstate(all="ignore"):
+        ref = owm.nll(d["weights"], w.dims, d["z"], d["actions"], d["rewards"], d["dones"], dtype="fp32")
+    for k in ("loglik", "reward_se", "done_bce"):
+        got, want = getattr(b, k).cpu().numpy(), ref[k]
+        ok = np.isfinite(want) & (np.abs(want) < 1e30)
+        assert ok[:, [3, B - 1, 33]].any() and not ok[:, 40].any(), k
+        np.testing.assert_array_equal(np.isfinite(got) & (np.abs(got) < 1e30), ok, err_msg=k)
+        parity.close(got[ok], want[ok], parity.RTOL["fp32"], k)
