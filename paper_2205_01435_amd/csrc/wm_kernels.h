@@ -111,6 +111,7 @@ hipError_t launch_nll_persist(const Packed& P, const NllBufs& N, hipStream_t s);
 
 // The fp32 recurrence of the likelihood pass, one launch per step
 // (wm_recur.hip): the bytes of its operand planes, and the launches.
+size_t recur_weight_bytes(const Layout& L);  // of the weights' planes alone
 size_t recur_fwd_bytes(const Layout& L, int B, int T);
 hipError_t launch_recur_fwd(const Packed& P, const NllBufs& N, hipStream_t s);
 

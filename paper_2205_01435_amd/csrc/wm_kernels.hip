@@ -934,17 +934,31 @@ hipError_t rollout_impl(const Packed& P, const RolloutBufs& R, hipStream_t s) {
 }
 
 // Which fp32 recurrences run one launch per step on split products
-// (wm_recur.hip): those the persistent kernel does not serve, and of those it
-// does, the batches whose rows per XCD (above 32) make its fp32 MFMAs the
-// longer part, over enough steps to pay for splitting the weights (15 us, four
-// steps' gain).  Whole likelihood passes, T 32, Z 64, K 1, persistent and per
-// step, us:
+// (wm_recur.hip).  Splitting the operands costs three launches, 6 to 15 us of a
+// call (25 at H 2048), so it takes steps to pay for it.
+// Against one fp32 gate launch per step, us a step, gates and split, and the T
+// from which a whole pass is the shorter (-: never), Z 16 to 64:
+//   B            16              150             600            1500             4096
+//   H 128    4.8,  4.6  26   5.0,  4.8  47   7.3,  6.6  11   8.1,  8.8  -   13.2, 13.1  -
+//   H 256    5.9,  5.1   9   8.5,  5.8   3  11.2,  9.9   6  17.2, 16.1  7   34.5, 32.3  4
+//   H 512    6.9,  6.0  13    14,   10   5    25,   20   2    45,   37  1    105,   94  1
+//   H 1024    19,    8   2    27,   19   2    61,   45   1   125,  107  1    320,  280  1
+//   H 2048    34,   17   2    67,   52   3   194,  168   2   413,  407  6   1073,  998  7
+//   H 4096    82,   70  16   209,  345   -   655, 1340   -  1546, 3339  -   4089, 9136  -
+// Where a step is short on both sides (small H and few rows) its gain is small.
+// At H 4096 the weights' planes (411 MB) no longer fit the 256 MB last-level
+// cache; the line is drawn at half of it.
+// Of the batches that the persistent kernel serves, those whose rows per XCD
+// (above 32) make its fp32 MFMAs the longer part.  Whole likelihood passes, T 32,
+// Z 64, K 1, persistent and per step, us:
 //   B             128        200        256        384        512
 //   H 256     144, 197   197, 210   203, 206   326, 262   337, 254
 //   H 512     211, 254   310, 344   319, 309   587, 443   531, 471
 // While the persistent kernels' phases are being timed they serve all they can.
 bool recur_serves(const Layout& L, int B, int T) {
-  return !persist_usable(L, B, true) || (B > 256 && T >= 8 && !phases_timed());
+  if (persist_usable(L, B, true)) return B > 256 && T >= 8 && !phases_timed();
+  if (recur_weight_bytes(L) > ((size_t)128 << 20) || (L.H < 192 && B > 1024)) return false;
+  return T >= (L.H >= 768 ? 4 : (long)B * L.H <= 32768 ? 16 : 8);
 }
 
 // heads = false: the recurrence only (X_1 .. X_T), for the training gradient

@@ -16,6 +16,8 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "wm_device.h"
 #include "wm_gemm.h"
 #include "wm_kernels.h"
@@ -288,15 +290,21 @@ __global__ void __launch_bounds__(256, 1) k_recur_fwd(const FwdArgs p) {
 
 template <int MB>
 hipError_t launch_fwd(FwdArgs a, hipStream_t s) {
-  a.map = tile_map(a.H / 16, (a.B + 16 * MB - 1) / (16 * MB), (size_t)(a.H / 4) * (a.nz + a.nh) * kFrag);
+  // Weights too large for the L2s even in eighths are still split eight ways:
+  // an XCD that walked all of them would read them once per row tile (B 1000,
+  // H 1024: 135 us a step so, 74 with an eighth each; fp32 gate launches 86)
+  const size_t wbytes = (size_t)(a.H / 4) * (a.nz + a.nh) * kFrag;
+  a.map = tile_map(a.H / 16, (a.B + 16 * MB - 1) / (16 * MB), std::min(wbytes, 8 * kL2Budget));
   return launch("nll_step", k_recur_fwd<MB>, dim3(grid_of(a.map)), dim3(256), 0, s, a);
 }
 
 }  // namespace
 
+size_t recur_weight_bytes(const Layout& L) { return (size_t)(L.H / 4) * (slices(L.Z) + slices(L.H)) * kFrag; }
+
 size_t recur_fwd_bytes(const Layout& L, int B, int T) {
   const int nz = slices(L.Z), nh = slices(L.H);
-  return wm_align256((size_t)(L.H / 4) * (nz + nh) * kFrag) + wm_align256((size_t)T * blocks(B) * nz * kFrag) +
+  return wm_align256(recur_weight_bytes(L)) + wm_align256((size_t)T * blocks(B) * nz * kFrag) +
          wm_align256((size_t)2 * blocks(B) * nh * kFrag);
 }
 

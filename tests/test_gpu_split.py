@@ -52,10 +52,11 @@ def test_nll_large_tiles(K):
 
 
 @pytest.mark.parametrize("B,T,Z,H,A", [
-    (37, 3, 40, 48, 5),     # 16-row tiles; H and Z end inside a slice of 32 columns
-    (1, 2, 8, 16, 1),       # the smallest of everything
-    (300, 4, 24, 272, 7),   # 16-row tiles, the last row block short
-    (530, 3, 136, 528, 9),  # 32-row tiles; five slices of z
+    (37, 16, 40, 48, 5),    # 16-row tiles; H and Z end inside a slice of 32 columns
+    (1, 16, 8, 16, 1),      # the smallest of everything
+    (300, 8, 24, 272, 7),   # 16-row tiles, the last row block short
+    (530, 8, 136, 528, 9),  # 32-row tiles; five slices of z
+    (90, 4, 72, 1040, 2),   # weights that do not fit the L2s in eighths
     (512, 9, 64, 512, 64),  # a batch that the persistent kernel also serves
 ])
 def test_recurrence_per_step(B, T, Z, H, A):
@@ -80,14 +81,41 @@ def test_recurrence_per_step(B, T, Z, H, A):
     ref = owm.nll(d["weights"], w.dims, d["z"], a, d["rewards"], d["dones"], dtype="fp32")
     for k in ("loglik", "reward_se", "done_bce", "means"):
         parity.close(getattr(b, k).cpu().numpy(), ref[k], parity.RTOL["fp32"], k)
-    if T * B <= 2000:
+    if T * B <= 4500:
         d["lengths"] = None
         _check(w, d, f"per-step B {B} H {H}")
 
 
+@pytest.mark.parametrize("B,T,Z,H,steps", [
+    (37, 15, 40, 48, 0), (37, 16, 40, 48, 16),        # few rows, small H
+    (300, 7, 24, 272, 0), (300, 8, 24, 272, 8),
+    (43, 3, 16, 768, 0), (43, 4, 16, 768, 4),         # large H
+    (1030, 17, 8, 176, 0), (1030, 8, 8, 208, 8),      # many rows, small H
+    (512, 7, 64, 512, 0),                             # the persistent kernel
+])
+def test_recurrence_route(B, T, Z, H, steps):
+    """Few steps do not pay for splitting the operands: fp32 gate launches."""
+    w = wl.Workload("q", "nll", B=B, T=T, Z=Z, H=H, A=6, K=1, dtype="fp32", seed=80 + T)
+    d = wl.make_nll_inputs(w)
+    t = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()  # noqa: E731
+    m = wmlib.pack(d["weights"], Z, H, 6, 1, "fp32")
+    wmlib.profile_reset()
+    wmlib.profile_enable("nll_step")
+    try:
+        b = wmlib.nll(m, t(d["z"]), t(d["actions"]), t(d["rewards"]), t(d["dones"]))
+        torch.cuda.synchronize()
+        assert wmlib.profile_read("nll_step")[1] == steps
+    finally:
+        wmlib.profile_enable(None)
+        wmlib.profile_reset()
+    ref = owm.nll(d["weights"], w.dims, d["z"], d["actions"], d["rewards"], d["dones"], dtype="fp32")
+    for k in ("loglik", "reward_se", "done_bce", "means"):
+        parity.close(getattr(b, k).cpu().numpy(), ref[k], parity.RTOL["fp32"], k)
+
+
 @pytest.mark.parametrize("B,T,Z,H,K", [
-    (300, 6, 24, 272, 2),    # 16-row tiles of the recurrence
-    (530, 3, 136, 528, 3),   # 32-row tiles, several slices per wave
+    (300, 8, 24, 272, 2),    # 16-row tiles of the recurrence
+    (530, 8, 136, 528, 3),   # 32-row tiles, several slices per wave
     (512, 9, 64, 512, 5),    # a batch that the persistent kernel also serves
 ])
 def test_infinities_as_fp32_products(B, T, Z, H, K):
