@@ -191,7 +191,7 @@ size_t wm_workspace_bytes(const wm_dims* dims, int32_t B, int32_t T, int32_t whi
   if (which == 1) return wm::nll_workspace(L, B, T, nullptr, nullptr);
   if (which == 2) return 0;  // wm_controller_step takes no workspace
   if (which == 3)
-    return wm::wm_align256(wm::nll_workspace(L, B, T, nullptr, nullptr)) +
+    return wm::wm_align256(wm::nll_workspace(L, B, T, nullptr, nullptr, false)) +
            wm::grad_workspace(L, B, T, nullptr, nullptr);
   return 0;
 }
@@ -325,7 +325,7 @@ wm_status wm_nll_grad(const wm_dims* dims, const void* packed, int32_t B, int32_
   if (!aligned16(z)) return fail(WM_ERR_INVALID_ARG, "z must be 16-byte aligned");
   if ((int64_t)B * T > (int64_t)1 << 22) return fail(WM_ERR_UNSUPPORTED, "T*B above 2^22");
   if (T == 0) return ok();
-  const size_t nb = wm::wm_align256(wm::nll_workspace(L, B, T, nullptr, nullptr));
+  const size_t nb = wm::wm_align256(wm::nll_workspace(L, B, T, nullptr, nullptr, false));
   const size_t need = nb + wm::grad_workspace(L, B, T, nullptr, nullptr);
   if (!workspace || workspace_bytes < need)
     return fail(WM_ERR_WORKSPACE, "nll_grad workspace needs %zu bytes, got %zu", need, workspace_bytes);
@@ -341,7 +341,7 @@ wm_status wm_nll_grad(const wm_dims* dims, const void* packed, int32_t B, int32_
   wm::NllBufs N{};
   N.B = B; N.T = T; N.z = z; N.actions = actions; N.rewards = rewards; N.dones = dones;
   N.lengths = lengths;
-  wm::nll_workspace(L, B, T, ws, &N);
+  wm::nll_workspace(L, B, T, ws, &N, false);
   N.preset_err = (flags & WM_FLAG_TEST_ABORT) ? 1u : 0u;
   wm::GradWs G{};
   wm::grad_workspace(L, B, T, ws + nb, &G);

@@ -61,7 +61,7 @@ struct NllBufs {
   // c_{t+1} at [t+1] of [T+1, B, H]
   float* g_trace;
   float* c_trace;
-  void* planes;  // operand planes of the per-step recurrence (fp32; recur_fwd_bytes)
+  void* planes;  // operand planes of the split recurrence (recur_fwd_bytes), or null: it does not run
 };
 
 // Barrier and status words (zeroed by the init kernels) at offset 0 of the
@@ -75,7 +75,9 @@ constexpr int kSyncViol = 64 * 16 + 1;
 // Workspace sizes; with a non-null `ws` the workspace pointers of the
 // buffer struct are also set (ws must be 256-byte aligned).
 size_t rollout_workspace(const Layout& L, int B, char* ws, RolloutBufs* R);
-size_t nll_workspace(const Layout& L, int B, int T, char* ws, NllBufs* N);
+// with_planes = false: a pass whose recurrence never runs on split products (the
+// training gradient's).
+size_t nll_workspace(const Layout& L, int B, int T, char* ws, NllBufs* N, bool with_planes = true);
 
 hipError_t launch_pack(const Packed& P, void* packed, const float* W_g, const float* b_g,
                        const float* W_m, const float* b_m, const float* w_r, const float* b_r,
@@ -105,6 +107,9 @@ hipError_t launch_nll_recurrence(const Packed& P, const NllBufs& N, hipStream_t 
 // The launchers return hipErrorNotSupported when the dims, the batch or the
 // device are outside what they serve (or WM_PERSISTENT=0 is set).
 size_t persist_partial_bytes(const Layout& L, int B);  // 0 if not served
+// persist_plan: whether the dims and the batch are ones they serve at all;
+// persist_usable: ... and they are switched on and fit this device.
+bool persist_plan(const Layout& L, int B, bool nll);
 bool persist_usable(const Layout& L, int B, bool nll);
 hipError_t launch_rollout_persist(const Packed& P, const RolloutBufs& R, hipStream_t s);
 hipError_t launch_nll_persist(const Packed& P, const NllBufs& N, hipStream_t s);

@@ -954,11 +954,20 @@ hipError_t rollout_impl(const Packed& P, const RolloutBufs& R, hipStream_t s) {
 //   B             128        200        256        384        512
 //   H 256     144, 197   197, 210   203, 206   326, 262   337, 254
 //   H 512     211, 254   310, 344   319, 309   587, 443   531, 471
-// While the persistent kernels' phases are being timed they serve all they can.
 bool recur_serves(const Layout& L, int B, int T) {
-  if (persist_usable(L, B, true)) return B > 256 && T >= 8 && !phases_timed();
+  if (L.dt != 0) return false;
+  if (persist_plan(L, B, true)) return B > 256 && T >= 8;
   if (recur_weight_bytes(L) > ((size_t)128 << 20) || (L.H < 192 && B > 1024)) return false;
   return T >= (L.H >= 768 ? 4 : (long)B * L.H <= 32768 ? 16 : 8);
+}
+
+// The planes a call brings in its workspace, and no call that does not need
+// them: the size follows from the call's dims, B and T alone (not from the
+// device or a switch), and does not shrink as B or T grows, so that the
+// workspace of a larger call serves a smaller one.
+size_t recur_plane_bytes(const Layout& L, int B, int T) {
+  if (L.H < 192) B = std::min(B, 1024);
+  return recur_serves(L, B, T) ? recur_fwd_bytes(L, B, T) : 0;
 }
 
 // heads = false: the recurrence only (X_1 .. X_T), for the training gradient
@@ -986,10 +995,12 @@ hipError_t nll_impl(const Packed& P, const NllBufs& N, hipStream_t s, bool heads
   // per step, in fp32 on split products (recur_serves).  The training
   // gradient's (heads = false) keeps to the fp32 products: Adam's first step
   // divides by |g| + 1e-8, and where a gradient is that small another rounding
-  // of the sums moves the parameter by up to the whole step.
-  e = hipErrorNotSupported;
-  if (sizeof(DT) == 2 || !heads || !recur_serves(L, B, T)) e = launch_nll_persist(P, N, s);
-  else e = launch_recur_fwd(P, N, s);
+  // of the sums moves the parameter by up to the whole step.  While the
+  // persistent kernels' phases are being timed they serve all they can.
+  if (heads && N.planes && recur_serves(L, B, T) && !(phases_timed() && persist_usable(L, B, true)))
+    e = launch_recur_fwd(P, N, s);
+  else
+    e = launch_nll_persist(P, N, s);
   if (e != hipSuccess && e != hipErrorNotSupported) return e;
   for (int t = 0; e == hipErrorNotSupported && t < T; ++t) {
     ga.x_in = X + (long)t * BX;
@@ -1053,7 +1064,7 @@ size_t rollout_workspace(const Layout& L, int B, char* ws, RolloutBufs* R) {
   return o;
 }
 
-size_t nll_workspace(const Layout& L, int B, int T, char* ws, NllBufs* N) {
+size_t nll_workspace(const Layout& L, int B, int T, char* ws, NllBufs* N, bool with_planes) {
   const size_t M = (size_t)T * B;
   size_t o = 0;
   const size_t os = o;
@@ -1069,7 +1080,8 @@ size_t nll_workspace(const Layout& L, int B, int T, char* ws, NllBufs* N) {
   const size_t og = o;
   o = wm_align256(o + ((M + 255) / 256) * 4 * 4);  // block sums
   const size_t opl = o;
-  if (L.dt == 0) o = wm_align256(o + recur_fwd_bytes(L, B, T));  // operand planes of the recurrence
+  const size_t pb = with_planes ? recur_plane_bytes(L, B, T) : 0;
+  o = wm_align256(o + pb);  // operand planes of the split recurrence
   if (ws && N) {
     N->sync = reinterpret_cast<unsigned*>(ws + os);
     N->x = ws + ox;
@@ -1077,7 +1089,7 @@ size_t nll_workspace(const Layout& L, int B, int T, char* ws, NllBufs* N) {
     N->part = reinterpret_cast<float*>(ws + op);
     N->head = reinterpret_cast<float*>(ws + oh);
     N->wgsum = reinterpret_cast<float*>(ws + og);
-    N->planes = ws + opl;
+    N->planes = pb ? ws + opl : nullptr;
   }
   return o;
 }

@@ -1303,6 +1303,11 @@ size_t persist_partial_bytes(const Layout& L, int B) {
   return (size_t)B * L.Nc * 4 + (size_t)B * 4;  // Lh, then the row flags
 }
 
+bool persist_plan(const Layout& L, int B, bool nll) {
+  PPlan pl;
+  return plan(L, B, nll, pl);
+}
+
 bool persist_usable(const Layout& L, int B, bool nll) {
   PPlan pl;
   return persist_enabled() && plan(L, B, nll, pl) && device_fits();

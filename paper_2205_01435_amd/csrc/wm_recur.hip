@@ -300,11 +300,16 @@ hipError_t launch_fwd(FwdArgs a, hipStream_t s) {
 
 }  // namespace
 
+// The z planes of this many steps at a time: few enough that a long pass does
+// not hold planes by its length (6 bytes per value, rows in sixteens), enough
+// that their launch is lost in the steps.
+constexpr int kPlaneSteps = 256;
+
 size_t recur_weight_bytes(const Layout& L) { return (size_t)(L.H / 4) * (slices(L.Z) + slices(L.H)) * kFrag; }
 
 size_t recur_fwd_bytes(const Layout& L, int B, int T) {
   const int nz = slices(L.Z), nh = slices(L.H);
-  return wm_align256(recur_weight_bytes(L)) + wm_align256((size_t)T * blocks(B) * nz * kFrag) +
+  return wm_align256(recur_weight_bytes(L)) + wm_align256((size_t)std::min(T, kPlaneSteps) * blocks(B) * nz * kFrag) +
          wm_align256((size_t)2 * blocks(B) * nh * kFrag);
 }
 
@@ -314,18 +319,12 @@ hipError_t launch_recur_fwd(const Packed& P, const NllBufs& N, hipStream_t s) {
   const int B = N.B, T = N.T, Z = L.Z, H = L.H, nz = slices(Z), nh = slices(H), rbs = blocks(B);
   char* Wp = reinterpret_cast<char*>(N.planes);
   char* zp = Wp + wm_align256((size_t)(H / 4) * (nz + nh) * kFrag);
-  char* hp = zp + wm_align256((size_t)T * rbs * nz * kFrag);
+  char* hp = zp + wm_align256((size_t)std::min(T, kPlaneSteps) * rbs * nz * kFrag);
   const long hb = (long)rbs * nh * kFrag, zb = (long)rbs * nz * kFrag;
   auto grid = [](long n) { return (unsigned)((n + 255) / 256); };
   hipError_t e = launch("nll_planes", k_planes_gates, dim3(grid((long)(H / 4) * (nz + nh) * 64)), dim3(256), 0, s,
                         reinterpret_cast<const float*>(base + L.off_Wg), (long)L.ldk, Z, H, nz, nh, Wp);
   if (e != hipSuccess) return e;
-  for (int t0 = 0; t0 < T; t0 += 32768) {  // grid rows are limited to 65535
-    const int n = T - t0 < 32768 ? T - t0 : 32768;
-    e = launch("nll_planes", k_planes_rows, dim3(grid((long)rbs * nz * 64), (unsigned)n), dim3(256), 0, s,
-               N.z + (long)t0 * B * Z, (long)Z, B, Z, rbs, nz, (long)B * Z, zb, zp + t0 * zb);
-    if (e != hipSuccess) return e;
-  }
   e = launch("nll_planes", k_planes_zero, dim3(grid(2 * hb / 16)), dim3(256), 0, s, reinterpret_cast<uint4*>(hp),
              2 * hb / 16);
   if (e != hipSuccess) return e;
@@ -340,7 +339,12 @@ hipError_t launch_recur_fwd(const Packed& P, const NllBufs& N, hipStream_t s) {
   a.ldk = L.ldk;
   const long BX = (long)B * L.ldx;
   for (int t = 0; t < T; ++t) {
-    a.zp = zp + t * zb;
+    if (t % kPlaneSteps == 0) {
+      e = launch("nll_planes", k_planes_rows, dim3(grid((long)rbs * nz * 64), (unsigned)std::min(T - t, kPlaneSteps)),
+                 dim3(256), 0, s, N.z + (long)t * B * Z, (long)Z, B, Z, rbs, nz, (long)B * Z, zb, zp);
+      if (e != hipSuccess) return e;
+    }
+    a.zp = zp + t % kPlaneSteps * zb;
     a.hp = hp + (t & 1) * hb;
     a.hp_out = hp + ((t + 1) & 1) * hb;
     a.act = N.actions + (long)t * B;

@@ -170,6 +170,41 @@ def test_nll_grad_workspace_size():
     assert wmlib.workspace_bytes(wmlib.make_dims(64, 512, 64, 5, "bf16"), 512, 128, wmlib.WS_NLL_GRAD) > 0
 
 
+def test_nll_workspace_holds_planes_only_where_they_are_used():
+    """The operand planes of the split recurrence (6 bytes per value, rows in
+    sixteens) are asked for where it runs: not in a pass that the persistent
+    kernel serves, nor in one of few steps, nor in the training gradient's."""
+    def size(which, Z, H, K, B, T, A=8):
+        return wmlib.workspace_bytes(wmlib.make_dims(Z, H, A, K), B, T, which)
+
+    # one long sequence, on the persistent kernel and on the split: X and small
+    # sums, not 13 GB of planes
+    T = 1 << 20
+    assert size(wmlib.WS_NLL, 64, 512, 5, 1, T) < 4 * (T + 1) * (64 + 512 + 64)
+    assert size(wmlib.WS_NLL, 128, 512, 5, 1, T) < 4 * (T + 1) * (128 + 512 + 64)
+    # few rows: planes from 16 steps on, 512 x 1024 x 6 bytes of z alone
+    B, Z, H = 32, 1024, 16
+    row = 6 * B * Z
+    grow = [size(wmlib.WS_NLL, Z, H, 1, B, t) - size(wmlib.WS_NLL, Z, H, 1, B, t - 1) for t in (15, 16, 17)]
+    assert grow[0] < row and grow[1] > 16 * row and row < grow[2] < 3 * row
+    # ... and none of them in the gradient's workspace at any length
+    g = [size(wmlib.WS_NLL_GRAD, Z, H, 1, B, t) for t in (14, 15, 16)]
+    assert abs((g[2] - g[1]) - (g[1] - g[0])) < 1 << 16
+    assert g[2] < 25e6  # 26.5e6 with the planes
+
+
+def test_nll_workspace_of_a_larger_call_serves_a_smaller_one():
+    Bs, Ts = (1, 16, 200, 256, 257, 512, 513, 1024, 1025, 1500, 4096), (1, 3, 4, 7, 8, 15, 16, 40)
+    for Z, H, K in ((16, 128, 2), (64, 176, 1), (64, 256, 5), (64, 512, 5), (40, 368, 3), (64, 1024, 8), (64, 4096, 1)):
+        for dtype in ("fp32", "bf16"):
+            d = wmlib.make_dims(Z, H, 32, K, dtype)
+            n = [[wmlib.workspace_bytes(d, B, T, wmlib.WS_NLL) for T in Ts] for B in Bs]
+            for i in range(len(Bs)):
+                for j in range(len(Ts)):
+                    assert i == 0 or n[i][j] >= n[i - 1][j], (Z, H, Bs[i], Ts[j])
+                    assert j == 0 or n[i][j] >= n[i][j - 1], (Z, H, Bs[i], Ts[j])
+
+
 def test_missing_library_fails_loudly(tmp_path):
     saved = wmlib._lib
     try:

@@ -57,6 +57,7 @@ def test_nll_large_tiles(K):
     (300, 8, 24, 272, 7),   # 16-row tiles, the last row block short
     (530, 8, 136, 528, 9),  # 32-row tiles; five slices of z
     (90, 4, 72, 1040, 2),   # weights that do not fit the L2s in eighths
+    (3, 515, 40, 48, 2),    # planes of z in three rounds of steps
     (512, 9, 64, 512, 64),  # a batch that the persistent kernel also serves
 ])
 def test_recurrence_per_step(B, T, Z, H, A):
