@@ -299,12 +299,13 @@ __global__ void __launch_bounds__(256) k_ctrl_rows(const CtrlArgs p) {
     mxl = fmaxf(mxl, __shfl_xor(mxl, off));
   }
   float sx = 0.f, sl = 0.f;
+  // (a logit of -inf has no probability, also where all of a row's are)
   each(xb, [&](int k, int v) {
-    lx.v[k][v] = (mx >> (4 * k + v)) & 1u ? expf(lx.v[k][v] - mxx) : 0.f;
+    lx.v[k][v] = (mx >> (4 * k + v)) & 1u && lx.v[k][v] != -INFINITY ? expf(lx.v[k][v] - mxx) : 0.f;
     sx += lx.v[k][v];
   });
   each(lb, [&](int k, int v) {
-    ll.v[k][v] = (ml >> (4 * k + v)) & 1u ? expf(ll.v[k][v] - mxl) : 0.f;
+    ll.v[k][v] = (ml >> (4 * k + v)) & 1u && ll.v[k][v] != -INFINITY ? expf(ll.v[k][v] - mxl) : 0.f;
     sl += ll.v[k][v];
   });
 #pragma unroll

@@ -155,3 +155,32 @@ def test_two_level_controller_step(B, Z, H, N, L, dtype):
     assert a[B // 4] == -2 and np.all(p[B // 4, N + 1:] == 0)
     ok = a >= 0
     assert np.all(xm[ok, a[ok] // L] == 1) and np.all(lm[ok, a[ok] // L, a[ok] % L] == 1)
+
+
+@pytest.mark.parametrize("N,L,dtype", [(4, 20, "fp32"), (288, 200, "bf16"), (600, 300, "fp32")])
+def test_two_level_logits_of_minus_infinity(N, L, dtype):
+    """Transformations and locations switched off by a bias of -inf are never
+    picked and have probability 0, also on rows where nothing else is valid."""
+    say("two-level -inf", N, L, dtype)
+    B, Z, H = 20, 16, 128
+    w, z0, xm, lm = _inputs(B, 2, Z, H, N, L, 2, seed=N)
+    off, loc = [1, N - 1], [0, 7]
+    w["b_c"][off] = -np.inf
+    w["b_c"][[N + 1 + i for i in loc]] = -np.inf
+    xm[3] = 0
+    xm[3, off] = 1  # nothing left to pick
+    xm[5] = 0
+    xm[5, 2] = 1
+    lm[5, 2] = 0
+    lm[5, 2, loc] = 1  # ... at the location
+    h = np.zeros((B, H), np.float32)
+    m = wmlib.pack(w, Z, H, N * L, 2, dtype, N=N, L=L)
+    probs, action = wmlib.controller_step(m, _t(z0), _t(h), (_t(xm), _t(lm)), seed=5, step=1)
+    torch.cuda.synchronize()
+    p, a = probs.cpu().numpy(), action.cpu().numpy()
+    assert np.all(np.isfinite(p)) and np.all(p[:, off] == 0) and np.all(p[:, [N + 1 + i for i in loc]] == 0)
+    assert a[3] == -1 and np.all(p[3] == 0)
+    assert a[5] == -1 and p[5, 2] == 1 and np.all(p[5, N + 1:] == 0)
+    live = a >= 0
+    assert live.any() and not np.isin(a[live] // L, off).any() and not np.isin(a[live] % L, loc).any()
+    np.testing.assert_allclose(p[live].sum(1), 2.0, rtol=1e-5)
