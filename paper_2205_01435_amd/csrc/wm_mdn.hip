@@ -435,11 +435,25 @@ hipError_t launch_mdn(const MdnArgs& a, int Q, int ntiles, hipStream_t s) {
   return launch_mdn_k<DT>("mdn", a, Q, ntiles, s);
 }
 
+// The comparison is of times at H 512, where mdn_cost's fp32 figures were
+// taken; all of them grow with H alike.  What the controller saves, in these
+// units: about 6 us (10 from H 1024 on) up to 80 logits, 0.08 us a logit beyond.
+// Whole rollout steps, whole product and h part beside the mixture, us:
+//   rows                   64           300          1000          2000          4000
+//   H 128, A 32          16,  15                                 20,  18   (8000) 34,  36
+//   H 256, A 32          20,  18       24,  21       28,  25     35,  35       50,  53
+//   H 368, A 50          24,  19       29,  24       40,  34     59,  53       82,  76
+//   H 512, A 64          28,  23       43,  37       54,  54     82,  85      130, 139
+//   H 512, A 300         53,  29       67,  43       78,  61    104,  92
+//   H 1024, A 64         77,  57       93,  73      136, 139    225, 223      374, 428
+//   H 1024, A 600       259,  73      272,  90      316, 156
+//   H 2048, A 64        125,  84      188, 147      355, 340
+//   H 2048, A 400       336,  95      396, 158      569, 350
 bool ctrl_h_wanted(const Layout& L, int B) {
   if (L.dt == 1 || L.Z + L.ldh > L.ldk || L.Nc > L.Kx) return false;
   if (L.N > 0 && L.Nc / 16 > 20) return false;
   const float with = mdn_cost(L.dt == 1, L.Q, B, L.Z / 8 + (L.Nc + 32 * L.Q - 1) / (32 * L.Q)).best();
-  return with <= mdn_cost(L.dt == 1, L.Q, B, L.Z / 8).best() + 5.0f;
+  return with <= mdn_cost(L.dt == 1, L.Q, B, L.Z / 8).best() + std::max(L.H >= 1024 ? 10.0f : 6.0f, 0.08f * (float)L.Nc);
 }
 
 hipError_t launch_ctrl_h(MdnArgs a, int Q, hipStream_t s) {

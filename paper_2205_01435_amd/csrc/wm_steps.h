@@ -119,9 +119,8 @@ hipError_t launch_ctrl(const CtrlArgs& a, hipStream_t s);
 // rollout's sums keep one order, KSum), the matrix rows of W_c need to be
 // readable Z + ldh wide, the logits to fit the z and h columns of an activation
 // row (where they wait for the next step), the two-level controller's to fit
-// k_ctrl_z's staged rows, and the extra tiles to cost the mixture launch less than the deeper product costs the controller
-// (about 6 us; at B 4096, where they would start a second round of tiles, they
-// cost 10).
+// k_ctrl_z's staged rows, and the extra tiles to cost the mixture launch less
+// than the deeper product costs the controller.
 bool ctrl_h_wanted(const Layout& L, int B);
 // The controller's h part alone (MdnArgs::lh, zt = 0), and the rollout's
 // decision from it.
