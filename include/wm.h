@@ -348,7 +348,8 @@ float wm_poly_lr(int32_t epoch, float lr0, float lr_end, int32_t epochs);
 /*
  * Measurement aid (no counterpart in the paper).  While a prefix is set, every
  * kernel launch of the library whose name starts with it is bracketed by HIP
- * events on its stream.  Kernel names: "ctrl", "gates", "mdn", "init",
+ * events on its stream.  Kernel names: "ctrl", "gates", "mdn" (each followed by
+ * "/" and the tile that the call's sizes picked, as "gates/64x32"), "lh", "init",
  * "finish", "nll_init", "nll_reduce", "nll_means", "pack", "returns", "adam", and the
  * "grad_" kernels of wm_nll_grad; "" selects all,
  * NULL turns timing off.  wm_profile_read waits for the recorded events and

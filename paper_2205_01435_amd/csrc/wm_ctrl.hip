@@ -1043,13 +1043,16 @@ constexpr long kXLTiles = 256;
 constexpr int kRdCtrlRows = 1024;
 template <class C, class S>
 hipError_t launch_ctrl_cfg(const CtrlArgs& a, hipStream_t s) {
-  return launch("ctrl", k_ctrl<C, S>, dim3((a.M + C::BM - 1) / C::BM), dim3(C::NT), 0, s, a);
+  static const char* const names[2][5] = {{"ctrl/32x64", "ctrl/32x128", "ctrl/32x192", "", "ctrl/32x320"},
+                                          {"ctrl/64x64", "ctrl/64x128", "ctrl/64x192", "", "ctrl/64x320"}};
+  static_assert(C::BM == 32 || C::BM == 64, "named tiles");
+  return launch(names[C::BM / 64][C::BN / 64 - 1], k_ctrl<C, S>, dim3((a.M + C::BM - 1) / C::BM), dim3(C::NT), 0, s, a);
 }
 
 template <class S, int NBW, int MBW>
 hipError_t launch_ctrl_wide(const CtrlArgs& a, hipStream_t s) {
   constexpr int BM = 16 * MBW;
-  return launch("ctrl", k_ctrl_wide<S, NBW, MBW, Cfgs<typename S::DT>::WIDE_BKC>,
+  return launch("ctrl/wide", k_ctrl_wide<S, NBW, MBW, Cfgs<typename S::DT>::WIDE_BKC>,
                 dim3((a.M + BM - 1) / BM), dim3(256), 0, s, a);
 }
 
@@ -1058,14 +1061,14 @@ hipError_t launch_ctrl_rd(const CtrlArgs& a, int nw, hipStream_t s) {
   const size_t lds = R::lds_bytes(nw);
   hipError_t e = allow_lds(k_ctrl_rd<R, S>, lds);
   if (e != hipSuccess) return e;
-  return launch("ctrl", k_ctrl_rd<R, S>, dim3((a.M + R::BM - 1) / R::BM), dim3(64 * nw), lds, s, a);
+  return launch("ctrl/rd", k_ctrl_rd<R, S>, dim3((a.M + R::BM - 1) / R::BM), dim3(64 * nw), lds, s, a);
 }
 
 template <class C>
 hipError_t launch_ctrl_logits_cfg(CtrlArgs a, hipStream_t s) {
   a.map = tile_map((a.Nc + C::BN - 1) / C::BN, (a.M + C::BM - 1) / C::BM,
                    (size_t)a.Nc * a.ldk * sizeof(typename C::DT));
-  return launch("ctrl", k_ctrl_logits<C>, dim3(grid_of(a.map)), dim3(C::NT), 0, s, a);
+  return launch("ctrl/logits", k_ctrl_logits<C>, dim3(grid_of(a.map)), dim3(C::NT), 0, s, a);
 }
 
 // The largest tile that still gives every CU one, else the smallest (the
@@ -1110,9 +1113,9 @@ hipError_t launch_ctrl(const CtrlArgs& a, hipStream_t s) {
     // rollout 90.8 -> 88.5 us against four blocks of each)
     const dim3 grid((unsigned)((a.M + 3) / 4));
     const bool x1 = a.N + 1 <= 256, x2 = a.N + 1 <= 512, l1 = a.Lc <= 256;
-    if (x1 && l1) return launch("ctrl", k_ctrl_rows<1, 1>, grid, dim3(256), 0, s, g);
-    if (x2 && l1) return launch("ctrl", k_ctrl_rows<2, 1>, grid, dim3(256), 0, s, g);
-    return launch("ctrl", k_ctrl_rows<kRowBlk, kRowBlk>, grid, dim3(256), 0, s, g);
+    if (x1 && l1) return launch("ctrl/rows", k_ctrl_rows<1, 1>, grid, dim3(256), 0, s, g);
+    if (x2 && l1) return launch("ctrl/rows", k_ctrl_rows<2, 1>, grid, dim3(256), 0, s, g);
+    return launch("ctrl/rows", k_ctrl_rows<kRowBlk, kRowBlk>, grid, dim3(256), 0, s, g);
   }
   // (otherwise the two-level controller runs on the kernels that stage whole logit rows)
   if (a.M <= kRdCtrlRows && nbtot <= 9 && a.N == 0) {
@@ -1165,10 +1168,10 @@ hipError_t launch_ctrl(const CtrlArgs& a, hipStream_t s) {
 hipError_t launch_ctrl_z(const CtrlArgs& a, hipStream_t s) {
   const dim3 grid((unsigned)((a.M + 15) / 16));
   const int nbw = (a.Nc / 16 + 3) / 4;
-  if (a.N > 0) return launch("ctrl", k_ctrl_z<3, true>, grid, dim3(256), 0, s, a);
-  if (nbw <= 1) return launch("ctrl", k_ctrl_z<1, false>, grid, dim3(256), 0, s, a);
-  if (nbw <= 2) return launch("ctrl", k_ctrl_z<2, false>, grid, dim3(256), 0, s, a);
-  return launch("ctrl", k_ctrl_z<3, false>, grid, dim3(256), 0, s, a);
+  if (a.N > 0) return launch("ctrl/z", k_ctrl_z<3, true>, grid, dim3(256), 0, s, a);
+  if (nbw <= 1) return launch("ctrl/z", k_ctrl_z<1, false>, grid, dim3(256), 0, s, a);
+  if (nbw <= 2) return launch("ctrl/z", k_ctrl_z<2, false>, grid, dim3(256), 0, s, a);
+  return launch("ctrl/z", k_ctrl_z<3, false>, grid, dim3(256), 0, s, a);
 }
 
 template hipError_t launch_ctrl<SrcX<float>>(const CtrlArgs&, hipStream_t);

@@ -682,13 +682,13 @@ long gate_tiles(const GatesArgs& a) {
 // the epilogue from the accumulators where the core has four 16-row blocks
 // per wave, else through the staged tile
 template <class C, typename DT, bool FEW = false>
-hipError_t launch_gates_cfg(GatesArgs a, hipStream_t s) {
+hipError_t launch_gates_cfg(const char* name, GatesArgs a, hipStream_t s) {
   a.map = tile_map((4 * a.H + C::BN - 1) / C::BN, (a.M + C::BM - 1) / C::BM,
                    (size_t)4 * a.H * a.ldk * sizeof(DT));
   if constexpr (IsGemmD<C>::value && C::NBW == 4)
-    return launch("gates", k_gates_direct<C, FEW>, dim3(grid_of(a.map)), dim3(C::NT), 0, s, a);
+    return launch(name, k_gates_direct<C, FEW>, dim3(grid_of(a.map)), dim3(C::NT), 0, s, a);
   else
-    return launch("gates", k_gates<C>, dim3(grid_of(a.map)), dim3(C::NT), 0, s, a);
+    return launch(name, k_gates<C>, dim3(grid_of(a.map)), dim3(C::NT), 0, s, a);
 }
 
 // Register-direct gate launch with tile R on nw waves (rd_fit).
@@ -699,7 +699,7 @@ hipError_t launch_gates_rd(GatesArgs a, int nw, hipStream_t s) {
   if (e != hipSuccess) return e;
   a.map = tile_map((4 * a.H + R::BN - 1) / R::BN, (a.M + R::BM - 1) / R::BM,
                    (size_t)4 * a.H * a.ldk * sizeof(DT));
-  return launch("gates", k_gates_rd<R>, dim3(grid_of(a.map)), dim3(64 * nw), lds, s, a);
+  return launch(R::BM == 16 ? "gates/rd16" : "gates/rd32", k_gates_rd<R>, dim3(grid_of(a.map)), dim3(64 * nw), lds, s, a);
 }
 
 // Gate tile of a call.  A launch takes about fixed + per * n, n the number of
@@ -744,21 +744,21 @@ hipError_t launch_gates(GatesArgs a, hipStream_t s) {
   if constexpr (bf) {
     if (few) {
       a.runs = rd_run<RD32>((int)a.ldk, rd_fit<RD32>((int)a.ldk));
-      if (c128x64 <= small) return launch_gates_cfg<typename Cf::Gates128x64, DT, true>(a, s);
-      if (c64x64 <= small) return launch_gates_cfg<typename Cf::Gates64x64, DT, true>(a, s);
-      return launch_gates_cfg<typename Cf::Gates64x32, DT, true>(a, s);
+      if (c128x64 <= small) return launch_gates_cfg<typename Cf::Gates128x64, DT, true>("gates/128x64", a, s);
+      if (c64x64 <= small) return launch_gates_cfg<typename Cf::Gates64x64, DT, true>("gates/64x64", a, s);
+      return launch_gates_cfg<typename Cf::Gates64x32, DT, true>("gates/64x32", a, s);
     }
     const float c128 = cost(gate_tiles<typename Cf::Gates128>(a), 2.5f, 10.2f);
     const long t256 = gate_tiles<typename Cf::Gates256>(a);
     const float c256 = cost(t256, 0.0f, 38.0f);
     if (c256 <= c128 && c256 <= small)  // sixteen waves from the second tile per CU on
-      return t256 > kCUs ? launch_gates_cfg<typename Cf::Gates256w16, DT>(a, s)
-                         : launch_gates_cfg<typename Cf::Gates256, DT>(a, s);
-    if (c128 <= small) return launch_gates_cfg<typename Cf::Gates128, DT>(a, s);
+      return t256 > kCUs ? launch_gates_cfg<typename Cf::Gates256w16, DT>("gates/256x256/16", a, s)
+                         : launch_gates_cfg<typename Cf::Gates256, DT>("gates/256x256/8", a, s);
+    if (c128 <= small) return launch_gates_cfg<typename Cf::Gates128, DT>("gates/128x128", a, s);
   }
-  if (c128x64 <= small) return launch_gates_cfg<typename Cf::Gates128x64, DT>(a, s);
-  if (c64x64 <= small) return launch_gates_cfg<typename Cf::Gates64x64, DT>(a, s);
-  return launch_gates_cfg<typename Cf::Gates64x32, DT>(a, s);
+  if (c128x64 <= small) return launch_gates_cfg<typename Cf::Gates128x64, DT>("gates/128x64", a, s);
+  if (c64x64 <= small) return launch_gates_cfg<typename Cf::Gates64x64, DT>("gates/64x64", a, s);
+  return launch_gates_cfg<typename Cf::Gates64x32, DT>("gates/64x32", a, s);
 }
 
 namespace {

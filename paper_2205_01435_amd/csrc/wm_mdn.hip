@@ -327,10 +327,12 @@ template <> struct Cfgs<bf16_t> {
   template <int Q> using Mdn128 = GemmD<bf16_t, Q, 2, 2, 4, 2>;  // eight waves
 };
 
+// name: of the launch, or null: "mdn" and its tile
 template <class C, typename DT, int KC, KSum ORD = KSum::Chain>
 hipError_t launch_mdn_cfg(const char* name, MdnArgs a, int ntiles, hipStream_t s) {
   a.map = tile_map(ntiles, (a.M + C::BM - 1) / C::BM, (size_t)a.Nm * a.ldh * sizeof(DT));
-  return launch(name, k_mdn<C, KC, ORD>, dim3(grid_of(a.map)), dim3(C::NT), 0, s, a);
+  constexpr const char* tile = C::BM == 16 ? "mdn/16" : C::BM == 32 ? "mdn/32" : C::BM == 64 ? "mdn/64" : "mdn/128";
+  return launch(name ? name : tile, k_mdn<C, KC, ORD>, dim3(grid_of(a.map)), dim3(C::NT), 0, s, a);
 }
 
 // Mixture tile of a call, chosen as the gate tiles are (launch_gates): the
@@ -384,7 +386,7 @@ hipError_t launch_mdn_q(const char* name, const MdnArgs& a, int ntiles, hipStrea
       hipError_t e = allow_lds(k_mdn_rd<R>, lds);
       if (e != hipSuccess) return e;
       b.map = tile_map(nt, (a.M + R::BM - 1) / R::BM, (size_t)a.Nm * a.ldh * sizeof(DT));
-      return launch(name, k_mdn_rd<R>, dim3(grid_of(b.map)), dim3(64 * nw), lds, s, b);
+      return launch(name ? name : "mdn/rd", k_mdn_rd<R>, dim3(grid_of(b.map)), dim3(64 * nw), lds, s, b);
     }
     b.runs = rd_run<R>((int)a.ldh, nw);
   }
@@ -432,7 +434,7 @@ hipError_t launch_mdn_k(const char* name, const MdnArgs& a, int Q, int ntiles, h
 
 template <typename DT>
 hipError_t launch_mdn(const MdnArgs& a, int Q, int ntiles, hipStream_t s) {
-  return launch_mdn_k<DT>("mdn", a, Q, ntiles, s);
+  return launch_mdn_k<DT>(nullptr, a, Q, ntiles, s);
 }
 
 // The comparison is of times at H 512, where mdn_cost's fp32 figures were

@@ -83,27 +83,44 @@ def test_ragged_shapes_reanchored(B, T, Z, H, A, K, dtype):
                                tau=1.3, dtype=dtype) <= parity.free_run_cap(B)
 
 
-# Staged controller tiles with one or two 64-output blocks (more than 1024
-# rows, at most 126 actions), on four and eight waves; the last row tile is
-# ragged.  nrows: rows re-anchored against the oracle (None: all).
+# Staged controller tiles (rows x outputs): more than 1024 rows, on four, eight
+# and sixteen waves; the last row tile is ragged.  fp32 rollouts run them where
+# the controller's h part has no room beside the mixture's columns (Z 8, H 368:
+# Z + 384 columns of a row of 384).  nrows: rows re-anchored against the oracle
+# (None: all).
 FEW_ACTIONS = [
-    (2048 + 7, 3, 32, 256, 60, 3, "bf16", None),   # 32-row tiles, one output block
-    (2048 + 7, 3, 32, 256, 100, 3, "bf16", None),  # 32-row tiles, two output blocks
-    (2048 + 7, 3, 32, 256, 100, 3, "fp32", None),  # the same on the fp32 core
-    (16384 + 3, 2, 32, 128, 60, 2, "bf16", 48),    # 64-row tiles
+    (2048 + 7, 3, 32, 256, 60, 3, "bf16", None, "32x64"),
+    (2048 + 7, 3, 32, 256, 100, 3, "bf16", None, "32x128"),
+    (2048 + 7, 3, 32, 256, 100, 3, "fp32", None, "z"),  # the h part beside the mixture
+    (2048 + 7, 3, 8, 368, 60, 3, "fp32", 96, "32x64"),
+    (2048 + 7, 3, 8, 368, 100, 3, "fp32", 96, "32x128"),
+    (2048 + 7, 3, 8, 368, 180, 3, "fp32", 96, "32x192"),
+    (2048 + 7, 3, 8, 368, 300, 3, "fp32", 96, "32x320"),
+    (2048 + 7, 3, 32, 256, 180, 3, "bf16", 96, "32x192"),
+    (16384 + 3, 2, 32, 128, 60, 2, "bf16", 48, "64x64"),
+    (16384 + 3, 2, 32, 128, 100, 2, "bf16", 48, "64x128"),
+    (16384 + 3, 2, 32, 128, 180, 2, "bf16", 48, "64x192"),
+    (16384 + 3, 2, 32, 128, 300, 2, "bf16", 48, "64x320"),
 ]
 
 
-@pytest.mark.parametrize("B,T,Z,H,A,K,dtype,nrows", FEW_ACTIONS)
-def test_few_action_controller_tiles(B, T, Z, H, A, K, dtype, nrows, monkeypatch):
+@pytest.mark.parametrize("B,T,Z,H,A,K,dtype,nrows,tile", FEW_ACTIONS)
+def test_few_action_controller_tiles(B, T, Z, H, A, K, dtype, nrows, tile, monkeypatch):
     say("few-action controller tiles", B, T, Z, H, A, K, dtype)
     monkeypatch.setenv("WM_PERSISTENT", "0")  # the multi-launch kernels
     w, inp = _case(B, T, Z, H, A, K, dtype)
     mask = inp["mask"].copy()
     mask[B - 2] = 0  # a row without a valid action, in the ragged tile
     m = wmlib.pack(inp["weights"], Z, H, A, K, dtype)
-    b = wmlib.rollout(m, _t(inp["z0"]), _t(mask), T=T, seed=37, tau=1.0, done=True, trace=True)
-    torch.cuda.synchronize()
+    wmlib.profile_reset()
+    wmlib.profile_enable("ctrl")
+    try:
+        b = wmlib.rollout(m, _t(inp["z0"]), _t(mask), T=T, seed=37, tau=1.0, done=True, trace=True)
+        torch.cuda.synchronize()
+        assert wmlib.profile_read("ctrl/" + tile)[1] == wmlib.profile_read("ctrl")[1] == T + 1
+    finally:
+        wmlib.profile_enable(None)
+        wmlib.profile_reset()
     rows = np.arange(B) if nrows is None else np.unique(
         np.concatenate([np.linspace(0, B - 1, nrows).astype(np.int64), np.arange(B - 6, B)]))
     ri = torch.from_numpy(rows).cuda()
