@@ -386,7 +386,9 @@ wm_status wm_profile_reset(void);
  *   out[8..10]       0, then the mean work of gates and mdn
  *   out[11], out[12] set-up before step 0 and the tail after the last step
  *                    (max work)
- * Slots 6, 7, 10 and 12 are 0 for the NLL recurrence.
+ * Slots 6, 7, 10 and 12 are 0 for the NLL recurrence.  While phases are timed
+ * the persistent kernel runs the recurrence of every likelihood pass it can
+ * serve, also where the call otherwise runs one launch per step.
  */
 wm_status wm_profile_phases(int32_t on);
 wm_status wm_profile_phases_read(double *out, int32_t n);

@@ -1035,7 +1035,7 @@ template <> struct Cfgs<bf16_t> {
   static constexpr int WIDE_BKC = 128;
 };
 
-// The 256-row tiles serve calls that still give every CU at least one tile.
+// The 64-row controller tiles serve calls that give every CU at least one.
 constexpr long kXLTiles = 256;
 
 // The register-direct controller serves calls with at most this many rows,
@@ -1108,9 +1108,10 @@ hipError_t launch_ctrl(const CtrlArgs& a, hipStream_t s) {
     else if (nbw <= 33) e = launch_ctrl_wide<S, 33, 1>(g, s);
     else return hipErrorInvalidValue;
     if (e != hipSuccess) return e;
-    // as many blocks per lane as the rows have: a load that only reads past
-    // the row takes as long as the others (B 4096, N 288, L 200: a step of the
-    // rollout 90.8 -> 88.5 us against four blocks of each)
+    // one block per lane of either row where it fits, two of the xfers', else
+    // four of both: a load that only reads past the row takes as long as the
+    // others (B 4096, N 288, L 200: a step of the rollout 90.8 -> 88.5 us
+    // against four blocks of each)
     const dim3 grid((unsigned)((a.M + 3) / 4));
     const bool x1 = a.N + 1 <= 256, x2 = a.N + 1 <= 512, l1 = a.Lc <= 256;
     if (x1 && l1) return launch("ctrl/rows", k_ctrl_rows<1, 1>, grid, dim3(256), 0, s, g);

@@ -11,10 +11,10 @@ namespace wm {
 // ---------------------------------------------------------------------------
 // fp32 products on the bf16 matrix unit.  A float is the exact sum of three
 // bf16 values, x = h + m + l (8 significant bits each, rounded to nearest, so
-// that the signs carry the rest: |m| <= 2^-9 |x|, |l| <= 2^-18 |x|), and six
+// that the signs carry the rest: |m| <= 2^-8 |x|, |l| <= 2^-17 |x|), and six
 // of the nine products of two such sums, accumulated in fp32, leave out only
-// m l + l m + l l, at most 2^-26 of the product: less than the rounding of
-// one fp32 product (2^-25).  At 16 times the fp32 MFMA rate the six cost 3/8
+// m l + l m + l l, at most about 2^-24 of the product: as much as the rounding
+// of one fp32 product.  At 16 times the fp32 MFMA rate the six cost 3/8
 // of the fp32 instruction's time.  Error against 64 bits of a K 512 dot
 // product (uniform operands, fp32 accumulation either way): 3.3e-7 of the
 // result's norm, 4.1e-7 with the fp32 MFMA; K 1056 4.9e-7 and 5.8e-7.

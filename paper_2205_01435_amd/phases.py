@@ -2,8 +2,9 @@
 
     python3 -m paper_2205_01435_amd.phases --workload tiny_rollout --out profiles/<file>.md
 
-runs one workload served by the persistent kernels (the tiny and medium
-dream rollouts, the NLL pass) with phase stamps on, a few warm-up calls and
+runs one workload that the persistent kernels can serve (the tiny and medium
+dream rollouts; the NLL pass, whose recurrence they run only while phases are
+timed and otherwise one launch per step does) with phase stamps on, a few warm-up calls and
 then ``--calls`` stamped calls, and writes the median of each slot over the
 calls (microseconds per step) as a short markdown summary.  The stamps are
 the device's constant-rate clock, taken by one lane of each work-group at
@@ -80,6 +81,9 @@ def summary(name: str, res: dict, calls: int) -> str:
              "", f"Command: `{cmd}`", "",
              f"Median over {calls} stamped calls of each slot, microseconds per step (set-up and tail: per call).",
              "", "| slot | us | what |", "|---|---:|---|"]
+    if w.kind == "nll":
+        lines[4:4] = ["The persistent kernel serves this pass only while phases are timed: unstamped calls of these",
+                      "sizes run one launch per step on split products.", ""]
     for k in wmlib.PHASE_SLOTS[1:]:
         if k in ("ctrl", "ctrl_barrier", "ctrl_mean"):
             continue  # the controller decisions run inside gates(t)
